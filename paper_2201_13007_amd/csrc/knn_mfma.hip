@@ -9,17 +9,10 @@
 // product) is then formed in 32-bit integers and rounded once to float, which is the key
 // the scan produces, bit for bit.
 //
-// Work split.  A workgroup of four wavefronts owns MQ = 64 queries, whose bf16 rows stay
-// in registers as the A operands (4 row blocks x d/32 k-steps).  The base streams in
-// tiles of MT = 64 rows; wavefront w multiplies rows 16w .. 16w+15 of each tile against
-// all 64 queries, loading its B operands from memory straight into a ring of registers
-// that runs one or two tiles ahead of the products.
-//
-// Selection.  A product passes a cheap integer test first: u <= B_q with u = |x|^2 - 2 q.x
-// and B_q = T_q - |q|^2, where T_q bounds from above every integer distance whose float
-// rounding does not exceed the query's current k-th distance.  Only passing products
-// build a 64-bit key and enter the query's LDS buffer, which is sorted and merged into
-// the query's top-k list as in the scan.
+// Both forms run the staged product-and-filter of knn_tile.h.  A product passes a cheap
+// test first: round(|x|^2 - 2 q.x) <= round(B_q) with B_q = T_q - |q|^2, where T_q bounds
+// from above every integer distance whose float rounding does not exceed the query's
+// threshold key; only passing products build a 64-bit key and are compared with it.
 //
 // Float data (d <= 1024, k <= 96; above d = 128 the chunks of 32 dimensions are loaded per
 // tile instead of held in registers).  Each coordinate is split into bf16 parts x = h + l + r
@@ -35,9 +28,12 @@
 // that exceeds the k-th exact key, none can enter the k best, and the result is the
 // scan's, bit for bit.  The queries that cannot show that margin (ties within the bound)
 // are listed and rescored by the scan alone.
-#include "knn_select.h"
+#include "knn_tile.h"
 
-#include <climits>
+#include <algorithm>
+#include <cmath>
+#include <numeric>
+#include <vector>
 
 namespace sa {
 namespace {
@@ -51,206 +47,201 @@ constexpr int MQ = 64;                 // queries per workgroup
 constexpr int MT = 64;                 // base rows per tile
 constexpr int MNT = 256;               // four wavefronts
 constexpr int MBUF = 128;              // candidates buffered per query; flushed when > MBUF - MT
-// the integer kernel's buffer: with its sorted lists k keys long (not rounded up), a
-// workgroup then takes 76 KB of LDS at k = 65 and two fit on a CU (at 128 and a rounded
-// list, 133 KB: one workgroup, one wavefront per SIMD, nothing to hide a barrier or a load)
-constexpr int MBUF_I = 80;
-constexpr int32_t NORM_PAD = 1 << 30;  // norm of padding rows
+
+using knn_tile::SelArgs;
+using knn_tile::TileArgs;
+using knn_tile::TROWS;
 
 struct PrepArgs {
     const float *x;
-    int64_t n, ld, rows;  // rows: n rounded up to the tile size
-    int32_t d, dpad, metric;
-    __bf16 *out;          // rows x dpad
-    int32_t *norm;        // rows
+    int64_t n, ld, rows;   // rows: n rounded up to whole tiles (base) or workgroups (queries)
+    int32_t d, ks;
+    int64_t ntile, mul;    // base: position 64 t + o holds row o * ntile + (t * mul) % ntile; mul 0: its own row
+    int32_t metric;
+    unsigned char *out;    // blocks in operand order (knn_tile.h); null: only the check
+    float *norm;           // base: |x|^2 (exact integers; 0 for the inner product), +inf for padding
+    int32_t *qnorm;        // queries: |q|^2
+    int32_t *tab;
     int32_t *bad;
+    int32_t *max_norm;     // largest |x|^2 (null: not wanted)
+    float scale;           // the copy holds scale * x (a power of two of either sign)
 };
 
-// One wavefront per row: the bf16 copy (zero padded to dpad columns and `rows` rows), the
-// exact integer squared norm (0 for the inner product, NORM_PAD for padding rows), and a
-// flag raised by any value that is not an integer in [-255, 255] (NaN included).
+// One wavefront per block of 16 rows: the bf16 copy in operand order (zero padded), the
+// exact integer squared norms, and a flag raised by any value that is not an integer in
+// [-255, 255] (NaN included); once it is raised the remaining blocks do nothing.
 __global__ void __launch_bounds__(256) knn_prep_kernel(PrepArgs P)
 {
     const int lane = __lane_id();
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= P.rows) return;
+    const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blk * 16 >= P.rows || __hip_atomic_load(P.bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    const int r = lane & 15, g = lane >> 4;
+    int64_t row = blk * 16 + r;
+    if (P.mul) {
+        const int64_t t = blk >> 2, off = (t * P.mul) % P.ntile;
+        if ((blk & 3) == 0 && lane == 0) P.tab[t] = (int32_t)off;
+        row = ((blk & 3) * 16 + r) * P.ntile + off;
+    }
+    const float *src = P.x + row * P.ld;
     int sum = 0;
     bool bad = false;
-    for (int c = lane; c < P.dpad; c += 64) {
-        float v = 0.f;
-        if (row < P.n && c < P.d) v = P.x[row * P.ld + c];
-        const bool ok = fabsf(v) <= 255.f && v == rintf(v);
-        bad |= !ok;
-        const int iv = ok ? (int)v : 0;
-        sum += iv * iv;
-        P.out[row * P.dpad + c] = (__bf16)(ok ? v : 0.f);
+    for (int ks = 0; ks < P.ks; ++ks) {
+        const int c = 32 * ks + 8 * g;
+        float4 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            v[h] = row < P.n && c + 4 * h < P.d ? *reinterpret_cast<const float4 *>(src + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float f[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+        knn_tile::bf16x8 o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bool ok = fabsf(f[i]) <= 255.f && f[i] == rintf(f[i]);
+            bad |= !ok;
+            const int iv = ok ? (int)f[i] : 0;
+            sum += iv * iv;
+            o[i] = (__bf16)(ok ? P.scale * f[i] : 0.f);
+        }
+        if (P.out) *reinterpret_cast<knn_tile::bf16x8 *>(P.out + (blk * P.ks + ks) * 1024 + 16 * lane) = o;
     }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
     if (bad) atomicOr(P.bad, 1);
-    if (lane == 0) P.norm[row] = row < P.n ? (P.metric == SA_L2 ? sum : 0) : NORM_PAD;
+    if (P.max_norm) {
+        int mx = sum;
+        for (int o = 1; o < 16; o <<= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+        // (most blocks see a larger value there already: one address, few atomics)
+        if (lane == 0 && mx > __hip_atomic_load(P.max_norm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(P.max_norm, mx);
+    }
+    if (g == 0 && P.out) {
+        const int nv = P.metric == SA_L2 ? sum : 0;
+        if (P.qnorm) P.qnorm[blk * 16 + r] = nv;
+        else P.norm[blk * 16 + r] = row < P.n ? (float)nv : __builtin_inff();
+    }
 }
 
-// Upper bound, minus |q|^2, on the integer distances whose float rounding is at most the
-// distance of key thr.  Distances here are roundings of integers, so the float is
-// integral; below 2^24 it is exact, above it one unit in the last place covers every
-// integer that rounds down onto it.  INT_MAX while the list is not full.
-__device__ inline int prefilter_bound(uint64_t thr, int32_t qnorm)
+// Results of the integer form: the first k of each query's list; the queries whose buffers
+// overflowed are listed for the scan.
+__global__ void knn_emit_kernel(const uint64_t *list, int kt, const int32_t *over, int64_t nq, int64_t q0, int k,
+                                int32_t *ids, float *dists, int32_t *failed, int32_t *failed_list)
 {
-    if (thr == KEY_EMPTY) return INT_MAX;
-    const float f = key_dist(thr);
-    int64_t t = (int64_t)f;
-    const float a = fabsf(f);
-    if (a >= 16777216.f) t += int64_t(1) << ((int)((__float_as_uint(a) >> 23) & 0xFF) - 127 - 23);
-    t -= qnorm;
-    return t > INT_MAX ? INT_MAX : (int)t;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nq * k) return;
+    const int64_t q = i / k, j = i - q * k;
+    if (over[q]) {
+        if (j == 0) failed_list[atomicAdd(failed, 1)] = (int32_t)(q0 + q);
+        return;
+    }
+    const uint64_t key = list[q * kt + j];
+    const bool ok = key != KEY_EMPTY;
+    ids[(q0 + q) * k + j] = ok ? key_id(key) : -1;
+    dists[(q0 + q) * k + j] = ok ? key_dist(key) : __builtin_inff();
 }
 
-struct MArgs {
-    const __bf16 *xb;    // base rows, xrows x dpad
-    const int32_t *xn;   // their norms
-    const __bf16 *qb;    // query rows, a multiple of MQ rows x dpad
-    const int32_t *qn;
-    int64_t n, nq, xrows;
-    int32_t dpad, k, kpad, exclude_self;
-    int32_t *ids;
-    float *dists;
+// ---------------------------------------------------------------- stages (host)
+
+struct Stage {
+    int t0, t1, splits, capseg;
+    int wave_cap;   // keys of a selection by one wavefront; 0: by a workgroup
 };
 
-template <int KS, bool L2>
-__global__ void __launch_bounds__(MNT) knn_mfma_kernel(MArgs A)
+constexpr int QCHUNK = 65536;   // queries per pass over the base: bounds the buffers at about half a gigabyte
+
+// The stages of one pass: a first sample of the tiles, then each up to r times as many.  A
+// stage lets about kt (r - 1) rows pass per query.  Few queries are bound by launches (a
+// product and a selection each stage, some 15 us): a sample of 1024 rows and r up to 16;
+// many by the keys (each passing one breaks the product loop for some hundred cycles and
+// is sorted): 256 rows up to kt = 64, 512 up to 128, and r up to 6.  Both within what a
+// selection holds.  Each stage is split over two to four times the workgroups that the
+// device holds (1024 to 2048), which bounds what an uneven last round costs.
+std::vector<Stage> plan_stages(int ntile, int kt, int64_t nq, int qtiles, int unit)
 {
-    constexpr int NB = KS <= 4 ? 3 : 2;  // register ring: tiles in flight + the one in use
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint64_t *top = reinterpret_cast<uint64_t *>(smem);   // [MQ][kpad] sorted best keys
-    uint64_t *buf = top + (size_t)MQ * A.kpad;             // [MQ][MBUF_I] unsorted candidates
-    uint64_t *thr = buf + (size_t)MQ * MBUF_I;             // [MQ] k-th key (or empty)
-    int *cnt = reinterpret_cast<int *>(thr + MQ);          // [MQ] buffered candidates
-    int *len = cnt + MQ;                                   // [MQ] length of top
-    int *bnd = len + MQ;                                   // [MQ] B_q of the prefilter
-    int *qns = bnd + MQ;                                   // [MQ] |q|^2
-    int *need = qns + MQ;  // 1 + index of the last tile in which a buffer passed MBUF_I - MT
-
-    const int tid = threadIdx.x, lane = __lane_id(), w = tid >> 6;
-    const int64_t q0 = (int64_t)blockIdx.x * MQ;
-    for (int i = tid; i < MQ; i += MNT) {
-        cnt[i] = 0;
-        len[i] = 0;
-        thr[i] = KEY_EMPTY;
-        bnd[i] = q0 + i < A.nq ? INT_MAX : INT_MIN;  // padding queries take nothing
-        qns[i] = A.qn[q0 + i];
-    }
-    if (tid == 0) *need = 0;
-
-    bf16x8 a[4][KS];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-        const __bf16 *p = A.qb + (q0 + rb * 16 + (lane & 15)) * A.dpad + 8 * (lane >> 4);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) a[rb][ks] = *reinterpret_cast<const bf16x8 *>(p + ks * 32);
-    }
-    __syncthreads();
-    // lane holds output rows 4 (lane / 16) + r of each row block, column lane % 16
-    int bq[4][4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bq[rb][r] = bnd[rb * 16 + 4 * (lane >> 4) + r];
-
-    const int64_t ntile = A.xrows / MT;
-    bf16x8 b[NB][KS];
-    int bn[NB];
-#pragma unroll
-    for (int j = 0; j < NB - 1; ++j) {
-        const int64_t row = (j < ntile ? j : ntile - 1) * MT + 16 * w + (lane & 15);
-        const __bf16 *p = A.xb + row * A.dpad + 8 * (lane >> 4);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) b[j][ks] = *reinterpret_cast<const bf16x8 *>(p + ks * 32);
-        bn[j] = A.xn[row];
-    }
-
-    for (int64_t t0 = 0; t0 < ntile; t0 += NB) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int64_t t = t0 + j;
-            if (t >= ntile) break;
-            {
-                // refill the slot freed by the previous tile; past the end, reload the last tile
-                const int jn = (j + NB - 1) % NB;
-                const int64_t tn = t + NB - 1 < ntile ? t + NB - 1 : ntile - 1;
-                const int64_t row = tn * MT + 16 * w + (lane & 15);
-                const __bf16 *p = A.xb + row * A.dpad + 8 * (lane >> 4);
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) b[jn][ks] = *reinterpret_cast<const bf16x8 *>(p + ks * 32);
-                bn[jn] = A.xn[row];
-            }
-            f32x4 acc[4];
-#pragma unroll
-            for (int rb = 0; rb < 4; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-                    acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb][ks], b[j][ks], acc[rb], 0, 0, 0);
-            const int64_t col = t * MT + 16 * w + (lane & 15);
-            const int nx = bn[j];
-#pragma unroll
-            for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int dneg = (int)(-acc[rb][r]);  // -q.x, exact
-                    const int u = L2 ? nx + 2 * dneg : dneg;
-                    if (u <= bq[rb][r]) {
-                        const int row = rb * 16 + 4 * (lane >> 4) + r;
-                        if (col < A.n && !(A.exclude_self && col == q0 + row)) {
-                            const uint64_t key = make_key((float)(qns[row] + u), (int32_t)col);
-                            if (key < thr[row]) {
-                                const int pos = atomicAdd(&cnt[row], 1);
-                                buf[(size_t)row * MBUF_I + pos] = key;
-                                if (pos + 1 > MBUF_I - MT) *need = (int)(t + 1);
-                            }
-                        }
-                    }
-                }
-            __syncthreads();
-            // every wavefront reads the same value: a later tile can only write after the
-            // barrier that follows a flush
-            const bool last = t + 1 == ntile;
-            if (*need == (int)(t + 1) || last) {
-                for (int qr = w; qr < MQ; qr += MNT / 64) {
-                    const int c = cnt[qr];
-                    if (c == 0) continue;
-                    flush_query(top + (size_t)qr * A.kpad, &len[qr], buf + (size_t)qr * MBUF_I, c, A.k);
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane == 0) {
-                        cnt[qr] = 0;
-                        if (len[qr] >= A.k) {
-                            const uint64_t th = top[(size_t)qr * A.kpad + A.k - 1];
-                            thr[qr] = th;
-                            bnd[qr] = prefilter_bound(th, qns[qr]);
-                        }
-                    }
-                }
-                __syncthreads();
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) bq[rb][r] = bnd[rb * 16 + 4 * (lane >> 4) + r];
-            }
+    std::vector<Stage> st;
+    const bool many = nq >= 4096;
+    const int m0 = std::min(ntile, many && kt <= 64 ? 4 : many && kt <= 128 ? 8 : 16);
+    const double rmax = std::min(many ? 6.0 : 16.0, std::max(3.0, 1024.0 / kt));
+    const double ratio = (double)ntile / m0;
+    const int ns = ratio > 1.0 ? std::max(1, (int)std::ceil(std::log(ratio) / std::log(rmax))) : 0;
+    const double r = ns > 0 ? std::pow(ratio, 1.0 / ns) : 1.0;
+    int t0 = 0;
+    for (int i = 0; i <= ns; ++i) {
+        int t1 = i == ns ? ntile : std::min(ntile, (int)(m0 * std::pow(r, i) / 2.0 + 0.5) * 2);
+        if (i == 0) t1 = m0;
+        if (t1 <= t0) continue;
+        const int ntl = t1 - t0;
+        const int target = (int64_t)ntl * qtiles >= 65536 ? 2048 : 1024;
+        Stage s{t0, t1, 1, 0, 0};
+        s.splits = std::max(1, std::min({target / std::max(1, qtiles), ntl / (2 * unit), knn_tile::MAX_SPLITS}));
+        double keys = (double)ntl * TROWS;   // a selection's keys, and its room for them
+        if (t0 > 0) {
+            // room for twice the expected keys and six deviations
+            const double all = 2.0 * kt * ((double)ntl / t0), mu = all / s.splits;
+            const int most = ((ntl + s.splits - 1) / s.splits + unit) * TROWS;
+            s.capseg = std::min(most, ((int)(mu + 6.0 * std::sqrt(mu) + 16.0) + 1) / 2 * 2);
+            keys = kt + all + 6.0 * std::sqrt(all);
         }
-    }
-    for (int i = tid; i < MQ * A.k; i += MNT) {
-        const int qr = i / A.k, j = i % A.k;
-        const int64_t qg = q0 + qr;
-        if (qg >= A.nq) continue;
-        if (j < len[qr]) {
-            const uint64_t key = top[(size_t)qr * A.kpad + j];
-            A.ids[qg * A.k + j] = key_id(key);
-            A.dists[qg * A.k + j] = key_dist(key);
-        } else {
-            A.ids[qg * A.k + j] = -1;
-            A.dists[qg * A.k + j] = __builtin_inff();
+        if (many && s.splits <= 64 && keys <= 1024.0) {
+            s.wave_cap = 64;
+            while (s.wave_cap < keys) s.wave_cap *= 2;
         }
+        st.push_back(s);
+        t0 = t1;
     }
+    return st;
+}
+
+// buffer bytes of a stage for nq queries
+size_t stage_bytes(const Stage &s, int64_t nq)
+{
+    return s.t0 == 0 ? (size_t)nq * (s.t1 - s.t0) * TROWS * 8 : (size_t)nq * s.splits * s.capseg * 8;
+}
+
+// odd multiplier near 0.618 ntile that is prime to ntile: the tile permutation
+int64_t tile_mul(int64_t ntile)
+{
+    int64_t m = std::max<int64_t>(1, (int64_t)(0.6180339887498949 * (double)ntile));
+    while (std::gcd(m, ntile) != 1) ++m;
+    return m;
+}
+
+struct DeviceBlock {
+    void *p = nullptr;
+    ~DeviceBlock()
+    {
+        if (p) (void)hipFree(p);
+    }
+};
+
+size_t align256(size_t v) { return (v + 255) / 256 * 256; }
+
+using TKernel = void (*)(TileArgs);
+
+// The stages of one chunk of queries (A holds everything but the stage's own fields).
+int run_stages(TileArgs A, const std::vector<Stage> &st, TKernel kern, size_t lds, int kt, uint64_t *list, uint64_t *thr,
+               int32_t *over, hipStream_t s)
+{
+    bool first = true;
+    for (const Stage &g : st) {
+        A.t0 = g.t0; A.t1 = g.t1; A.splits = g.splits; A.capseg = g.capseg; A.dense = g.t0 == 0 ? 1 : 0;
+        A.thr = thr;
+        const int64_t jobs = (int64_t)g.splits * A.qtiles, per = (jobs + 7) / 8;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per)), dim3(MNT), lds, s, A);
+        SA_HIP(hipGetLastError());
+        SelArgs S;
+        S.buf = A.buf; S.cnt = A.cnt; S.splits = g.splits; S.capseg = g.capseg;
+        S.dense_rows = A.dense ? (g.t1 - g.t0) * TROWS : 0;
+        S.kt = kt; S.nq = A.nq; S.first = first ? 1 : 0;
+        S.list = list; S.thr = thr; S.over = over;
+        S.cap = g.wave_cap;
+        if (g.wave_cap > 0)
+            hipLaunchKernelGGL(knn_tile::knn_select_wave_kernel, dim3((unsigned)((A.nq + 3) / 4)), dim3(256),
+                               32 * (size_t)g.wave_cap, s, S);
+        else
+            hipLaunchKernelGGL(knn_tile::knn_select_kernel, dim3((unsigned)A.nq), dim3(256), 0, s, S);
+        SA_HIP(hipGetLastError());
+        first = false;
+    }
+    return SA_OK;
 }
 
 // ---------------------------------------------------------------- float data
@@ -677,38 +668,29 @@ FKernel pick_float_kernel(int ks, int metric)
     }
 }
 
-using MKernel = void (*)(MArgs);
-
-template <int KS>
-MKernel pick(int metric)
+// the resident kernel of ks k-steps for wq wavefronts of queries
+template <int KS, int NP, int FORM>
+TKernel pick_wq(int wq)
 {
-    return metric == SA_L2 ? knn_mfma_kernel<KS, true> : knn_mfma_kernel<KS, false>;
+    return wq == 4 ? knn_tile::knn_tile_kernel<KS, NP, 4, FORM>
+                   : wq == 2 ? knn_tile::knn_tile_kernel<KS, NP, 2, FORM> : knn_tile::knn_tile_kernel<KS, NP, 1, FORM>;
 }
 
-MKernel pick_kernel(int ks, int metric)
+template <int FORM>
+TKernel pick_int_kernel(int ks, int wq)
 {
     switch (ks) {
-    case 1: return pick<1>(metric);
-    case 2: return pick<2>(metric);
-    case 3: return pick<3>(metric);
-    case 4: return pick<4>(metric);
-    case 6: return pick<6>(metric);
-    case 8: return pick<8>(metric);
+    case 1: return pick_wq<1, 1, FORM>(wq);
+    case 2: return pick_wq<2, 1, FORM>(wq);
+    case 3: return pick_wq<3, 1, FORM>(wq);
+    case 4: return pick_wq<4, 1, FORM>(wq);
+    case 6: return pick_wq<6, 1, FORM>(wq);
+    case 8: return pick_wq<8, 1, FORM>(wq);
     default: return nullptr;
     }
 }
 
-struct DeviceBlock {
-    void *p = nullptr;
-    ~DeviceBlock()
-    {
-        if (p) (void)hipFree(p);
-    }
-};
-
-size_t align256(size_t v) { return (v + 255) / 256 * 256; }
-
-// Runs the matrix-core path if every coordinate qualifies; *ran tells whether it did.
+// The integer path if every coordinate qualifies; *ran tells whether it did.  Synchronous.
 int launch_knn_mfma(const float *base, int64_t n, int32_t d, int64_t ld, const float *queries, int64_t nq,
                     int64_t ldq, int32_t k, int32_t metric, int32_t exclude_self, int32_t *ids, float *dists,
                     bool *ran, hipStream_t s)
@@ -717,54 +699,98 @@ int launch_knn_mfma(const float *base, int64_t n, int32_t d, int64_t ld, const f
     int ks = (d + 31) / 32;
     if (ks == 5) ks = 6;
     if (ks == 7) ks = 8;
-    const int dpad = 32 * ks;
-    const int64_t xrows = (n + MT - 1) / MT * MT;
-    const bool shared_q = queries == base && ldq == ld && nq <= n;
-    const int64_t qrows = shared_q ? xrows : (nq + MQ - 1) / MQ * MQ;
-    const size_t xb_bytes = align256((size_t)xrows * dpad * 2), xn_bytes = align256((size_t)xrows * 4);
-    const size_t qb_bytes = shared_q ? 0 : align256((size_t)qrows * dpad * 2);
-    const size_t qn_bytes = shared_q ? 0 : align256((size_t)qrows * 4);
+    const int64_t ntile = (n + 2 * TROWS - 1) / (2 * TROWS) * 2;
+    const int kt = std::max(k, 24);   // (a threshold from fewer keys strays too far)
     DeviceBlock mem;
-    if (hipMalloc(&mem.p, xb_bytes + xn_bytes + qb_bytes + qn_bytes + 256) != hipSuccess) {
+    const size_t xb = align256((size_t)ntile * 4 * ks * 1024), xn_b = align256((size_t)ntile * TROWS * 4);
+    const size_t tab_b = align256((size_t)ntile * 4), fl_b = align256((size_t)nq * 4);
+    int64_t qc = std::min<int64_t>(nq, QCHUNK), qpad = 0;
+    int wq = 4, qtiles = 0;
+    std::vector<Stage> st;
+    size_t buf_b = 0, cnt_b = 0, qb = 0, qn_b = 0, list_b = 0;
+    for (;; qc = std::max<int64_t>(1024, qc / 2)) {
+        // wavefronts of 64 queries per workgroup: as many as there are queries for
+        wq = qc <= 64 ? 1 : qc <= 128 ? 2 : 4;
+        qtiles = (int)((qc + 64 * wq - 1) / (64 * wq));
+        qpad = (int64_t)qtiles * 64 * wq;
+        st = plan_stages((int)ntile, kt, qc, qtiles, 1);
+        buf_b = cnt_b = 0;
+        for (const Stage &g : st) {
+            buf_b = std::max(buf_b, align256(stage_bytes(g, qc)));
+            cnt_b = std::max(cnt_b, align256((size_t)qc * g.splits * 4));
+        }
+        qb = align256((size_t)qpad * ks * 64);
+        qn_b = align256((size_t)qpad * 4);
+        list_b = align256((size_t)qc * kt * 8);
+        const size_t total = xb + xn_b + tab_b + fl_b + buf_b + cnt_b + qb + 2 * qn_b + list_b + align256((size_t)qc * 8) + 256;
+        if (hipMalloc(&mem.p, total) == hipSuccess) break;
         (void)hipGetLastError();
         mem.p = nullptr;
-        return set_error(SA_ENOMEM, "hipMalloc of the bf16 copies failed");
+        if (qc <= 1024) return set_error(SA_ENOMEM, "hipMalloc of the bf16 copies failed");
     }
     unsigned char *m = static_cast<unsigned char *>(mem.p);
-    __bf16 *xb = reinterpret_cast<__bf16 *>(m);
-    int32_t *xn = reinterpret_cast<int32_t *>(m + xb_bytes);
-    __bf16 *qb = shared_q ? xb : reinterpret_cast<__bf16 *>(m + xb_bytes + xn_bytes);
-    int32_t *qn = shared_q ? xn : reinterpret_cast<int32_t *>(m + xb_bytes + xn_bytes + qb_bytes);
-    int32_t *bad = reinterpret_cast<int32_t *>(m + xb_bytes + xn_bytes + qb_bytes + qn_bytes);
+    unsigned char *xt = m; m += xb;
+    float *xn = reinterpret_cast<float *>(m); m += xn_b;
+    int32_t *tab = reinterpret_cast<int32_t *>(m); m += tab_b;
+    int32_t *failed_list = reinterpret_cast<int32_t *>(m); m += fl_b;
+    uint64_t *buf = reinterpret_cast<uint64_t *>(m); m += buf_b;
+    int32_t *cnt = reinterpret_cast<int32_t *>(m); m += cnt_b;
+    unsigned char *qt = m; m += qb;
+    int32_t *qn = reinterpret_cast<int32_t *>(m); m += qn_b;
+    int32_t *over = reinterpret_cast<int32_t *>(m); m += qn_b;
+    uint64_t *list = reinterpret_cast<uint64_t *>(m); m += list_b;
+    uint64_t *thr = reinterpret_cast<uint64_t *>(m); m += align256((size_t)qc * 8);
+    // [0] not integer data, [1] overflowed queries, [2] largest |x|^2, [3] largest |q|^2
+    int32_t *flags = reinterpret_cast<int32_t *>(m);
 
-    SA_HIP(hipMemsetAsync(bad, 0, sizeof(int32_t), s));
-    PrepArgs P{base, n, ld, xrows, d, dpad, metric, xb, xn, bad};
-    hipLaunchKernelGGL(knn_prep_kernel, dim3((unsigned)((xrows + 3) / 4)), dim3(256), 0, s, P);
-    SA_HIP(hipGetLastError());
-    if (!shared_q) {
-        PrepArgs Q{queries, nq, ldq, qrows, d, dpad, metric, qb, qn, bad};
-        hipLaunchKernelGGL(knn_prep_kernel, dim3((unsigned)((qrows + 3) / 4)), dim3(256), 0, s, Q);
-        SA_HIP(hipGetLastError());
-    }
-    int32_t flag = 0;
-    SA_HIP(hipMemcpyAsync(&flag, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    SA_HIP(hipMemsetAsync(flags, 0, 16, s));
+    const float sgn = metric == SA_L2 ? -2.f : -1.f;
+    // (queries are stored times the factor of the distance; the unfolded kernels undo it
+    // with a factor of one: their products then carry it already)
+    auto prep = [&](const float *x, int64_t rows, int64_t stride, int64_t padded, int64_t mul, unsigned char *out,
+                    int32_t *qnorm, int32_t *mx) {
+        PrepArgs P{x, rows, stride, padded, d, ks, ntile, mul, metric, out, xn, qnorm, tab, flags, mx, qnorm ? sgn : 1.f};
+        hipLaunchKernelGGL(knn_prep_kernel, dim3((unsigned)((padded / 16 + 3) / 4)), dim3(256), 0, s, P);
+        return hipGetLastError();
+    };
+    const bool self = queries == base && ldq == ld && nq <= n;
+    SA_HIP(prep(base, n, ld, ntile * TROWS, tile_mul(ntile), xt, nullptr, flags + 2));
+    if (nq <= qc) SA_HIP(prep(queries, nq, ldq, qpad, 0, qt, qn, flags + 3));
+    else if (!self) SA_HIP(prep(queries, nq, ldq, (nq + 15) / 16 * 16, 0, nullptr, nullptr, flags + 3));
+    int32_t hf[4] = {0, 0, 0, 0};
+    SA_HIP(hipMemcpyAsync(hf, flags, 16, hipMemcpyDeviceToHost, s));
     SA_HIP(hipStreamSynchronize(s));
-    if (flag) return SA_OK;
+    if (hf[0]) return SA_OK;
+    const double nx = hf[2], nqm = self ? hf[2] : hf[3];
+    const bool fold = nx + 2.0 * std::sqrt(nx * nqm) < 16777216.0;
 
-    MArgs A;
-    A.xb = xb; A.xn = xn; A.qb = qb; A.qn = qn;
-    A.n = n; A.nq = nq; A.xrows = xrows;
-    A.dpad = dpad; A.k = k; A.kpad = k; A.exclude_self = exclude_self;
-    A.ids = ids; A.dists = dists;
-    const size_t lds = 8ull * MQ * A.kpad + 8ull * MQ * MBUF_I + 8ull * MQ + 4ull * 4 * MQ + 16;
-    if (lds > 160u * 1024u) return set_error(SA_EINVAL, "k=%d needs too much LDS", k);
-    MKernel kern = pick_kernel(ks, metric);
+    TKernel kern = fold ? pick_int_kernel<knn_tile::FOLDED>(ks, wq) : pick_int_kernel<knn_tile::INT>(ks, wq);
     if (!kern) return set_error(SA_EUNSUPPORTED, "d=%d", d);
+    const size_t lds = 2 * (4096 * (size_t)ks + 256) + 64 * (size_t)wq * 16;
     SA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)lds));
-    hipLaunchKernelGGL(kern, dim3((unsigned)((nq + MQ - 1) / MQ)), dim3(MNT), lds, s, A);
-    SA_HIP(hipGetLastError());
+    TileArgs A;
+    A.xt = xt; A.xn = xn; A.tab = tab; A.qt = qt; A.qn = qn;
+    A.n = n; A.ntile = (int32_t)ntile; A.qtiles = qtiles; A.nks = ks;
+    A.s = 1.f;
+    A.exclude_self = exclude_self; A.buf = buf; A.cnt = cnt;
+    for (int64_t q0 = 0; q0 < nq; q0 += qc) {
+        const int64_t cn = std::min(qc, nq - q0);
+        if (nq > qc) SA_HIP(prep(queries + q0 * ldq, cn, ldq, qpad, 0, qt, qn, nullptr));
+        A.q0 = q0; A.nq = (int32_t)cn;
+        const int rc = run_stages(A, st, kern, lds, kt, list, thr, over, s);
+        if (rc != SA_OK) return rc;
+        hipLaunchKernelGGL(knn_emit_kernel, dim3((unsigned)((cn * k + 255) / 256)), dim3(256), 0, s, list, kt, over, cn,
+                           q0, k, ids, dists, flags + 1, failed_list);
+        SA_HIP(hipGetLastError());
+    }
+    SA_HIP(hipMemcpyAsync(hf, flags, 8, hipMemcpyDeviceToHost, s));
     SA_HIP(hipStreamSynchronize(s));
+    if (hf[1] > 0) {
+        const int rc = launch_knn_scan(base, n, d, ld, queries, hf[1], ldq, k, metric, exclude_self, ids, dists, s, failed_list);
+        if (rc != SA_OK) return rc;
+        SA_HIP(hipStreamSynchronize(s));
+    }
     *ran = true;
     return SA_OK;
 }
