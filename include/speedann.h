@@ -141,15 +141,17 @@ int sa_knn(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float 
  *                Other finite float data (d <= 1024, k <= 96): coordinates split into bf16
  *                high and low parts, three products per block give approximate distances
  *                within a proven bound (L2 data are first moved by the base mean, which
- *                leaves distances unchanged), each query keeps its 128 best candidates, and a
+ *                leaves distances unchanged), each query keeps its 128 best candidates (k + 32 or more
+ *                above k = 96), and a
  *                second kernel rescores them with the scan's double-precision arithmetic;
  *                where the bound shows that no other point can enter a query's k best,
  *                its row is the scan's bit for bit, and the queries for which it cannot
  *                (many distances tied within the bound) are rescored by the scan alone
  *                (sa_knn_last_rescanned counts them).  Either form copies
  *                base and queries to temporary bf16 arrays (hipMalloc, freed before
- *                returning) and checks the values on the device first.
- *   SA_KNN_AUTO  SA_KNN_MFMA when a form applies and succeeds, else SA_KNN_SCAN. */
+ *                returning; see sa_knn_ws) and checks the values on the device first.
+ *   SA_KNN_AUTO  SA_KNN_MFMA when a form applies and succeeds, else SA_KNN_SCAN.  From 2048
+ *                base rows up the forms apply to every k up to 256. */
 typedef enum { SA_KNN_AUTO = 0, SA_KNN_SCAN = 1, SA_KNN_MFMA = 2 } sa_knn_path;
 
 /* sa_knn with an explicit path.  SA_KNN_MFMA on data or shapes it cannot take exactly
@@ -158,6 +160,16 @@ typedef enum { SA_KNN_AUTO = 0, SA_KNN_SCAN = 1, SA_KNN_MFMA = 2 } sa_knn_path;
 int sa_knn_ex(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float *queries_dev, int64_t nq,
               int64_t ldq, int32_t k, int32_t metric, int32_t exclude_self, int32_t *ids_dev, float *dists_dev,
               int32_t path, int32_t *path_used_out, void *hip_stream);
+
+/* sa_knn_ex in device memory of the caller's (256-byte aligned, any contents; NULL: allocated
+ * for the call, as sa_knn_ex does), for callers whose allocator keeps memory: allocating and
+ * freeing it takes some 0.4 ms a call.  sa_knn_workspace_bytes is what a call runs best with
+ * (0 where it needs none); with less, its queries go in smaller chunks, and SA_ECAPACITY is
+ * returned if not even a small chunk fits. */
+size_t sa_knn_workspace_bytes(int64_t n, int32_t d, int64_t nq, int32_t k, int32_t path);
+int sa_knn_ws(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float *queries_dev, int64_t nq,
+              int64_t ldq, int32_t k, int32_t metric, int32_t exclude_self, int32_t *ids_dev, float *dists_dev,
+              int32_t path, int32_t *path_used_out, void *workspace, size_t ws_bytes, void *hip_stream);
 
 /* The number of queries that the last sa_knn / sa_knn_ex call made on the calling thread
  * handed from the float form of SA_KNN_MFMA to the scan because their candidate lists

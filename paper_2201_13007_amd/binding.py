@@ -19,7 +19,7 @@ SA_L2, SA_IP = 0, 1
 SYNC = {"bsp": 0, "static": 1, "adaptive": 2}
 QFLAG_MAX_STEPS, QFLAG_CAPACITY, QFLAG_SPILLED = 1, 2, 4
 
-EXPORTS = ["sa_last_error", "sa_default_params", "sa_knn", "sa_knn_ex", "sa_quantize", "sa_index_create_q", "sa_medoid", "sa_prune", "sa_reverse_edges",
+EXPORTS = ["sa_last_error", "sa_default_params", "sa_knn", "sa_knn_ex", "sa_knn_ws", "sa_knn_workspace_bytes", "sa_quantize", "sa_index_create_q", "sa_medoid", "sa_prune", "sa_reverse_edges",
            "sa_repair", "sa_build_graph", "sa_index_create", "sa_index_destroy", "sa_search_workspace_bytes", "sa_search",
            "sa_batch_create", "sa_batch_destroy", "sa_batch_workspace_bytes", "sa_batch_upload", "sa_batch_run",
            "sa_batch_tune", "sa_batch_set_config", "sa_batch_classes", "sa_batch_class_options", "sa_batch_set_class",
@@ -65,6 +65,10 @@ def lib():
         L.sa_default_params.argtypes = [C.POINTER(SearchParams)]
         L.sa_knn.argtypes = [vp, i64, i32, i64, vp, i64, i64, i32, i32, i32, vp, vp, vp]
         L.sa_knn_ex.argtypes = [vp, i64, i32, i64, vp, i64, i64, i32, i32, i32, vp, vp, i32, C.POINTER(C.c_int32), vp]
+        L.sa_knn_workspace_bytes.argtypes = [i64, i32, i64, i32, i32]
+        L.sa_knn_workspace_bytes.restype = sz
+        L.sa_knn_ws.argtypes = [vp, i64, i32, i64, vp, i64, i64, i32, i32, i32, vp, vp, i32, C.POINTER(C.c_int32), vp, sz, vp]
+        L.sa_knn_ws.restype = C.c_int
         L.sa_knn_last_rescanned.argtypes = []
         L.sa_knn_last_rescanned.restype = i64
         L.sa_index_analyze.argtypes = [vp, vp]
@@ -162,6 +166,18 @@ def pad_dim(x: torch.Tensor) -> torch.Tensor:
     return out
 
 
+def _scratch(nbytes: int, device, stream=None):
+    """Device memory for one synchronous library call on `stream`, from torch's allocator, which
+    keeps it for the next call; None (the library allocates its own) where there is none left."""
+    if nbytes <= 0:
+        return None
+    try:
+        with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream()):
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 KNN_PATHS = {"auto": 0, "scan": 1, "mfma": 2}
 
 
@@ -178,9 +194,11 @@ def knn(base: torch.Tensor, queries: torch.Tensor, k: int, metric="l2", exclude_
     ids = torch.empty((nq, k), dtype=torch.int32, device=base.device)
     dists = torch.empty((nq, k), dtype=torch.float32, device=base.device)
     used = C.c_int32(0)
-    _check(lib().sa_knn_ex(base.data_ptr(), base.shape[0], base.shape[1], base.stride(0), queries.data_ptr(), nq,
+    ws = _scratch(lib().sa_knn_workspace_bytes(base.shape[0], base.shape[1], nq, int(k), KNN_PATHS[path]), base.device, stream)
+    _check(lib().sa_knn_ws(base.data_ptr(), base.shape[0], base.shape[1], base.stride(0), queries.data_ptr(), nq,
                            queries.stride(0), k, _metric(metric), int(exclude_self), ids.data_ptr(),
-                           dists.data_ptr(), KNN_PATHS[path], C.byref(used), _stream(stream)), "sa_knn_ex")
+                           dists.data_ptr(), KNN_PATHS[path], C.byref(used), ws.data_ptr() if ws is not None else None,
+                           ws.numel() if ws is not None else 0, _stream(stream)), "sa_knn_ws")
     if return_path:
         names = {v: n for n, v in KNN_PATHS.items()}
         return ids, dists, names[int(used.value)]

@@ -96,9 +96,15 @@ void sa_default_params(sa_search_params *out)
     out->staged = 1;
 }
 
-int sa_knn_ex(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float *queries_dev, int64_t nq,
+size_t sa_knn_workspace_bytes(int64_t n, int32_t d, int64_t nq, int32_t k, int32_t path)
+{
+    if (n < 1 || n >= (int64_t(1) << 31) || d < 4 || d > 4096 || nq < 1 || k < 1 || k > 256) return 0;
+    return knn_workspace_bytes(n, d, nq, k, path);
+}
+
+int sa_knn_ws(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float *queries_dev, int64_t nq,
               int64_t ldq, int32_t k, int32_t metric, int32_t exclude_self, int32_t *ids_dev, float *dists_dev,
-              int32_t path, int32_t *path_used_out, void *hip_stream)
+              int32_t path, int32_t *path_used_out, void *workspace, size_t ws_bytes, void *hip_stream)
 {
     int rc;
     if (path_used_out) *path_used_out = SA_KNN_AUTO;
@@ -111,9 +117,18 @@ int sa_knn_ex(const float *base_dev, int64_t n, int32_t d, int64_t ld, const flo
     if (exclude_self && nq > n) return set_error(SA_EINVAL, "exclude_self needs the queries to be base rows");
     if (path != SA_KNN_AUTO && path != SA_KNN_SCAN && path != SA_KNN_MFMA)
         return set_error(SA_EINVAL, "unknown kNN path %d", path);
+    if (((uintptr_t)workspace & 255u) != 0) return set_error(SA_EINVAL, "workspace must be 256-byte aligned");
     if ((rc = check_device()) != SA_OK) return rc;
     return launch_knn(base_dev, n, d, ld, queries_dev, nq, ldq, k, metric, exclude_self, ids_dev, dists_dev, path,
-                      path_used_out, (hipStream_t)hip_stream);
+                      path_used_out, workspace, ws_bytes, (hipStream_t)hip_stream);
+}
+
+int sa_knn_ex(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float *queries_dev, int64_t nq,
+              int64_t ldq, int32_t k, int32_t metric, int32_t exclude_self, int32_t *ids_dev, float *dists_dev,
+              int32_t path, int32_t *path_used_out, void *hip_stream)
+{
+    return sa_knn_ws(base_dev, n, d, ld, queries_dev, nq, ldq, k, metric, exclude_self, ids_dev, dists_dev, path,
+                     path_used_out, nullptr, 0, hip_stream);
 }
 
 int64_t sa_knn_last_rescanned(void) { return knn_rescanned; }
@@ -224,7 +239,7 @@ int sa_build_graph(const float *base_dev, int64_t n, int32_t d, int64_t ld, int3
         if (cand) (void)hipFree(cand);
         return set_error(SA_ENOMEM, "build_graph: candidate lists do not fit");
     }
-    rc = launch_knn(base_dev, n, d, ld, base_dev, n, ld, knn_k, metric, 1, cand, cd, SA_KNN_AUTO, nullptr, s);
+    rc = launch_knn(base_dev, n, d, ld, base_dev, n, ld, knn_k, metric, 1, cand, cd, SA_KNN_AUTO, nullptr, nullptr, 0, s);
     if (rc == SA_OK) rc = prune_device(base_dev, n, d, ld, metric, cand, knn_k, R, prune, adj_dev, s);
     if (rc == SA_OK) {
         hipError_t e = hipStreamSynchronize(s);

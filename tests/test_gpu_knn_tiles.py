@@ -73,3 +73,49 @@ def test_knn_integer_overflow_is_rescued(B):
     base[sample_rows(9_000)] = 255.0
     print("case: staged knn int, overflowing buffers", flush=True)
     assert _check(B, base, w.queries, 50) == "mfma"
+
+
+# float data: the resident kernels (d <= 128) and the wide one, each at its tile, stage and
+# query-block edges; k = 100 and 256 take longer candidate lists (from 2048 rows up)
+@pytest.mark.parametrize("d", [20, 64, 96, 128, 132, 384])
+@pytest.mark.parametrize("n,nq", [(1, 2), (65, 64), (130, 129), (2048, 257), (3001, 70)])
+def test_knn_float_tile_edges(B, d, n, nq):
+    w = synth.deep_like(n=n, nq=nq, d=d, ncomp=8)
+    for k, metric in ((1, "ip"), (10, "l2"), (96, "l2"), (100, "ip"), (256, "l2")):
+        if k > 96 and n < 2048:
+            continue
+        print(f"case: staged knn float n={n} d={d} nq={nq} k={k} {metric}", flush=True)
+        assert _check(B, w.base, w.queries, k, metric) == "mfma"
+
+
+def test_knn_float_many_queries(B):
+    # the plan for 4096 queries and more, and a self-join
+    w = synth.tiny(n=5_000, nq=4_200, d=24)
+    print("case: staged knn float 5000x24, 4200 queries", flush=True)
+    assert _check(B, w.base, w.queries, 12) == "mfma"
+    print("case: staged knn float 5000x24 self-join", flush=True)
+    assert _check(B, w.base, None, 40, self_join=True) == "mfma"
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 1e-25])
+def test_knn_float_values_for_the_scan(B, bad):
+    # one value that the matrix cores cannot take sends the call to the scan
+    w = synth.deep_like(n=2100, nq=20, d=96, ncomp=8)
+    base = w.base.copy()
+    base[1234, 7] = bad
+    print(f"case: staged knn float with {bad}", flush=True)
+    dev = torch.from_numpy(base).cuda(), torch.from_numpy(w.queries).cuda()
+    ids, d, path = B.knn(*dev, 10, metric="ip", return_path=True)
+    sids, sd = B.knn(*dev, 10, metric="ip", path="scan")
+    assert path == "scan"
+    assert torch.equal(ids, sids)
+    np.testing.assert_array_equal(d.cpu().numpy(), sd.cpu().numpy())
+
+
+def test_knn_float_overflow_is_rescued(B):
+    w = synth.deep_like(n=9_000, nq=7, d=96, ncomp=8)
+    base = w.base.copy()
+    base[sample_rows(9_000)] += 100.0
+    print("case: staged knn float, overflowing buffers", flush=True)
+    assert _check(B, base, w.queries, 50) == "mfma"
+    assert B.knn_last_rescanned() == 7
