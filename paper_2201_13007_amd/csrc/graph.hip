@@ -9,7 +9,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <numeric>
 #include <vector>
 
 namespace sa {
@@ -45,15 +44,45 @@ __device__ float dist_seq(const float *a, const float *b, int d, int metric)
 
 constexpr int MED_CHUNK = 4096;
 
-__global__ void colsum_partial(const float *base, int64_t n, int d, int64_t ld, double *part)
+// Sum in double, one addend after the other, of x[rows[i] * ld] (rows null: row i) over i <
+// cnt: two groups of 32 loads in turn, one in flight while the other is added.  The order of
+// the additions is fixed, so the loads in flight are all that hides their latency (one load
+// at a time: 1.02 ms for 4,096-row chunks of 150K x 128 floats, against 0.09 ms).
+__device__ __forceinline__ double seq_sum(const float *x, int64_t ld, const int32_t *rows, int64_t cnt)
 {
-    const int64_t r0 = (int64_t)blockIdx.x * MED_CHUNK;
-    const int64_t r1 = min(n, r0 + MED_CHUNK);
-    for (int c = threadIdx.x; c < d; c += blockDim.x) {
-        double s = 0.0;
-        for (int64_t r = r0; r < r1; ++r) s += (double)base[r * ld + c];
-        part[(int64_t)blockIdx.x * d + c] = s;
+    constexpr int U = 32;
+    float a[2][U];
+    double s = 0.0;
+    auto load = [&](float (&v)[U], int64_t i0) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int64_t i = i0 + j < cnt ? i0 + j : cnt - 1;
+            v[j] = x[(rows ? (int64_t)rows[i] : i) * ld];
+        }
+    };
+    auto add = [&](const float (&v)[U], int64_t i0) {
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (i0 + j < cnt) s += (double)v[j];
+    };
+    if (cnt <= 0) return s;
+    load(a[0], 0);
+    for (int64_t i = 0; i < cnt; i += 2 * U) {
+        load(a[1], i + U < cnt ? i + U : cnt - 1);
+        add(a[0], i);
+        load(a[0], i + 2 * U < cnt ? i + 2 * U : cnt - 1);
+        add(a[1], i + U);
     }
+    return s;
+}
+
+// column sums of chunks of rows: one wavefront per 64 columns and chunk
+__global__ void __launch_bounds__(64) colsum_partial(const float *base, int64_t n, int d, int64_t ld, int64_t chunk, double *part)
+{
+    const int64_t r0 = (int64_t)blockIdx.x * chunk;
+    const int c = blockIdx.y * 64 + threadIdx.x;
+    if (c >= d) return;
+    part[(int64_t)blockIdx.x * d + c] = seq_sum(base + r0 * ld + c, ld, nullptr, min(chunk, n - r0));
 }
 
 __global__ void colsum_final(const double *part, int64_t nchunks, int d, int64_t n, double *mean)
@@ -145,25 +174,60 @@ __global__ void prune_kernel(const float *base, int64_t n, int d, int64_t ld, in
 // ---------------------------------------------------------------- repair helpers
 
 // For several vertices at once: results[j] = the smallest key (distance to us[j], id)
-// over the marked vertices with a free slot (grid.y = j); results start as KEY_EMPTY
-__global__ void nearest_marked_batch(const float *base, int64_t n, int d, int64_t ld, int metric, const uint8_t *mask,
-                                     const int32_t *deg, int R, const int32_t *us, unsigned long long *results)
+// over the marked vertices with a free slot (grid.y: groups of NM_Q of them); results start
+// as KEY_EMPTY.  A thread takes one vertex against NM_Q queries, whose chunks of 32
+// dimensions sit in LDS, so its row is read once for all (each query by itself: 9.4 ms for
+// 256 against 150K x 128, eight at a time 1.6).
+constexpr int NM_Q = 8;
+
+__global__ void __launch_bounds__(256) nearest_marked_batch(const float *base, int64_t n, int d, int64_t ld, int metric,
+                                                            const uint8_t *mask, const int32_t *deg, int R,
+                                                            const int32_t *us, int nus, unsigned long long *results)
 {
-    __shared__ unsigned long long sk[256];
+    __shared__ float qs[NM_Q][32];
     const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t u = us[blockIdx.y];
-    unsigned long long key = KEY_EMPTY;
-    if (w < n && mask[w] && deg[w] < R) {
-        float dd = dist_seq(base + w * ld, base + (int64_t)u * ld, d, metric);
-        key = make_key(dd, (int32_t)w);
-    }
-    sk[threadIdx.x] = key;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s && sk[threadIdx.x + s] < sk[threadIdx.x]) sk[threadIdx.x] = sk[threadIdx.x + s];
+    const int j0 = blockIdx.y * NM_Q;
+    const bool in = w < n && mask[w] && deg[w] < R;
+    const float *x = base + (in ? w : 0) * ld;
+    double acc[NM_Q];
+#pragma unroll
+    for (int j = 0; j < NM_Q; ++j) acc[j] = 0.0;
+    for (int c0 = 0; c0 < d; c0 += 32) {
         __syncthreads();
+        for (int i = threadIdx.x; i < NM_Q * 32; i += 256) {
+            const int j = i >> 5, c = c0 + (i & 31);
+            qs[j][i & 31] = j0 + j < nus && c < d ? base[(int64_t)us[j0 + j] * ld + c] : 0.f;
+        }
+        __syncthreads();
+        if (!in) continue;
+        const int cn = min(32, d - c0);
+        for (int c = 0; c < cn; c += 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(x + c0 + c);
+            const float xv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < NM_Q; ++j) {
+                    const float q = qs[j][c + i];
+                    if (metric == SA_L2) {
+                        const double t = (double)xv[i] - (double)q;
+                        acc[j] += t * t;
+                    } else {
+                        acc[j] += (double)xv[i] * (double)q;
+                    }
+                }
+        }
     }
-    if (threadIdx.x == 0 && sk[0] != KEY_EMPTY) atomicMin(results + blockIdx.y, sk[0]);
+#pragma unroll
+    for (int j = 0; j < NM_Q; ++j) {
+        unsigned long long key = in ? make_key(metric == SA_L2 ? (float)acc[j] : (float)(-acc[j]), (int32_t)w) : KEY_EMPTY;
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long k = __shfl_xor(key, o, 64);
+            key = k < key ? k : key;
+        }
+        if (__lane_id() == 0 && j0 + j < nus && key < __hip_atomic_load(results + j0 + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMin(results + j0 + j, key);
+    }
 }
 
 __global__ void fill_u64_n(unsigned long long *p, int64_t cnt, unsigned long long v)
@@ -172,15 +236,410 @@ __global__ void fill_u64_n(unsigned long long *p, int64_t cnt, unsigned long lon
     if (i < cnt) p[i] = v;
 }
 
-// distance of every edge p -> c, computed as d(c, p)
-__global__ void edge_dists(const float *base, int64_t n, int d, int64_t ld, int metric, const int32_t *adj, int R,
-                           float *out)
+// ---------------------------------------------------------------- rows and scans
+
+// deg[v]: entries of row v before the first negative one (prefix), or not negative (all)
+__global__ void __launch_bounds__(256) row_degrees(const int32_t *adj, int64_t n, int R, int prefix, int32_t *deg)
+{
+    const int lane = __lane_id();
+    const int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (v >= n) return;
+    const uint64_t neg = __ballot(lane >= R || adj[v * R + (lane < R ? lane : 0)] < 0);
+    if (lane == 0) deg[v] = prefix ? (neg ? __builtin_ctzll(neg) : 64) : 64 - __popcll(neg);
+}
+
+constexpr int SCAN_CHUNK = 2048;   // elements per workgroup of the prefix sum
+
+// exclusive prefix sums of cnt[0 .. n) into out[0 .. n] (out[n]: the total), in three
+// launches: sums of chunks, their prefix, the elements
+__global__ void __launch_bounds__(256) scan_sums(const int32_t *cnt, int64_t n, int64_t *sums)
+{
+    __shared__ int64_t part[4];
+    const int64_t i0 = (int64_t)blockIdx.x * SCAN_CHUNK;
+    int64_t t = 0;
+    for (int j = threadIdx.x; j < SCAN_CHUNK; j += 256)
+        if (i0 + j < n) t += cnt[i0 + j];
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor((long long)t, o, 64);
+    if (__lane_id() == 0) part[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+__global__ void __launch_bounds__(64) scan_chunks(int64_t *sums, int64_t nchunk, int64_t *total)
+{
+    const int lane = __lane_id();
+    int64_t run = 0;
+    for (int64_t i0 = 0; i0 < nchunk; i0 += 64) {
+        const int64_t v = i0 + lane < nchunk ? sums[i0 + lane] : 0;
+        int64_t inc = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t u = __shfl_up((long long)inc, o, 64);
+            if (lane >= o) inc += u;
+        }
+        if (i0 + lane < nchunk) sums[i0 + lane] = run + inc - v;
+        run += __shfl((long long)inc, 63, 64);
+    }
+    if (lane == 0) *total = run;
+}
+
+__global__ void __launch_bounds__(256) scan_write(const int32_t *cnt, int64_t n, const int64_t *sums, int64_t *out)
+{
+    __shared__ int64_t part[4];
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
+    int64_t run = sums[blockIdx.x];
+    for (int j0 = 0; j0 < SCAN_CHUNK; j0 += 256) {
+        const int64_t i = (int64_t)blockIdx.x * SCAN_CHUNK + j0 + threadIdx.x;
+        const int64_t v = i < n ? cnt[i] : 0;
+        int64_t inc = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t u = __shfl_up((long long)inc, o, 64);
+            if (lane >= o) inc += u;
+        }
+        if (lane == 63) part[w] = inc;
+        __syncthreads();
+        int64_t base = run;
+        for (int k = 0; k < w; ++k) base += part[k];
+        if (i < n) out[i] = base + inc - v;
+        run += part[0] + part[1] + part[2] + part[3];
+        __syncthreads();
+    }
+}
+
+// sums: room for (n + SCAN_CHUNK - 1) / SCAN_CHUNK entries
+hipError_t prefix_sums(const int32_t *cnt, int64_t n, int64_t *sums, int64_t *out, hipStream_t s)
+{
+    const int64_t nchunk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    hipLaunchKernelGGL(scan_sums, dim3((unsigned)nchunk), dim3(256), 0, s, cnt, n, sums);
+    hipLaunchKernelGGL(scan_chunks, dim3(1), dim3(64), 0, s, sums, nchunk, out + n);
+    hipLaunchKernelGGL(scan_write, dim3((unsigned)nchunk), dim3(256), 0, s, cnt, n, sums, out);
+    return hipGetLastError();
+}
+
+__global__ void fill_i32(int32_t *p, int64_t cnt, int32_t v)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < cnt) p[i] = v;
+}
+
+unsigned blocks_for(int64_t cnt, int per) { return (unsigned)((cnt + per - 1) / per); }
+
+// ---------------------------------------------------------------- reverse edges
+
+// In-edges of the vertices that have room, counted (in null) or written as keys
+// (d(c, p), p) in any order behind start[c]
+__global__ void in_edges(const float *base, int64_t n, int d, int64_t ld, int metric, const int32_t *adj, int R,
+                         const int32_t *deg, int32_t *cnt, const int64_t *start, uint64_t *in)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n * R) return;
     const int64_t p = e / R;
     const int32_t c = adj[e];
-    out[e] = (c >= 0 && c < n) ? dist_seq(base + (int64_t)c * ld, base + p * ld, d, metric) : 0.f;
+    if (c < 0 || c >= n || deg[c] >= R) return;
+    const int pos = atomicAdd(cnt + c, 1);
+    if (in) in[start[c] + pos] = make_key(dist_seq(base + (int64_t)c * ld, base + p * ld, d, metric), (int32_t)p);
+}
+
+// sorts one key per lane, ascending
+__device__ __forceinline__ uint64_t sort64(uint64_t v)
+{
+    const int lane = __lane_id();
+    for (int k = 2; k <= 64; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)v, j, 64);
+            const bool low = (lane & j) == 0, up = (lane & k) == 0;
+            v = (low == up) == (o < v) ? o : v;
+        }
+    return v;
+}
+
+// One wavefront per vertex with room: the 64 smallest in-edge keys above the last ones
+// taken, by merging sorted chunks of 64 into a sorted list held one key per lane; each is
+// appended unless the row holds its vertex, and the list is read again if 64 were not
+// enough (at most R of them can be known already).  On the host this was the longest part
+// of a graph build (60 ms of 197 at 150K x 128).
+__global__ void __launch_bounds__(256) append_in_edges(int64_t n, int R, const int32_t *deg, const int64_t *start,
+                                                       const uint64_t *in, int32_t *adj, unsigned long long *added)
+{
+    const int lane = __lane_id();
+    const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (c >= n) return;
+    int len = deg[c];
+    const int64_t b = start[c], e = start[c + 1];
+    if (len >= R || b == e) return;
+    const int before = len;
+    int32_t row = lane < len ? adj[c * R + lane] : -1;
+    uint64_t last = 0;
+    bool some = false, more = true;
+    while (more && len < R) {
+        uint64_t best = KEY_EMPTY;
+        for (int64_t i0 = b; i0 < e; i0 += 64) {
+            uint64_t v = i0 + lane < e ? in[i0 + lane] : KEY_EMPTY;
+            if (some && v <= last) v = KEY_EMPTY;
+            const uint64_t worst = (uint64_t)__shfl((unsigned long long)best, 63, 64);
+            if (__ballot(v < worst) == 0) continue;
+            v = sort64(v);
+            // the smaller of best[l] and v[63 - l] are the 64 smallest, bitonic in l
+            const uint64_t r = (uint64_t)__shfl((unsigned long long)v, 63 - lane, 64);
+            best = r < best ? r : best;
+            for (int j = 32; j > 0; j >>= 1) {
+                const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)best, j, 64);
+                best = ((lane & j) == 0) == (o < best) ? o : best;
+            }
+        }
+        const int got = __popcll(__ballot(best != KEY_EMPTY));
+        for (int i = 0; i < got && len < R; ++i) {
+            const int32_t p = key_id((uint64_t)__shfl((unsigned long long)best, i, 64));
+            if (__ballot(row == p)) continue;
+            if (lane == len) row = p;
+            ++len;
+        }
+        more = got == 64;
+        some = true;
+        last = (uint64_t)__shfl((unsigned long long)best, 63, 64);
+    }
+    if (lane >= before && lane < len) adj[c * R + lane] = row;
+    if (lane == 0 && len > before) atomicAdd(added, (unsigned long long)(len - before));
+}
+
+// ---------------------------------------------------------------- repair
+
+// Union-find over the edges: a root only ever gets a smaller root as its parent, so every
+// component ends with its smallest vertex as root.
+__device__ __forceinline__ int32_t uf_load(int32_t *par, int32_t v)
+{
+    return __hip_atomic_load(par + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ int32_t uf_root(int32_t *par, int32_t v)
+{
+    int32_t p = uf_load(par, v);
+    while (p != v) {
+        const int32_t g = uf_load(par, p);
+        if (g != p) __hip_atomic_store(par + v, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = p;
+        p = g;
+    }
+    return v;
+}
+
+__global__ void uf_init(int32_t *par, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) par[i] = (int32_t)i;
+}
+
+__global__ void uf_hook(const int32_t *adj, int64_t n, int R, int32_t *par)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n * R) return;
+    const int32_t u = adj[e];
+    if (u < 0 || u >= n) return;
+    int32_t a = uf_root(par, (int32_t)(e / R)), b = uf_root(par, u);
+    while (a != b) {
+        const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
+        const int32_t old = atomicCAS(par + hi, hi, lo);
+        if (old == hi) break;   // hi was still a root
+        a = uf_root(par, old);
+        b = uf_root(par, lo);
+    }
+}
+
+__global__ void uf_flatten(int32_t *par, int64_t n, int32_t *root, int32_t *is_root)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t r = uf_root(par, (int32_t)i);
+    root[i] = r;
+    is_root[i] = r == i;
+}
+
+// comp[v] = number of v's component (in the order of their smallest vertices)
+__global__ void comp_of(const int32_t *root, const int64_t *number, int64_t n, int32_t *comp)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) comp[i] = (int32_t)number[root[i]];
+}
+
+// mean of each group of rows: members[start[g] .. start[g + 1]) (members null: the rows
+// themselves), summed in that order; one wavefront per 64 columns and group
+__global__ void __launch_bounds__(64) group_means(const float *base, int d, int64_t ld, const int32_t *members,
+                                                  const int64_t *start, double *mean)
+{
+    const int64_t g = blockIdx.x;
+    const int c = blockIdx.y * 64 + threadIdx.x;
+    if (c >= d) return;
+    const int64_t b = start[g], cnt = start[g + 1] - b;
+    const double s = members ? seq_sum(base + c, ld, members + b, cnt) : seq_sum(base + b * ld + c, ld, nullptr, cnt);
+    mean[g * d + c] = s / (double)cnt;
+}
+
+// squared distance of every row to its group's mean (comp null: group 0), in double
+__global__ void mean_dists(const float *base, int64_t n, int d, int64_t ld, const double *mean, const int32_t *comp,
+                           double *out)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    const double *m = mean + (comp ? (int64_t)comp[v] * d : 0);
+    double acc = 0.0;
+    for (int i = 0; i < d; i += 4) {
+        const float4 x = *reinterpret_cast<const float4 *>(base + v * ld + i);
+        double t;
+        t = (double)x.x - m[i]; acc += t * t;
+        t = (double)x.y - m[i + 1]; acc += t * t;
+        t = (double)x.z - m[i + 2]; acc += t * t;
+        t = (double)x.w - m[i + 3]; acc += t * t;
+    }
+    out[v] = acc;
+}
+
+// the nearest member of each group, ties to the smaller id: first the distance (bits of a
+// non-negative double order as integers), then the id
+__global__ void nearest_member(const double *dist, const int32_t *comp, int64_t n, int pass, unsigned long long *bestd,
+                               int32_t *best)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(dist[v]);
+    if (pass == 0) {
+        if (b < __hip_atomic_load(bestd + comp[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(bestd + comp[v], b);
+    } else if (b == bestd[comp[v]]) {
+        atomicMin(best + comp[v], (int32_t)v);
+    }
+}
+
+// out[i][j] = distance of rows us[i] and ws[j]
+__global__ void pair_dists(const float *base, int d, int64_t ld, int metric, const int32_t *us, int64_t nu,
+                           const int32_t *ws, int64_t nw, float *out)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= nu * nw) return;
+    out[e] = dist_seq(base + (int64_t)us[e / nw] * ld, base + (int64_t)ws[e % nw] * ld, d, metric);
+}
+
+constexpr int LINK_REPS = 4096;   // representatives the link kernel can sort in LDS
+
+// One workgroup per gateway vertex v = src[a]: links to representatives, in key order,
+// kept unless a kept one is nearer to the candidate than v is (rd: distances between
+// representatives, dv: from the sources), then the nearest of the others, up to R less
+// the local edges kept.
+__global__ void __launch_bounds__(256) link_kernel(const int32_t *src, int64_t nc, const int32_t *rep, const int32_t *comp,
+                                                   const float *rd, const float *dv, int R, int keep_rep, int keep_hub,
+                                                   int P, int32_t *links)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint64_t *const key = reinterpret_cast<uint64_t *>(smem);             // [P]
+    uint8_t *const used = reinterpret_cast<uint8_t *>(key + P);            // [P]
+    const int64_t a = blockIdx.x;
+    const int32_t v = src[a];
+    const int cap = R - (a < nc ? keep_rep : keep_hub);
+    for (int i = threadIdx.x; i < P; i += 256) {
+        key[i] = i < nc && rep[i] != v ? make_key(dv[a * nc + i], rep[i]) : KEY_EMPTY;
+        used[i] = 0;
+    }
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (int i = threadIdx.x; i < P / 2; i += 256) {
+                const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1)), hi = lo | j;
+                const uint64_t x = key[lo], y = key[hi];
+                if ((x > y) == ((lo & k) == 0)) {
+                    key[lo] = y;
+                    key[hi] = x;
+                }
+            }
+        }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int lane = __lane_id();
+    int nk = 0;
+    int32_t mine = -1, mine_comp = 0;   // lane l: the l-th link and its component
+    for (int i = 0; i < P && nk < cap; ++i) {
+        const uint64_t k = key[i];
+        if (k == KEY_EMPTY) break;
+        const int32_t id = key_id(k), c = comp[id];
+        const bool occl = lane < nk && rd[(int64_t)mine_comp * nc + c] < key_dist(k);
+        if (__ballot(occl)) continue;
+        if (lane == nk) {
+            mine = id;
+            mine_comp = c;
+        }
+        if (lane == 0) used[i] = 1;
+        ++nk;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = 0; i < P && nk < cap; ++i) {
+        if (key[i] == KEY_EMPTY) break;
+        if (used[i]) continue;
+        if (lane == nk) mine = key_id(key[i]);
+        ++nk;
+    }
+    if (lane < R) links[a * R + lane] = lane < nk ? mine : -1;
+}
+
+// the new rows of the gateway vertices: the first local edges that are no links, then the links
+__global__ void __launch_bounds__(64) gateway_rows(const int32_t *src, int64_t nc, const int32_t *links, int R, int keep_rep,
+                                                   int keep_hub, int32_t *adj)
+{
+    const int lane = __lane_id();
+    const int64_t a = blockIdx.x;
+    int32_t *const row = adj + (int64_t)src[a] * R;
+    const int kl = a < nc ? keep_rep : keep_hub;
+    const int32_t old = lane < R ? row[lane] : -1, lk = lane < R ? links[a * R + lane] : -1;
+    int len = 0;
+    int32_t out = -1;
+    for (int r = 0; r < R && len < kl; ++r) {
+        const int32_t u = __shfl(old, r, 64);
+        if (u < 0 || __ballot(lk == u)) continue;
+        if (lane == len) out = u;
+        ++len;
+    }
+    for (int r = 0; r < R; ++r) {
+        const int32_t u = __shfl(lk, r, 64);
+        if (u < 0) continue;
+        if (lane == len) out = u;
+        ++len;
+    }
+    if (lane < R) row[lane] = out;
+}
+
+// One level of a breadth-first walk: the out-neighbours of the vertices at level cur get
+// cur + 1; *changed is set if there was one.
+__global__ void __launch_bounds__(256) bfs_level(const int32_t *adj, int64_t n, int R, int32_t *level, int32_t cur, int32_t *changed)
+{
+    const int lane = __lane_id();
+    const int64_t v0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+    const int64_t v = v0 + lane;
+    uint64_t front = __ballot(v < n && level[v < n ? v : 0] == cur);
+    bool any = false;
+    for (; front; front &= front - 1) {
+        const int64_t f = v0 + __builtin_ctzll(front);
+        const int32_t u = lane < R ? adj[f * R + lane] : -1;
+        if (u >= 0 && u < n && level[u] < 0) {
+            level[u] = cur + 1;   // (every writer of this launch writes the same)
+            any = true;
+        }
+    }
+    if (__ballot(any) && lane == 0) *changed = 1;
+}
+
+__global__ void level_marks(const int32_t *level, int64_t n, uint8_t *mark)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) mark[i] = level[i] >= 0;
+}
+
+// rows ids[i] of src (row_words 32-bit words, stride words apart) to dst row i
+__global__ void gather_rows(const int32_t *src, int64_t stride, int row_words, const int32_t *ids, int64_t cnt, int32_t *dst)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < cnt * row_words) dst[e] = src[(int64_t)ids[e / row_words] * stride + e % row_words];
+}
+
+__global__ void apply_edits(const int64_t *pos, const int32_t *val, int64_t cnt, int32_t *adj)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < cnt) adj[pos[i]] = val[i];
 }
 
 // host-side distance with the same arithmetic as dist_seq
@@ -199,61 +658,6 @@ float host_dist(const float *a, const float *b, int d, int metric)
 }
 
 bool key_less_host(float da, int32_t ia, float db, int32_t ib) { return da < db || (da == db && ia < ib); }
-
-// medoid of a set of rows: mean summed in the listed order, then the nearest row
-int32_t host_medoid(const float *X, int64_t ld, int d, const int32_t *members, int64_t cnt)
-{
-    std::vector<double> mean(d, 0.0);
-    for (int64_t a = 0; a < cnt; ++a) {
-        const float *x = X + (int64_t)members[a] * ld;
-        for (int i = 0; i < d; ++i) mean[i] += (double)x[i];
-    }
-    for (int i = 0; i < d; ++i) mean[i] /= (double)cnt;
-    int32_t best = -1;
-    double bestd = INFINITY;
-    for (int64_t a = 0; a < cnt; ++a) {
-        const int32_t v = members[a];
-        const float *x = X + (int64_t)v * ld;
-        double acc = 0.0;
-        for (int i = 0; i < d; ++i) {
-            double t = (double)x[i] - mean[i];
-            acc += t * t;
-        }
-        if (acc < bestd || (acc == bestd && v < best)) {
-            bestd = acc;
-            best = v;
-        }
-    }
-    return best;
-}
-
-int64_t mark_from(const std::vector<int32_t> &adj, int R, int64_t n, int32_t src, std::vector<uint8_t> &mark,
-                  std::vector<int32_t> &newly)
-{
-    newly.clear();
-    if (mark[src]) return 0;
-    mark[src] = 1;
-    newly.push_back(src);
-    for (size_t h = 0; h < newly.size(); ++h) {
-        const int32_t v = newly[h];
-        for (int r = 0; r < R; ++r) {
-            const int32_t u = adj[(int64_t)v * R + r];
-            if (u < 0 || u >= n || mark[u]) continue;
-            mark[u] = 1;
-            newly.push_back(u);
-        }
-    }
-    return (int64_t)newly.size();
-}
-
-int64_t uf_find(std::vector<int64_t> &par, int64_t x)
-{
-    while (par[x] != x) {
-        par[x] = par[par[x]];
-        x = par[x];
-    }
-    return x;
-}
 
 // device buffer that frees itself
 template <typename T>
@@ -277,7 +681,8 @@ int medoid_device(const float *base, int64_t n, int d, int64_t ld, int32_t *out,
     if (part.alloc(nchunks * d) != hipSuccess || mean.alloc(d) != hipSuccess || bestd.alloc(nblk) != hipSuccess ||
         besti.alloc(nblk) != hipSuccess)
         return set_error(SA_ENOMEM, "medoid: device allocation failed");
-    hipLaunchKernelGGL(colsum_partial, dim3((unsigned)nchunks), dim3(128), 0, s, base, n, d, ld, part.p);
+    hipLaunchKernelGGL(colsum_partial, dim3((unsigned)nchunks, (unsigned)((d + 63) / 64)), dim3(64), 0, s, base, n, d, ld,
+                       (int64_t)MED_CHUNK, part.p);
     hipLaunchKernelGGL(colsum_final, dim3((d + 127) / 128), dim3(128), 0, s, part.p, nchunks, d, n, mean.p);
     hipLaunchKernelGGL(dist_to_mean, dim3((unsigned)nblk), dim3(256), 0, s, base, n, d, ld, mean.p, bestd.p, besti.p);
     SA_HIP(hipGetLastError());
@@ -307,297 +712,409 @@ int prune_device(const float *base, int64_t n, int d, int64_t ld, int metric, co
     return SA_OK;
 }
 
+namespace {
+
+// one device allocation cut into parts
+struct Arena {
+    unsigned char *p = nullptr;
+    size_t at = 0;
+    template <typename T>
+    size_t want(int64_t count)
+    {
+        const size_t o = at;
+        at += (sizeof(T) * (size_t)(count > 0 ? count : 1) + 255) / 256 * 256;
+        return o;
+    }
+    hipError_t alloc() { return hipMalloc(reinterpret_cast<void **>(&p), at); }
+    template <typename T>
+    T *get(size_t o) const { return reinterpret_cast<T *>(p + o); }
+    ~Arena()
+    {
+        if (p) (void)hipFree(p);
+    }
+};
+
+}  // namespace
+
 int reverse_edges_device(const float *base, int64_t n, int d, int64_t ld, int metric, int32_t *adj_dev, int R,
                          int64_t *added_out, hipStream_t s)
 {
-    const int64_t ne = n * R;
-    DevBuf<float> dd;
-    if (dd.alloc(ne) != hipSuccess) return set_error(SA_ENOMEM, "reverse edges: device allocation failed");
-    hipLaunchKernelGGL(edge_dists, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, s, base, n, d, ld, metric,
-                       adj_dev, R, dd.p);
+    if (added_out) *added_out = 0;
+    if (n < 1) return SA_OK;
+    const int64_t ne = n * R, nchunk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    Arena A;
+    const size_t o_deg = A.want<int32_t>(n), o_cnt = A.want<int32_t>(n), o_start = A.want<int64_t>(n + 1);
+    const size_t o_sums = A.want<int64_t>(nchunk), o_added = A.want<unsigned long long>(1);
+    if (A.alloc() != hipSuccess) return set_error(SA_ENOMEM, "reverse edges: device allocation failed");
+    int32_t *const deg = A.get<int32_t>(o_deg), *const cnt = A.get<int32_t>(o_cnt);
+    int64_t *const start = A.get<int64_t>(o_start);
+    unsigned long long *const added = A.get<unsigned long long>(o_added);
+    hipLaunchKernelGGL(row_degrees, dim3(blocks_for(n, 4)), dim3(256), 0, s, adj_dev, n, R, 1, deg);
+    hipLaunchKernelGGL(fill_i32, dim3(blocks_for(n, 256)), dim3(256), 0, s, cnt, n, 0);
+    hipLaunchKernelGGL(in_edges, dim3(blocks_for(ne, 256)), dim3(256), 0, s, base, n, d, ld, metric, adj_dev, R, deg, cnt,
+                       (const int64_t *)nullptr, (uint64_t *)nullptr);
     SA_HIP(hipGetLastError());
-    std::vector<int32_t> snap((size_t)ne);
-    std::vector<float> ed((size_t)ne);
-    SA_HIP(hipMemcpyAsync(snap.data(), adj_dev, sizeof(int32_t) * ne, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipMemcpyAsync(ed.data(), dd.p, sizeof(float) * ne, hipMemcpyDeviceToHost, s));
+    SA_HIP(prefix_sums(cnt, n, A.get<int64_t>(o_sums), start, s));
+    int64_t total = 0;
+    SA_HIP(hipMemcpyAsync(&total, start + n, 8, hipMemcpyDeviceToHost, s));
     SA_HIP(hipStreamSynchronize(s));
-    // in-edges grouped by target, each group in key order (d(c, p), p)
-    std::vector<int64_t> start(n + 1, 0);
-    for (int64_t e = 0; e < ne; ++e)
-        if (snap[e] >= 0 && snap[e] < n) start[snap[e] + 1]++;
-    for (int64_t c = 0; c < n; ++c) start[c + 1] += start[c];
-    struct In {
-        float d;
-        int32_t p;
-    };
-    std::vector<In> in((size_t)start[n]);
-    {
-        std::vector<int64_t> fill(start.begin(), start.end() - 1);
-        for (int64_t e = 0; e < ne; ++e) {
-            const int32_t c = snap[e];
-            if (c >= 0 && c < n) in[fill[c]++] = {ed[e], (int32_t)(e / R)};
-        }
-    }
-    std::vector<int32_t> adj(snap);
-    int64_t added = 0;
-    for (int64_t c = 0; c < n; ++c) {
-        int deg = 0;
-        while (deg < R && adj[c * R + deg] >= 0) ++deg;
-        if (deg >= R || start[c + 1] == start[c]) continue;
-        In *b = in.data() + start[c], *e = in.data() + start[c + 1];
-        std::sort(b, e, [](const In &x, const In &y) { return key_less_host(x.d, x.p, y.d, y.p); });
-        for (In *it = b; it != e && deg < R; ++it) {
-            bool dup = false;
-            for (int r = 0; r < deg; ++r)
-                if (adj[c * R + r] == it->p) {
-                    dup = true;
-                    break;
-                }
-            if (dup) continue;
-            adj[c * R + deg++] = it->p;
-            ++added;
-        }
-    }
-    SA_HIP(hipMemcpyAsync(adj_dev, adj.data(), sizeof(int32_t) * ne, hipMemcpyHostToDevice, s));
+    Arena K;
+    const size_t o_in = K.want<uint64_t>(total);
+    if (K.alloc() != hipSuccess) return set_error(SA_ENOMEM, "reverse edges: device allocation failed");
+    uint64_t *const in = K.get<uint64_t>(o_in);
+    hipLaunchKernelGGL(fill_i32, dim3(blocks_for(n, 256)), dim3(256), 0, s, cnt, n, 0);
+    hipLaunchKernelGGL(fill_u64_n, dim3(1), dim3(64), 0, s, added, (int64_t)1, 0ull);
+    hipLaunchKernelGGL(in_edges, dim3(blocks_for(ne, 256)), dim3(256), 0, s, base, n, d, ld, metric, adj_dev, R, deg, cnt,
+                       (const int64_t *)start, in);
+    hipLaunchKernelGGL(append_in_edges, dim3(blocks_for(n, 4)), dim3(256), 0, s, n, R, deg, start, in, adj_dev, added);
+    SA_HIP(hipGetLastError());
+    unsigned long long h = 0;
+    SA_HIP(hipMemcpyAsync(&h, added, 8, hipMemcpyDeviceToHost, s));
     SA_HIP(hipStreamSynchronize(s));
-    if (added_out) *added_out = added;
+    if (added_out) *added_out = (int64_t)h;
     return SA_OK;
 }
+
+namespace {
+
+// Links of the gateway vertices on the host, for more representatives than link_kernel
+// sorts: dv[a][c] distances of source a (nc representatives first) to representative c.
+void host_links(const std::vector<int32_t> &src, const std::vector<int32_t> &rep, const std::vector<float> &dv, int R,
+                int keep_local, int hub_keep_local, std::vector<int32_t> &links)
+{
+    const int64_t nc = (int64_t)rep.size();
+    struct Cd {
+        float d;
+        int32_t id, c;
+        bool used;
+    };
+    std::vector<Cd> cand;
+    for (int64_t a = 0; a < (int64_t)src.size(); ++a) {
+        const int cap = R - (a < nc ? keep_local : hub_keep_local);
+        if (cap <= 0) continue;
+        cand.clear();
+        for (int64_t c = 0; c < nc; ++c)
+            if (rep[c] != src[a]) cand.push_back({dv[(size_t)(a * nc + c)], rep[c], (int32_t)c, false});
+        std::sort(cand.begin(), cand.end(), [](const Cd &x, const Cd &y) { return key_less_host(x.d, x.id, y.d, y.id); });
+        int32_t *out = &links[(size_t)a * R];
+        std::vector<int32_t> kc;
+        for (auto &c : cand) {
+            if ((int)kc.size() >= cap) break;
+            bool keep = true;
+            for (int32_t x : kc)
+                if (dv[(size_t)x * nc + c.c] < c.d) {
+                    keep = false;
+                    break;
+                }
+            if (keep) {
+                kc.push_back(c.c);
+                c.used = true;
+            }
+        }
+        int kept = 0;
+        for (int32_t x : kc) out[kept++] = rep[x];
+        for (auto &c : cand) {
+            if (kept >= cap) break;
+            if (!c.used) out[kept++] = c.id;
+        }
+    }
+}
+
+}  // namespace
 
 int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, int32_t *adj_dev, int R,
                   int32_t entry, int keep_local, int hubs, int hub_keep_local, int64_t *bridges_out,
                   int64_t *ncomp_out, hipStream_t s)
 {
-    std::vector<int32_t> adj((size_t)n * R);
-    std::vector<float> X((size_t)n * ld);
-    SA_HIP(hipMemcpyAsync(adj.data(), adj_dev, sizeof(int32_t) * adj.size(), hipMemcpyDeviceToHost, s));
-    SA_HIP(hipMemcpyAsync(X.data(), base, sizeof(float) * X.size(), hipMemcpyDeviceToHost, s));
-    SA_HIP(hipStreamSynchronize(s));
+    const int64_t ne = n * R, nchunk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    const int dcol = (d + 63) / 64;
+    Arena A;
+    const size_t o_par = A.want<int32_t>(n), o_root = A.want<int32_t>(n), o_flag = A.want<int32_t>(n), o_num = A.want<int64_t>(n + 1);
+    const size_t o_sums = A.want<int64_t>(nchunk), o_dist = A.want<double>(n), o_mark = A.want<uint8_t>(n), o_chg = A.want<int32_t>(1);
+    if (A.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+    int32_t *const par = A.get<int32_t>(o_par), *const root = A.get<int32_t>(o_root), *const flag = A.get<int32_t>(o_flag);
+    int64_t *const num = A.get<int64_t>(o_num);
+    double *const dist = A.get<double>(o_dist);
+    const dim3 bn(blocks_for(n, 256)), t256(256);
 
-    // (1) weakly connected components, numbered by smallest member; medoid of each
-    std::vector<int64_t> par(n);
-    std::iota(par.begin(), par.end(), 0);
-    for (int64_t v = 0; v < n; ++v)
-        for (int r = 0; r < R; ++r) {
-            const int32_t u = adj[v * R + r];
-            if (u < 0) continue;
-            int64_t a = uf_find(par, v), b = uf_find(par, u);
-            if (a != b) {
-                if (a < b) par[b] = a;
-                else par[a] = b;
-            }
-        }
-    std::vector<int64_t> comp(n), root_comp(n, -1);
+    // (1) weakly connected components, numbered by smallest member
+    hipLaunchKernelGGL(uf_init, bn, t256, 0, s, par, n);
+    hipLaunchKernelGGL(uf_hook, dim3(blocks_for(ne, 256)), t256, 0, s, adj_dev, n, R, par);
+    hipLaunchKernelGGL(uf_flatten, bn, t256, 0, s, par, n, root, flag);
+    SA_HIP(hipGetLastError());
+    SA_HIP(prefix_sums(flag, n, A.get<int64_t>(o_sums), num, s));
     int64_t nc = 0;
-    for (int64_t i = 0; i < n; ++i) {
-        int64_t rt = uf_find(par, i);
-        if (root_comp[rt] < 0) root_comp[rt] = nc++;
-        comp[i] = root_comp[rt];
-    }
-    std::vector<int64_t> start(nc + 1, 0);
-    for (int64_t i = 0; i < n; ++i) start[comp[i] + 1]++;
-    for (int64_t c = 0; c < nc; ++c) start[c + 1] += start[c];
-    std::vector<int32_t> members(n);
-    {
-        std::vector<int64_t> fill(start.begin(), start.end() - 1);
-        for (int64_t i = 0; i < n; ++i) members[fill[comp[i]]++] = (int32_t)i;
-    }
-    std::vector<int32_t> rep(nc);
-    for (int64_t c = 0; c < nc; ++c) rep[c] = host_medoid(X.data(), ld, d, members.data() + start[c], start[c + 1] - start[c]);
+    SA_HIP(hipMemcpyAsync(&nc, num + n, 8, hipMemcpyDeviceToHost, s));
+    SA_HIP(hipStreamSynchronize(s));
     if (ncomp_out) *ncomp_out = nc;
 
-    // (2) gateway rows for the representatives, the entry and the hubs (the vertices
-    // nearest to the mean of all rows)
-    std::vector<uint8_t> is_rep(n, 0);
-    for (int64_t c = 0; c < nc; ++c) is_rep[rep[c]] = 1;
-    std::vector<int32_t> hub;
+    // (2) gateway rows for the representatives (each component's medoid), the entry and the
+    // hubs (the vertices nearest to the mean of all rows)
     if (nc > 1) {
-        if (!is_rep[entry]) hub.push_back(entry);
-        if (hubs > 1) {
-            std::vector<double> mean(d, 0.0);
-            for (int64_t v = 0; v < n; ++v)
-                for (int i = 0; i < d; ++i) mean[i] += (double)X[(size_t)v * ld + i];
-            for (int i = 0; i < d; ++i) mean[i] /= (double)n;
+        int32_t *const comp = par;   // (the union-find is done with it)
+        hipLaunchKernelGGL(comp_of, bn, t256, 0, s, root, num, n, comp);
+        std::vector<int32_t> hcomp((size_t)n), members((size_t)n);
+        SA_HIP(hipMemcpyAsync(hcomp.data(), comp, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipStreamSynchronize(s));
+        std::vector<int64_t> start((size_t)nc + 1, 0);
+        for (int64_t i = 0; i < n; ++i) start[hcomp[i] + 1]++;
+        for (int64_t c = 0; c < nc; ++c) start[c + 1] += start[c];
+        {
+            std::vector<int64_t> fill(start.begin(), start.end() - 1);
+            for (int64_t i = 0; i < n; ++i) members[fill[hcomp[i]]++] = (int32_t)i;
+        }
+        Arena C;
+        const size_t o_mem = C.want<int32_t>(n), o_start = C.want<int64_t>(nc + 3), o_mean = C.want<double>(nc * d);
+        const size_t o_best = C.want<unsigned long long>(nc), o_rep = C.want<int32_t>(nc);
+        if (C.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+        int32_t *const rep_dev = C.get<int32_t>(o_rep);
+        int64_t *const start_dev = C.get<int64_t>(o_start);
+        double *const mean = C.get<double>(o_mean);
+        start.push_back(0);   // (after the groups: the one group of all rows)
+        start.push_back(n);
+        SA_HIP(hipMemcpyAsync(C.get<int32_t>(o_mem), members.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+        SA_HIP(hipMemcpyAsync(start_dev, start.data(), sizeof(int64_t) * (nc + 3), hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(group_means, dim3((unsigned)nc, (unsigned)dcol), dim3(64), 0, s, base, d, ld, C.get<int32_t>(o_mem),
+                           start_dev, mean);
+        hipLaunchKernelGGL(mean_dists, bn, t256, 0, s, base, n, d, ld, mean, comp, dist);
+        hipLaunchKernelGGL(fill_u64_n, dim3(blocks_for(nc, 256)), t256, 0, s, C.get<unsigned long long>(o_best), nc,
+                           (unsigned long long)KEY_EMPTY);
+        hipLaunchKernelGGL(fill_i32, dim3(blocks_for(nc, 256)), t256, 0, s, rep_dev, nc, INT32_MAX);
+        for (int pass = 0; pass < 2; ++pass)
+            hipLaunchKernelGGL(nearest_member, bn, t256, 0, s, dist, comp, n, pass, C.get<unsigned long long>(o_best), rep_dev);
+        SA_HIP(hipGetLastError());
+        std::vector<int32_t> rep((size_t)nc);
+        SA_HIP(hipMemcpyAsync(rep.data(), rep_dev, sizeof(int32_t) * nc, hipMemcpyDeviceToHost, s));
+        const bool want_hubs = hubs > 1;
+        std::vector<double> hd;
+        if (want_hubs) {
+            hipLaunchKernelGGL(group_means, dim3(1, (unsigned)dcol), dim3(64), 0, s, base, d, ld, (const int32_t *)nullptr,
+                               start_dev + nc + 1, mean);
+            hipLaunchKernelGGL(mean_dists, bn, t256, 0, s, base, n, d, ld, mean, (const int32_t *)nullptr, dist);
+            SA_HIP(hipGetLastError());
+            hd.resize((size_t)n);
+            SA_HIP(hipMemcpyAsync(hd.data(), dist, sizeof(double) * n, hipMemcpyDeviceToHost, s));
+        }
+        SA_HIP(hipStreamSynchronize(s));
+        std::vector<uint8_t> is_rep((size_t)n, 0);
+        for (int64_t c = 0; c < nc; ++c) is_rep[rep[c]] = 1;
+        std::vector<int32_t> src(rep);
+        if (!is_rep[entry]) src.push_back(entry);
+        if (want_hubs) {
             struct H {
                 double d;
                 int32_t v;
             };
             std::vector<H> hv;
-            hv.reserve(n);
-            for (int64_t v = 0; v < n; ++v) {
-                if (is_rep[v] || v == entry) continue;
-                double acc = 0.0;
-                for (int i = 0; i < d; ++i) {
-                    double t = (double)X[(size_t)v * ld + i] - mean[i];
-                    acc += t * t;
-                }
-                hv.push_back({acc, (int32_t)v});
-            }
+            hv.reserve((size_t)n);
+            for (int64_t v = 0; v < n; ++v)
+                if (!is_rep[v] && v != entry) hv.push_back({hd[v], (int32_t)v});
             const size_t take = std::min(hv.size(), (size_t)(hubs - 1));
             std::partial_sort(hv.begin(), hv.begin() + take, hv.end(),
                               [](const H &x, const H &y) { return x.d < y.d || (x.d == y.d && x.v < y.v); });
-            for (size_t j = 0; j < take; ++j) hub.push_back(hv[j].v);
+            for (size_t j = 0; j < take; ++j) src.push_back(hv[j].v);
         }
-    }
-    const int64_t nsrc = nc > 1 ? nc + (int64_t)hub.size() : 0;
-    if (nsrc > 0) {
-        // representative-to-representative distances, used by the occlusion test
-        std::vector<float> rd((size_t)nc * nc);
-        for (int64_t i = 0; i < nc; ++i)
-            for (int64_t j = 0; j < nc; ++j)
-                rd[(size_t)i * nc + j] = host_dist(&X[(size_t)rep[i] * ld], &X[(size_t)rep[j] * ld], d, metric);
-        std::vector<int32_t> links((size_t)nsrc * R, -1);
-        std::vector<int> kept_local(nsrc);
-        for (int64_t a = 0; a < nsrc; ++a) {
-            const int32_t v = a < nc ? rep[a] : hub[a - nc];
-            const int kl = a < nc ? keep_local : hub_keep_local;
-            kept_local[a] = kl;
-            const int cap = R - kl;
-            if (cap <= 0) continue;
-            struct Cd {
-                float d;
-                int32_t id;
-                int32_t c;
-                bool used;
-            };
-            std::vector<Cd> cand;
-            cand.reserve(nc);
-            for (int64_t c = 0; c < nc; ++c) {
-                if (rep[c] == v) continue;
-                cand.push_back({host_dist(&X[(size_t)v * ld], &X[(size_t)rep[c] * ld], d, metric), rep[c], (int32_t)c,
-                                false});
-            }
-            std::sort(cand.begin(), cand.end(), [](const Cd &x, const Cd &y) { return key_less_host(x.d, x.id, y.d, y.id); });
-            int32_t *out = &links[(size_t)a * R];
-            std::vector<int32_t> kc;
-            for (auto &c : cand) {
-                if ((int)kc.size() >= cap) break;
-                bool keep = true;
-                for (int32_t x : kc)
-                    if (rd[(size_t)x * nc + c.c] < c.d) {
-                        keep = false;
-                        break;
-                    }
-                if (keep) {
-                    kc.push_back(c.c);
-                    c.used = true;
-                }
-            }
-            int kept = 0;
-            for (int32_t x : kc) out[kept++] = rep[x];
-            for (auto &c : cand) {
-                if (kept >= cap) break;
-                if (!c.used) out[kept++] = c.id;
-            }
+        const int64_t nsrc = (int64_t)src.size();
+        Arena D;
+        const size_t o_src = D.want<int32_t>(nsrc), o_dv = D.want<float>(nsrc * nc), o_links = D.want<int32_t>(nsrc * R);
+        if (D.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+        int32_t *const src_dev = D.get<int32_t>(o_src), *const links = D.get<int32_t>(o_links);
+        float *const dv = D.get<float>(o_dv);
+        SA_HIP(hipMemcpyAsync(src_dev, src.data(), sizeof(int32_t) * nsrc, hipMemcpyHostToDevice, s));
+        // rows 0 .. nc - 1: distances between representatives, for the occlusion test
+        hipLaunchKernelGGL(pair_dists, dim3(blocks_for(nsrc * nc, 256)), t256, 0, s, base, d, ld, metric, src_dev, nsrc, rep_dev,
+                           nc, dv);
+        SA_HIP(hipGetLastError());
+        if (nc <= LINK_REPS) {
+            int P = 64;
+            while (P < nc) P <<= 1;
+            hipLaunchKernelGGL(link_kernel, dim3((unsigned)nsrc), t256, 9 * (size_t)P, s, src_dev, nc, rep_dev, comp, dv, dv, R,
+                               keep_local, hub_keep_local, P, links);
+            SA_HIP(hipGetLastError());
+        } else {
+            std::vector<float> hdv((size_t)(nsrc * nc));
+            SA_HIP(hipMemcpyAsync(hdv.data(), dv, sizeof(float) * hdv.size(), hipMemcpyDeviceToHost, s));
+            SA_HIP(hipStreamSynchronize(s));
+            std::vector<int32_t> hl((size_t)nsrc * R, -1);
+            host_links(src, rep, hdv, R, keep_local, hub_keep_local, hl);
+            SA_HIP(hipMemcpyAsync(links, hl.data(), sizeof(int32_t) * hl.size(), hipMemcpyHostToDevice, s));
+            SA_HIP(hipStreamSynchronize(s));
         }
-        for (int64_t a = 0; a < nsrc; ++a) {
-            const int32_t v = a < nc ? rep[a] : hub[a - nc];
-            int32_t *rw = &adj[(int64_t)v * R];
-            const int32_t *lk = &links[(size_t)a * R];
-            std::vector<int32_t> nr;
-            for (int r = 0; r < R && (int)nr.size() < kept_local[a]; ++r) {
-                const int32_t u = rw[r];
-                if (u < 0) continue;
-                if (std::find(lk, lk + R, u) != lk + R) continue;
-                nr.push_back(u);
-            }
-            for (int x = 0; x < R; ++x)
-                if (lk[x] >= 0) nr.push_back(lk[x]);
-            for (int r = 0; r < R; ++r) rw[r] = r < (int)nr.size() ? nr[r] : -1;
-        }
+        hipLaunchKernelGGL(gateway_rows, dim3((unsigned)nsrc), dim3(64), 0, s, src_dev, nc, links, R, keep_local, hub_keep_local,
+                           adj_dev);
+        SA_HIP(hipGetLastError());
+        SA_HIP(hipStreamSynchronize(s));
     }
 
     // (3) reachability: bridge every unreachable vertex, in id order, from the nearest
     // reachable vertex with a free slot
-    std::vector<uint8_t> mark(n, 0);
-    std::vector<int32_t> newly;
-    mark_from(adj, R, n, entry, mark, newly);
-    std::vector<int32_t> deg(n);
-    for (int64_t v = 0; v < n; ++v) {
-        int c = 0;
-        for (int r = 0; r < R; ++r) c += adj[v * R + r] >= 0;
-        deg[v] = c;
+    int32_t *const level = root, *const deg = flag, *const changed = A.get<int32_t>(o_chg);
+    uint8_t *const dmask = A.get<uint8_t>(o_mark);
+    hipLaunchKernelGGL(fill_i32, bn, t256, 0, s, level, n, -1);
+    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, level + entry, (int64_t)1, 0);
+    SA_HIP(hipGetLastError());
+    // A level a launch, eight launches a look at the flag; what is not finished after 128
+    // levels is a long thin graph, which the host walks faster (a level is some 6 us here).
+    bool done = false;
+    for (int32_t cur = 0; !done && cur < 128; cur += 8) {
+        for (int32_t i = 0; i < 8; ++i) {
+            if (i == 7) hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, changed, (int64_t)1, 0);
+            hipLaunchKernelGGL(bfs_level, dim3(blocks_for(n, 256)), t256, 0, s, adj_dev, n, R, level, cur + i, changed);
+        }
+        SA_HIP(hipGetLastError());
+        int32_t h = 0;
+        SA_HIP(hipMemcpyAsync(&h, changed, 4, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipStreamSynchronize(s));
+        done = h == 0;
     }
+    if (!done) {
+        std::vector<int32_t> adj((size_t)ne), lv((size_t)n), walk;
+        SA_HIP(hipMemcpyAsync(adj.data(), adj_dev, sizeof(int32_t) * ne, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipMemcpyAsync(lv.data(), level, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipStreamSynchronize(s));
+        for (int64_t v = 0; v < n; ++v)
+            if (lv[v] >= 0) walk.push_back((int32_t)v);
+        for (size_t h = 0; h < walk.size(); ++h)
+            for (int r = 0; r < R; ++r) {
+                const int32_t u = adj[(int64_t)walk[h] * R + r];
+                if (u < 0 || u >= n || lv[u] >= 0) continue;
+                lv[u] = 0;
+                walk.push_back(u);
+            }
+        SA_HIP(hipMemcpyAsync(level, lv.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+        SA_HIP(hipStreamSynchronize(s));
+    }
+    hipLaunchKernelGGL(level_marks, bn, t256, 0, s, level, n, dmask);
+    hipLaunchKernelGGL(row_degrees, dim3(blocks_for(n, 4)), t256, 0, s, adj_dev, n, R, 0, deg);
+    SA_HIP(hipGetLastError());
+    std::vector<uint8_t> mark((size_t)n);
+    SA_HIP(hipMemcpyAsync(mark.data(), dmask, n, hipMemcpyDeviceToHost, s));
+    SA_HIP(hipStreamSynchronize(s));
+    std::vector<int32_t> lost;   // unreachable vertices, in id order
+    for (int64_t v = 0; v < n; ++v)
+        if (!mark[v]) lost.push_back((int32_t)v);
     int64_t added = 0;
-    int64_t first_unmarked = 0;
-    while (first_unmarked < n && mark[first_unmarked]) ++first_unmarked;
-    if (first_unmarked < n) {
+    if (!lost.empty()) {
+        // Only rows and vectors of unreachable vertices are looked at from here on: a walk
+        // from one of them marks none but them.
+        const int64_t nl = (int64_t)lost.size();
+        constexpr int WIN = 256;
+        constexpr size_t MAX_NEW = 4096;
+        std::vector<int32_t> hdeg((size_t)n), lrow((size_t)nl * R);
+        std::vector<float> lvec((size_t)nl * d);
+        Arena G;
+        const size_t o_ids = G.want<int32_t>(nl), o_rows = G.want<int32_t>(nl * R), o_vecs = G.want<float>(nl * d);
+        const size_t o_us = G.want<int32_t>(WIN), o_res = G.want<unsigned long long>(WIN);
+        if (G.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+        int32_t *const ids = G.get<int32_t>(o_ids), *const dus = G.get<int32_t>(o_us);
+        unsigned long long *const dres = G.get<unsigned long long>(o_res);
+        SA_HIP(hipMemcpyAsync(hdeg.data(), deg, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipMemcpyAsync(ids, lost.data(), sizeof(int32_t) * nl, hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(gather_rows, dim3(blocks_for(nl * R, 256)), t256, 0, s, adj_dev, (int64_t)R, R, ids, nl,
+                           G.get<int32_t>(o_rows));
+        hipLaunchKernelGGL(gather_rows, dim3(blocks_for(nl * d, 256)), t256, 0, s, reinterpret_cast<const int32_t *>(base), ld, d,
+                           ids, nl, G.get<int32_t>(o_vecs));
+        SA_HIP(hipGetLastError());
+        SA_HIP(hipMemcpyAsync(lrow.data(), G.get<int32_t>(o_rows), sizeof(int32_t) * lrow.size(), hipMemcpyDeviceToHost, s));
+        SA_HIP(hipMemcpyAsync(lvec.data(), G.get<float>(o_vecs), sizeof(float) * lvec.size(), hipMemcpyDeviceToHost, s));
+        SA_HIP(hipStreamSynchronize(s));
+        auto slot_of = [&](int32_t v) { return (size_t)(std::lower_bound(lost.begin(), lost.end(), v) - lost.begin()); };
+        // marks src and what its rows reach; newly gets them in the order met
+        std::vector<int32_t> newly;
+        auto mark_from = [&](int32_t src) {
+            newly.clear();
+            if (mark[src]) return;
+            mark[src] = 1;
+            newly.push_back(src);
+            for (size_t h = 0; h < newly.size(); ++h) {
+                const int32_t *row = &lrow[slot_of(newly[h]) * R];
+                for (int r = 0; r < R; ++r) {
+                    const int32_t u = row[r];
+                    if (u < 0 || u >= n || mark[u]) continue;
+                    mark[u] = 1;
+                    newly.push_back(u);
+                }
+            }
+        };
         // In id order, as one at a time, but the searches go out in windows of WIN vertices:
         // one launch finds, for each, the nearest vertex with a free slot among those marked
         // when the window starts; processing the window in order, each answer is corrected
         // with the vertices marked since (the same distance arithmetic on the host), and
         // found again alone if its vertex has no free slot left.  The edges are those the
         // one-at-a-time loop adds.  A window ends early once many vertices were marked in it.
-        constexpr int WIN = 256;
-        constexpr size_t MAX_NEW = 4096;
-        DevBuf<uint8_t> dmask;
-        DevBuf<int32_t> ddeg, dus;
-        DevBuf<unsigned long long> dres;
-        if (dmask.alloc(n) != hipSuccess || ddeg.alloc(n) != hipSuccess || dus.alloc(WIN) != hipSuccess ||
-            dres.alloc(WIN) != hipSuccess)
-            return set_error(SA_ENOMEM, "repair: device allocation failed");
         std::vector<int32_t> us;
         std::vector<unsigned long long> res(WIN);
-        std::vector<int32_t> since;   // vertices marked since the window's searches
-        // nearest marked vertex with a free slot for each of us, under the current marks and degrees
+        std::vector<int32_t> since;      // vertices marked since the window's searches
+        std::vector<int64_t> edit_pos;   // the edges added
+        std::vector<int32_t> edit_val;
+        // nearest marked vertex with a free slot for each of q, under the current marks and degrees
         auto search = [&](const std::vector<int32_t> &q) -> int {
-            SA_HIP(hipMemcpyAsync(dmask.p, mark.data(), n, hipMemcpyHostToDevice, s));
-            SA_HIP(hipMemcpyAsync(ddeg.p, deg.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-            SA_HIP(hipMemcpyAsync(dus.p, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice, s));
-            hipLaunchKernelGGL(fill_u64_n, dim3(1), dim3(WIN), 0, s, dres.p, (int64_t)q.size(),
-                               (unsigned long long)KEY_EMPTY);
-            hipLaunchKernelGGL(nearest_marked_batch, dim3((unsigned)((n + 255) / 256), (unsigned)q.size()), dim3(256),
-                               0, s, base, n, d, ld, metric, dmask.p, ddeg.p, R, dus.p, dres.p);
+            SA_HIP(hipMemcpyAsync(dmask, mark.data(), n, hipMemcpyHostToDevice, s));
+            SA_HIP(hipMemcpyAsync(deg, hdeg.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+            SA_HIP(hipMemcpyAsync(dus, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice, s));
+            hipLaunchKernelGGL(fill_u64_n, dim3(1), dim3(WIN), 0, s, dres, (int64_t)q.size(), (unsigned long long)KEY_EMPTY);
+            hipLaunchKernelGGL(nearest_marked_batch, dim3(blocks_for(n, 256), blocks_for((int64_t)q.size(), NM_Q)), t256, 0, s,
+                               base, n, d, ld, metric, dmask, deg, R, dus, (int)q.size(), dres);
             SA_HIP(hipGetLastError());
-            SA_HIP(hipMemcpyAsync(res.data(), dres.p, sizeof(unsigned long long) * q.size(), hipMemcpyDeviceToHost, s));
+            SA_HIP(hipMemcpyAsync(res.data(), dres, sizeof(unsigned long long) * q.size(), hipMemcpyDeviceToHost, s));
             SA_HIP(hipStreamSynchronize(s));
             return SA_OK;
         };
-        int64_t next = first_unmarked;
-        while (next < n) {
+        size_t next = 0;   // place in lost
+        while (next < lost.size()) {
             us.clear();
-            for (int64_t u = next; u < n && (int)us.size() < WIN; ++u)
-                if (!mark[u]) us.push_back((int32_t)u);
+            size_t at = next;
+            for (; at < lost.size() && (int)us.size() < WIN; ++at)
+                if (!mark[lost[at]]) us.push_back(lost[at]);
             if (us.empty()) break;
             int rc = search(us);
             if (rc != SA_OK) return rc;
             since.clear();
-            next = (int64_t)us.back() + 1;
+            next = at;
             for (size_t j = 0; j < us.size(); ++j) {
                 const int32_t u = us[j];
                 if (mark[u]) continue;
+                const size_t su = slot_of(u);
                 if (since.size() > MAX_NEW) {   // many new candidates: search the rest of the window again
-                    next = u;
+                    next = su;
                     break;
                 }
                 // the window's answer is the best over the vertices marked at its start; those
                 // that filled up since cannot be taken, and those marked since are candidates
                 unsigned long long best = res[j];
-                if (best != KEY_EMPTY && deg[key_id(best)] >= R) {
+                if (best != KEY_EMPTY && hdeg[key_id(best)] >= R) {
                     const std::vector<unsigned long long> saved(res);
                     if ((rc = search(std::vector<int32_t>{u})) != SA_OK) return rc;
                     best = res[0];
                     res = saved;
                 } else {
                     for (int32_t w : since)
-                        if (deg[w] < R) {
+                        if (hdeg[w] < R) {
                             const unsigned long long k =
-                                make_key(host_dist(&X[(size_t)w * ld], &X[(size_t)u * ld], d, metric), w);
+                                make_key(host_dist(&lvec[slot_of(w) * d], &lvec[su * d], d, metric), w);
                             if (k < best) best = k;
                         }
                 }
                 if (best == KEY_EMPTY) return set_error(SA_ECAPACITY, "repair: no reachable vertex has a free slot");
                 const int32_t r = key_id(best);
-                adj[(int64_t)r * R + deg[r]] = u;
-                deg[r]++;
+                edit_pos.push_back((int64_t)r * R + hdeg[r]);
+                edit_val.push_back(u);
+                hdeg[r]++;
                 ++added;
-                mark_from(adj, R, n, u, mark, newly);
+                mark_from(u);
                 since.insert(since.end(), newly.begin(), newly.end());
             }
         }
+        Arena E;
+        const size_t o_pos = E.want<int64_t>(added), o_val = E.want<int32_t>(added);
+        if (E.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+        SA_HIP(hipMemcpyAsync(E.get<int64_t>(o_pos), edit_pos.data(), sizeof(int64_t) * added, hipMemcpyHostToDevice, s));
+        SA_HIP(hipMemcpyAsync(E.get<int32_t>(o_val), edit_val.data(), sizeof(int32_t) * added, hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(apply_edits, dim3(blocks_for(added, 256)), t256, 0, s, E.get<int64_t>(o_pos), E.get<int32_t>(o_val),
+                           added, adj_dev);
+        SA_HIP(hipGetLastError());
+        SA_HIP(hipStreamSynchronize(s));
     }
-    SA_HIP(hipMemcpyAsync(adj_dev, adj.data(), sizeof(int32_t) * adj.size(), hipMemcpyHostToDevice, s));
-    SA_HIP(hipStreamSynchronize(s));
     if (bridges_out) *bridges_out = added;
     return SA_OK;
 }
