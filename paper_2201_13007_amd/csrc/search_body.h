@@ -110,7 +110,11 @@ __device__ __forceinline__ void release_jobs(int32_t *ctr)
     }
 }
 
-__device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << __lane_id()) - 1ull; }
+// set bits of the wave-uniform m in the lanes below this one
+__device__ __forceinline__ int bits_below(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
 __device__ __forceinline__ uint32_t hash_slot(uint32_t id, int log2cap)
 {
@@ -177,6 +181,14 @@ __device__ __forceinline__ uint32_t dpp32(uint32_t v, uint32_t old)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWMASK, 0xF, false);
 }
 
+// v of the lane N below in its row of 16, zero in the first N lanes (in a form that the
+// compiler folds into the instruction that uses it)
+template <int N>
+__device__ __forceinline__ uint32_t row_shr0(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_ROW_SHR + N, 0xF, 0xF, true);
+}
+
 template <int CTRL, int ROWMASK = 0xF>
 __device__ __forceinline__ double dpp_f64(double v)
 {
@@ -203,10 +215,10 @@ __device__ __forceinline__ double group_sum(double v)
 template <int LPV>
 __device__ __forceinline__ float group_sum_f32(float v)
 {
-    if constexpr (LPV >= 2) v += __uint_as_float(dpp32<DPP_ROW_SHR + 1>(__float_as_uint(v), 0u));
-    if constexpr (LPV >= 4) v += __uint_as_float(dpp32<DPP_ROW_SHR + 2>(__float_as_uint(v), 0u));
-    if constexpr (LPV >= 8) v += __uint_as_float(dpp32<DPP_ROW_SHR + 4>(__float_as_uint(v), 0u));
-    if constexpr (LPV >= 16) v += __uint_as_float(dpp32<DPP_ROW_SHR + 8>(__float_as_uint(v), 0u));
+    if constexpr (LPV >= 2) v += __uint_as_float(row_shr0<1>(__float_as_uint(v)));
+    if constexpr (LPV >= 4) v += __uint_as_float(row_shr0<2>(__float_as_uint(v)));
+    if constexpr (LPV >= 8) v += __uint_as_float(row_shr0<4>(__float_as_uint(v)));
+    if constexpr (LPV >= 16) v += __uint_as_float(row_shr0<8>(__float_as_uint(v)));
     if constexpr (LPV >= 32) v += __uint_as_float(dpp32<DPP_ROW_BCAST15, 0xA>(__float_as_uint(v), 0u));
     if constexpr (LPV >= 64) v += __uint_as_float(dpp32<DPP_ROW_BCAST31, 0xC>(__float_as_uint(v), 0u));
     return v;
@@ -242,68 +254,73 @@ struct VecSrc {
     int64_t ld;
 };
 
-// Coordinates 4c .. 4c+3 of a row as stored: this raw form is what stays in registers
-// while the loads are in flight, and is decoded where the distance uses it.
+// Four coordinates of a row as stored: this raw form is what stays in registers while the
+// loads are in flight, and is decoded where the distance uses it.
 template <int DT> struct Raw4T { using type = uint32_t; };
 template <> struct Raw4T<SA_F32> { using type = float4; };
 template <> struct Raw4T<SA_BF16> { using type = uint2; };
 template <int DT> using Raw4 = typename Raw4T<DT>::type;
 
-template <int DT>
-__device__ __forceinline__ Raw4<DT> load_raw4(const VecSrc &V, int32_t id, int c)
-{
-    if constexpr (DT == SA_F32)
-        return *reinterpret_cast<const float4 *>(static_cast<const float *>(V.p) + (int64_t)id * V.ld + 4 * c);
-    else if constexpr (DT == SA_BF16)
-        return *(reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(V.p) + (int64_t)id * V.ld) + c);
-    else
-        return *(reinterpret_cast<const uint32_t *>(static_cast<const uint8_t *>(V.p) + (int64_t)id * V.ld) + c);
-}
-
 // Keys of the vectors ids[0..n) (n <= 64) to out[0..n), 64 / LPV vectors per pass; qs is
-// the query, zero padded to 16 LPV floats.  The loads are issued unconditionally, from
-// clamped addresses (a dropped id reads row 0): loads under lane conditions each get their
-// own wait, which would turn one memory round trip into four.  (Written as a pass loop
-// over arrays: the same steps as a per-vector helper cost some twenty more registers.)
+// the query, zero padded to 16 LPV floats.  ids[n..64) must be rows of the index too (any;
+// a pass reads them with the rest), and out[n..64) is overwritten.  The loads are issued
+// unconditionally, from clamped addresses, and the empty asm keeps them there: a load that
+// the compiler moves under a lane condition gets a wait of its own, which turns one memory
+// round trip into two.  (Written as a pass loop over arrays: the same steps as a per-vector
+// helper cost some twenty more registers.)
 // ACC32: accumulate in float32 (only where every partial sum is an integer below 2^24, so
 // that the float32 sum is exact and equals the double one)
 // PB: vectors per lane group in one pass (PB 64 / LPV a pass, each pass one memory round
 // trip; each more in flight costs sixteen registers at d = 128)
-template <int LPV, bool L2, int DT, bool ACC32 = false, int PB = 1>
+//
+// The searches issue instructions for a quarter (many queries) to half (few) of a wave's
+// life, so a pass is kept short: the query is read and converted once for all of its
+// vectors, products that are exact (inner products of float32 in double, everything with
+// ACC32) go through one fused multiply-add, and only a lane's third and fourth chunk are
+// masked, the ones that can lie past the row's end (LPV is the smallest power of two with
+// 4 LPV >= chunks).
+template <int LPV, bool L2, int DT, bool ACC32 = false, int PBMAX = 1>
 __device__ __forceinline__ void distances(const VecSrc &V, int d, const float *qs, const int32_t *ids, int n,
                                           uint64_t *out)
 {
     constexpr int VPW = 64 / LPV;
+    constexpr int PB = PBMAX < LPV ? PBMAX : LPV;   // VPW PB <= 64
+    constexpr int SURE = LPV == 1 ? 1 : 2;          // chunks inside the row for every lane
+    using Acc = typename std::conditional<ACC32, float, double>::type;
     const int lane = __lane_id(), grp = lane / LPV, g = lane % LPV;
     const int nch = d >> 2;
+    constexpr int CB = sizeof(Raw4<DT>);            // bytes of a chunk
+    const uint64_t stride = (uint64_t)V.ld * (CB / 4);
+    const char *const lane_base = static_cast<const char *>(V.p) + g * CB;
     for (int p0 = 0; p0 < n; p0 += VPW * PB) {
         Raw4<DT> x[PB][4];
         float sc[PB];
         int32_t id[PB];
 #pragma unroll
         for (int pp = 0; pp < PB; ++pp) {
-            const int idx = p0 + pp * VPW + grp;
-            const int32_t raw = ids[idx & 63];
-            id[pp] = idx < n ? raw : -1;
-            const int32_t row = id[pp] < 0 ? 0 : id[pp];
+            id[pp] = ids[p0 + pp * VPW + grp];
+            const char *const row = lane_base + (uint64_t)(uint32_t)id[pp] * stride;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = g + LPV * i;
-                x[pp][i] = load_raw4<DT>(V, row, c < nch ? c : 0);
-            }
-            sc[pp] = DT == SA_FP8E4M3 ? V.scale[row] : 1.f;
+            for (int i = 0; i < 4; ++i)
+                x[pp][i] = *reinterpret_cast<const Raw4<DT> *>(
+                    row + (i < SURE || g + LPV * i < nch ? LPV * i * CB : 0));
+            sc[pp] = DT == SA_FP8E4M3 ? V.scale[id[pp]] : 1.f;
         }
+        asm volatile("" ::: "memory");
+        Acc acc[PB];
 #pragma unroll
-        for (int pp = 0; pp < PB; ++pp) {
-            using Acc = typename std::conditional<ACC32, float, double>::type;
-            Acc acc = 0;
+        for (int pp = 0; pp < PB; ++pp) acc[pp] = 0;
+        float4 an = reinterpret_cast<const float4 *>(qs)[g];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const bool in = g + LPV * i < nch;
-                const float4 a = reinterpret_cast<const float4 *>(qs)[g + LPV * i];
-                // codes outside the row are taken as code 0, which is 0.0 in every storage
-                // type; the selects act on the loaded registers themselves (on a decoded
-                // copy they cost some twenty-five more registers)
+        for (int i = 0; i < 4; ++i) {
+            const bool in = i < SURE || g + LPV * i < nch;
+            const float4 a = an;
+            if (i < 3) an = reinterpret_cast<const float4 *>(qs)[g + LPV * (i + 1)];
+            __builtin_amdgcn_sched_barrier(0);
+            const Acc ax = (Acc)a.x, ay = (Acc)a.y, az = (Acc)a.z, aw = (Acc)a.w;
+#pragma unroll
+            for (int pp = 0; pp < PB; ++pp) {
+                // codes outside the row are taken as code 0, which is 0.0 in every storage type
                 float bx, by, bz, bw;
                 if constexpr (DT == SA_F32) {
                     bx = in ? x[pp][i].x : 0.f; by = in ? x[pp][i].y : 0.f;
@@ -313,36 +330,48 @@ __device__ __forceinline__ void distances(const VecSrc &V, int d, const float *q
                     bx = __uint_as_float(lo << 16); by = __uint_as_float(lo & 0xFFFF0000u);
                     bz = __uint_as_float(hi << 16); bw = __uint_as_float(hi & 0xFFFF0000u);
                 } else {
-                    // e4m3 -> f16 bit pattern: same mantissa bits, exponent bias 15 instead
-                    // of 7, so every value, subnormals included, comes out 2^-8 too small;
-                    // 2^8 joins the scale, and s * 2^8 * v rounds once like s * value.  (The
-                    // hardware fp8 conversion gives the same values but its vector results
-                    // cost the caller about twenty registers.)  Codes 0x7F / 0xFF, NaN in
-                    // e4m3, are never written and decode as 480 / -480 here.
-                    const uint32_t w = in ? x[pp][i] : 0u;
-                    const uint32_t h0 = ((w & 0x7Fu) << 7) | ((w & 0x80u) << 8);
-                    const uint32_t h1 = ((w >> 8 & 0x7Fu) << 7) | ((w >> 8 & 0x80u) << 8);
-                    const uint32_t h2 = ((w >> 16 & 0x7Fu) << 7) | ((w >> 16 & 0x80u) << 8);
-                    const uint32_t h3 = ((w >> 24 & 0x7Fu) << 7) | ((w >> 24 & 0x80u) << 8);
-                    const float s = sc[pp] * 256.f;
-                    bx = s * (float)__builtin_bit_cast(_Float16, (uint16_t)h0);
-                    by = s * (float)__builtin_bit_cast(_Float16, (uint16_t)h1);
-                    bz = s * (float)__builtin_bit_cast(_Float16, (uint16_t)h2);
-                    bw = s * (float)__builtin_bit_cast(_Float16, (uint16_t)h3);
+                    // e4m3 -> f16 bit pattern, two codes at a time: same mantissa bits,
+                    // exponent bias 15 instead of 7, so every value, subnormals included,
+                    // comes out 2^-8 too small; 2^8 joins the scale, and s * 2^8 * v rounds
+                    // once like s * value.  (The hardware fp8 conversion gives the same
+                    // values for every code that is written, but not for codes 0x7F / 0xFF,
+                    // NaN in e4m3, which decode as 480 / -480 here.)
+                    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+                    const uint32_t w = in ? x[pp][i] : 0u, w1 = w >> 8;
+                    const uint32_t h02 = ((w & 0x007F007Fu) << 7) | ((w & 0x00800080u) << 8);
+                    const uint32_t h13 = ((w1 & 0x007F007Fu) << 7) | ((w1 & 0x00800080u) << 8);
+                    const half2v e02 = __builtin_bit_cast(half2v, h02), e13 = __builtin_bit_cast(half2v, h13);
+                    const float s8 = sc[pp] * 256.f;
+                    bx = s8 * (float)e02.x;
+                    by = s8 * (float)e13.x;
+                    bz = s8 * (float)e02.y;
+                    bw = s8 * (float)e13.y;
                 }
+                Acc s = acc[pp];
                 if constexpr (L2) {
-                    const Acc t0 = (Acc)a.x - (Acc)bx, t1 = (Acc)a.y - (Acc)by;
-                    const Acc t2 = (Acc)a.z - (Acc)bz, t3 = (Acc)a.w - (Acc)bw;
-                    acc += t0 * t0; acc += t1 * t1; acc += t2 * t2; acc += t3 * t3;
+                    const Acc t0 = ax - (Acc)bx, t1 = ay - (Acc)by, t2 = az - (Acc)bz, t3 = aw - (Acc)bw;
+                    if constexpr (ACC32) {
+                        s = __builtin_fmaf(t0, t0, s); s = __builtin_fmaf(t1, t1, s);
+                        s = __builtin_fmaf(t2, t2, s); s = __builtin_fmaf(t3, t3, s);
+                    } else {
+                        s += t0 * t0; s += t1 * t1; s += t2 * t2; s += t3 * t3;
+                    }
+                } else if constexpr (ACC32) {
+                    s = __builtin_fmaf(ax, bx, s); s = __builtin_fmaf(ay, by, s);
+                    s = __builtin_fmaf(az, bz, s); s = __builtin_fmaf(aw, bw, s);
                 } else {
-                    acc += (Acc)a.x * (Acc)bx; acc += (Acc)a.y * (Acc)by;
-                    acc += (Acc)a.z * (Acc)bz; acc += (Acc)a.w * (Acc)bw;
+                    s = __builtin_fma(ax, (Acc)bx, s); s = __builtin_fma(ay, (Acc)by, s);
+                    s = __builtin_fma(az, (Acc)bz, s); s = __builtin_fma(aw, (Acc)bw, s);
                 }
+                acc[pp] = s;
             }
-            if constexpr (ACC32) acc = group_sum_f32<LPV>(acc);
-            else acc = group_sum<LPV>(acc);
-            const int idx = p0 + pp * VPW + grp;
-            if (g == LPV - 1 && idx < n) out[idx] = make_key(L2 ? (float)acc : (float)(-acc), id[pp]);
+        }
+#pragma unroll
+        for (int pp = 0; pp < PB; ++pp) {
+            Acc s = acc[pp];
+            if constexpr (ACC32) s = group_sum_f32<LPV>(s);
+            else s = group_sum<LPV>(s);
+            if (g == LPV - 1) out[p0 + pp * VPW + grp] = make_key(L2 ? (float)s : (float)(-s), id[pp]);
         }
     }
 }
@@ -489,7 +518,7 @@ __device__ __forceinline__ void record_slots(bool rec, uint32_t slot, int32_t *b
     int base = 0;
     if (__lane_id() == 0) base = atomicAdd(base_counter, __popcll(b));
     base = __shfl(base, 0, 64);
-    if (rec) slots[base + __popcll(b & lanemask_lt())] = slot;
+    if (rec) slots[base + bits_below(b)] = slot;
 }
 
 // Moves the LDS visited table into the (zero-filled) workspace table.
@@ -576,7 +605,7 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
 
     // the start point: its distance, the list holding only it, and the visited set
     if (w == 0) {
-        if (lane == 0) claim[0] = A.entry;
+        claim[lane] = A.entry;
         __builtin_amdgcn_wave_barrier();
         if (l2) distances<LPV, true, DT>(V, A.d, qs, claim, 1, nkey);
         else distances<LPV, false, DT>(V, A.d, qs, claim, 1, nkey);
@@ -653,7 +682,8 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                     const uint64_t cm = __ballot(fresh);
                     const int nclaim = __popcll(cm);
                     hcount += nclaim;
-                    if (fresh) claim[__popcll(cm & lanemask_lt())] = u;
+                    claim[lane] = 0;   // (the distances of a pass read 64 ids)
+                    if (fresh) claim[bits_below(cm)] = u;
                     __builtin_amdgcn_wave_barrier();
                     if (l2) distances<LPV, true, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
                     else distances<LPV, false, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
@@ -751,7 +781,7 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                 const uint8_t chk = valid ? Sc[j] : 1;
                 const bool unc = valid && !chk;
                 const uint64_t msk = __ballot(unc);
-                const int r = running + __popcll(msk & lanemask_lt());
+                const int r = running + bits_below(msk);
                 running += __popcll(msk);
                 if (w < m && valid) {
                     ls.k[i] = S[j];
@@ -822,7 +852,8 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                     if (mode) record_slots(fresh, slot, &C->nslot, gslots);
                     const uint64_t cm = __ballot(claimed);
                     const int nclaim = __popcll(cm);
-                    if (claimed) claim[__popcll(cm & lanemask_lt())] = u;
+                    claim[lane] = 0;   // (the distances of a pass read 64 ids)
+                    if (claimed) claim[bits_below(cm)] = u;
                     __builtin_amdgcn_wave_barrier();
                     if (l2) distances<LPV, true, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
                     else distances<LPV, false, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
@@ -917,7 +948,7 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                     const int p = i * 64 + lane;
                     const bool isN = w < m && p < len && (ls.m[i] & META_SIDX) == META_SIDX;
                     const uint64_t nm = __ballot(isN);
-                    rk[i] = p - (nb + __popcll(nm & lanemask_lt()));
+                    rk[i] = p - (nb + bits_below(nm));
                     nb += __popcll(nm);
                 }
             }
@@ -930,7 +961,7 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                         const int p = i * 64 + lane;
                         const bool isN = p < len && (ls.m[i] & META_SIDX) == META_SIDX;
                         const uint64_t nm = __ballot(isN);
-                        const int g = nb + __popcll(nm & lanemask_lt()) - c0;
+                        const int g = nb + bits_below(nm) - c0;
                         if (isN && g >= 0 && g < cn) pub[g] = ls.k[i];
                         nb += __popcll(nm);
                     }

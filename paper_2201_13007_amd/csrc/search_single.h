@@ -8,10 +8,9 @@
 // the latency of the random reads.
 //
 // Queue.  NI = ceil(L / 64) slots per lane hold the sorted 64-bit keys (order-preserving
-// distance bits, id); entry p sits in slot p / 64 of lane p % 64.  The CHECKED flags are
-// wave-uniform 64-bit masks, one per slot, so finding the first unchecked entry is scalar
-// work.  The new entries of a step are merged in one pass: each destination computes how
-// many of them land below it and pulls its old entry with a cross-lane permute.
+// distance bits, id); entry p sits in slot p / 64 of lane p % 64.  The unchecked entries are
+// wave-uniform 64-bit masks, one per slot, so finding the first of them is scalar work.
+// The new entries of a step are merged in one pass (see insert_batch).
 //
 // Visited set.  Open addressing over 32-bit entries (id + 1; zero is empty) in the
 // query's workspace region, claimed with compare-and-swap; the first probe of a vertex
@@ -36,12 +35,12 @@ namespace single_detail {
 using search_detail::KArgs;
 using search_detail::NO_SLOT;
 
-// LDS of a wavefront besides the filter of recently seen vertices: new keys, new ids, the
-// query row
+// LDS of a wavefront besides the filter of recently seen vertices: new keys (64, one that
+// the insert drops what it does not want into, one for alignment), new ids, the query row
 template <int LPV>
 constexpr uint32_t single_lds_base()
 {
-    return 64 * 8 + 64 * 4 + 64 * LPV;
+    return 66 * 8 + 64 * 4 + 64 * LPV;
 }
 
 // log2 of the sets of the per-query LDS filter of recently seen vertices (one 32-bit word
@@ -57,48 +56,46 @@ constexpr int seen_log2()
     return l;
 }
 using search_detail::VecSrc;
-using search_detail::bpermute64;
 using search_detail::distances;
 using search_detail::rerank_list;
-using search_detail::lanemask_lt;
-using search_detail::low_bits;
+using search_detail::bits_below;
+using search_detail::rdlane;
 using search_detail::rdlane64;
 
 template <int NI>
 struct Queue {
     uint64_t k[NI];    // keys; KEY_EMPTY past the end
-    uint64_t chk[NI];  // CHECKED bits (wave-uniform)
+    uint64_t un[NI];   // unchecked entries (wave-uniform; zero past the end)
     int len;
 };
 
-template <int NI>
-__device__ __forceinline__ int first_unchecked(const Queue<NI> &Q)
+// Takes the first entry of the masks m (one bit per queue entry) out of them and returns its
+// id, or -1 if they are empty.  The key is read with a lane read in the branch of its slot:
+// an access indexed by the slot would make the compiler move the arrays to scratch memory.
+template <int NI, int I = 0>
+__device__ __forceinline__ int32_t take_first(const uint64_t (&k)[NI], uint64_t (&m)[NI])
 {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const uint64_t b = low_bits(Q.len - 64 * i) & ~Q.chk[i];
-        if (b) return 64 * i + __builtin_ctzll(b);
+    if constexpr (I < NI) {
+        if (m[I] != 0ull) {
+            const int b = __builtin_ctzll(m[I]);
+            m[I] &= m[I] - 1ull;
+            return (int32_t)rdlane((uint32_t)k[I], b);
+        }
+        return take_first<NI, I + 1>(k, m);
     }
-    return 64 * NI;
+    return -1;
 }
 
-// first unchecked position after p (p may be 64 NI)
 template <int NI>
-__device__ __forceinline__ int next_unchecked(const Queue<NI> &Q, int p)
+__device__ __forceinline__ bool any_unchecked(const Queue<NI> &Q)
 {
+    uint64_t b = 0;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int lo = p + 1 - 64 * i;   // positions of this slot below lo are excluded
-        const uint64_t keep = lo <= 0 ? ~0ull : (lo >= 64 ? 0ull : (~0ull << lo));
-        const uint64_t b = low_bits(Q.len - 64 * i) & ~Q.chk[i] & keep;
-        if (b) return 64 * i + __builtin_ctzll(b);
-    }
-    return 64 * NI;
+    for (int i = 0; i < NI; ++i) b |= Q.un[i];
+    return b != 0ull;
 }
 
-// Uniform position p: the key is read with a lane read in the branch of its slot, and a
-// flag is set by a masked update of every slot.  Folding either into an access indexed by
-// p / 64 would make the compiler move the arrays to scratch memory.
+// key at the uniform position p
 template <int NI>
 __device__ __forceinline__ uint64_t get_key(const Queue<NI> &Q, int p)
 {
@@ -109,83 +106,81 @@ __device__ __forceinline__ uint64_t get_key(const Queue<NI> &Q, int p)
     return r;
 }
 
-template <int NI>
-__device__ __forceinline__ void mark_checked(Queue<NI> &Q, int p)
-{
-    const int s = p >> 6;
-    const uint64_t bit = 1ull << (p & 63);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) Q.chk[i] |= s == i ? bit : 0ull;
-}
-
-template <int NI>
-__device__ __forceinline__ int count_less(const Queue<NI> &Q, uint64_t key)
-{
-    int c = 0;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) c += __popcll(__ballot(Q.k[i] < key));
-    return c;
-}
-
 // Inserts the unchecked keys mk of the lanes in sbits (distinct, none in the queue),
 // keeping at most L entries, and returns the update position: the best position one of
-// them takes (L if none stays).  One pass for the whole batch: the key of rank r among
-// them lands at f = (queue keys below it) + r; the landing positions form a bit mask per
-// slot, and every other destination P takes the old entry at P - c(P), c(P) the number
-// of landings below P, which lies in P's slot or the one before at lane (P - c(P)) mod
-// 64.  stage (LDS, 64 keys) receives the batch sorted by rank.
+// them takes (L if none stays).  One compare per new key and slot gives both the key's
+// place (queue keys below it; its rank among the new keys is added per lane) and, summed
+// per lane, how far each old entry moves up.  Then each slot from the last down to the
+// first that changes is put together in LDS: its own entries that stay in it, those that
+// come up from the slot below (none moves by more than 64) and the new ones.  The
+// unchecked flags travel as bit 31 of the ids.  stage: 65 keys of LDS; the last takes what
+// lands elsewhere.
+//
+// This replaced a form that kept a landing mask per slot and pulled every entry with
+// cross-lane permutes: some 60 instructions per new key and 30 per slot against 25 and 25.
+// With 10 new keys a step that was half of a step's 1,300 instructions.
 template <int NI>
 __device__ __forceinline__ int insert_batch(Queue<NI> &Q, int L, uint64_t mk, uint64_t sbits, uint64_t *stage)
 {
     const int lane = __lane_id();
-    const bool surv = (sbits >> lane) & 1ull;
-    uint64_t land[NI];
+    // new keys below each entry: kept from the same compares up to four slots per lane;
+    // beyond, where the registers would cost waves, counted again per slot from the places
+    // (a new key is below entry p if its place among the old ones is at most p)
+    constexpr bool KEEP = NI <= 4;
+    int shift[KEEP ? NI : 1];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) land[i] = 0;
+    for (int i = 0; i < (KEEP ? NI : 1); ++i) shift[i] = 0;
+    int f = 1 << 20;   // where this lane's new key lands
+    int r = 0;         // new keys below it
     int fmin = L;
     for (uint64_t b = sbits; b; b &= b - 1) {
         const int j = __builtin_ctzll(b);
         const uint64_t kj = rdlane64(mk, j);
-        const int r = __popcll(__ballot(surv && mk < kj));
-        const int f = count_less(Q, kj) + r;
-        if (lane == 0) stage[r] = kj;
-        fmin = min(fmin, f);
-        const uint64_t bit = f < L ? 1ull << (f & 63) : 0ull;
+        int below = 64 * NI;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) land[i] |= (f >> 6) == i ? bit : 0ull;
+        for (int i = 0; i < NI; ++i) {
+            const bool above = Q.k[i] > kj;
+            if constexpr (KEEP) shift[i] += above ? 1 : 0;
+            below -= __popcll(__ballot(above));
+        }
+        r += kj < mk ? 1 : 0;
+        f = lane == j ? below : f;
+        fmin = min(fmin, below);   // the best new key has no other below it
     }
-    __builtin_amdgcn_wave_barrier();
     if (fmin >= L) return L;
+    const int place = f;
+    f += r;
+    const auto moves = [&](int i) {   // by how much this lane's entry of slot i moves up
+        if constexpr (KEEP) return shift[i];
+        const int p = 64 * i + lane;
+        int c = 0;
+        for (uint64_t b = sbits; b; b &= b - 1) c += (int)rdlane((uint32_t)place, __builtin_ctzll(b)) <= p ? 1 : 0;
+        return c;
+    };
     const int nlen = min(L, Q.len + __popcll(sbits));
     const int i_first = fmin >> 6;
-    int below = 0;   // landings in the slots under slot i
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-        if (i < i_first) below += __popcll(land[i]);
-    int base[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        base[i] = below;
-        if (i >= i_first) below += __popcll(land[i]);
-    }
+    int mine = moves(NI - 1);
 #pragma unroll
     for (int i = NI - 1; i >= 0; --i) {
         if (i < i_first) continue;
-        const int c = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(land[i] >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)land[i], (uint32_t)base[i]));
-        const bool lands = (land[i] >> lane) & 1ull;
-        const int src = (lane - c) & 63;
-        const int addr = src << 2;
-        const bool from_prev = lane < c;
-        const uint64_t cur = bpermute64(addr, Q.k[i]);
-        const uint64_t prv = i > 0 ? bpermute64(addr, Q.k[i > 0 ? i - 1 : 0]) : KEY_EMPTY;
-        const uint64_t prv_chk = i > 0 ? Q.chk[i > 0 ? i - 1 : 0] : 0ull;
-        const uint64_t sk = stage[c & 63];
-        const int P = 64 * i + lane;
-        const uint64_t ob = ((from_prev ? prv_chk : Q.chk[i]) >> src) & 1ull;
-        const bool keep = P < nlen;
-        Q.k[i] = keep ? (lands ? sk : (from_prev ? prv : cur)) : KEY_EMPTY;
-        Q.chk[i] = __ballot(keep && !lands && ob);
+        const int below = i > 0 ? moves(i > 0 ? i - 1 : 0) : 0;   // moves of the slot below
+        // offsets within the slot, 64 for what lands elsewhere
+        const uint32_t own = min((uint32_t)(lane + mine), 64u);
+        const uint32_t add = min((uint32_t)(f - 64 * i), 64u);
+        stage[own] = Q.k[i] | (__builtin_amdgcn_inverse_ballot_w64(Q.un[i]) ? 0x80000000ull : 0ull);
+        if (i > 0) {
+            const uint32_t up = min((uint32_t)(lane + below - 64), 64u);
+            stage[up] = Q.k[i > 0 ? i - 1 : 0] |
+                        (__builtin_amdgcn_inverse_ballot_w64(Q.un[i > 0 ? i - 1 : 0]) ? 0x80000000ull : 0ull);
+        }
+        stage[add] = mk | 0x80000000ull;
+        __builtin_amdgcn_wave_barrier();
+        const uint64_t v = stage[lane];
+        __builtin_amdgcn_wave_barrier();
+        const bool keep = lane < nlen - 64 * i;
+        Q.un[i] = __ballot(keep && ((uint32_t)v >> 31) != 0u);
+        Q.k[i] = keep ? v & ~0x80000000ull : KEY_EMPTY;
+        mine = below;
     }
     Q.len = nlen;
     return fmin;
@@ -261,7 +256,7 @@ __device__ __forceinline__ int grow_table(uint32_t *tbl, uint32_t *scratch, int 
     for (int b = 0; b < (1 << t1); b += 64) {   // 2^t1 >= 64 entries
         const uint32_t e = tbl[b + lane];
         const uint64_t m = __ballot(e != 0u);
-        if (e != 0u) scratch[cnt + __popcll(m & lanemask_lt())] = e;
+        if (e != 0u) scratch[cnt + bits_below(m)] = e;
         tbl[b + lane] = 0u;
         cnt += __popcll(m);
     }
@@ -289,8 +284,8 @@ template <int LPV, int NI, bool L2, int DT, bool ACC32>
 __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_t *tbl)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint64_t *const nkey = reinterpret_cast<uint64_t *>(smem);    // [64] keys of new vertices
-    int32_t *const sid = reinterpret_cast<int32_t *>(nkey + 64);   // [64] their ids
+    uint64_t *const nkey = reinterpret_cast<uint64_t *>(smem);    // [66] keys of new vertices
+    int32_t *const sid = reinterpret_cast<int32_t *>(nkey + 66);   // [64] their ids
     float *const qs = reinterpret_cast<float *>(sid + 64);          // [16 LPV] the query
     // [SEEN] sets of recently claimed or rejected vertices: a vertex found here is visited and
     // needs no compare-and-swap in the workspace table.  A vertex's id u is mapped by
@@ -339,7 +334,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
         }
         // with two passes, each query is searched by exactly one of them
         if (A.acc_pass >= 0 && (__ballot(outside) == 0ull) != (A.acc_pass == 1)) return;
-        if (lane == 0) sid[0] = A.entry;
+        sid[lane] = A.entry;
         for (int i = lane; i < SEEN; i += 64) seen[i] = 0u;
     }
     __builtin_amdgcn_wave_barrier();
@@ -352,7 +347,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         Q.k[i] = KEY_EMPTY;
-        Q.chk[i] = 0;
+        Q.un[i] = 0;
     }
     // dist(P, Q); P goes into the queue and the visited set
     distances<LPV, L2, DT, ACC32>(V, A.d, qs, sid, 1, nkey);
@@ -360,6 +355,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     {
         const uint64_t k0 = nkey[0];
         if (lane == 0) Q.k[0] = k0;
+        Q.un[0] = 1;
         Q.len = 1;
         bool fresh = false;
         if (lane == 0) (void)claim(tbl, t2, (uint32_t)A.entry, &fresh);
@@ -399,9 +395,16 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     const int aidx = two ? (lane & 31) : lane;
     const int32_t *const adj_lane = A.adj + (aidx < R ? aidx : 0);
     int32_t pv = -1, pv2 = -1, pu = -1;   // vertices whose rows are prefetched, and this lane's entry
-    int cur = 0;
+    // Algorithm 2's test U / 1 >= L rho, as a bound on the integer U
+    int u_merge;
+    {
+        const double t = ceil((double)L * A.rho);
+        u_merge = !(t <= 2147483647.0) ? 0x7FFFFFFF : (t <= -2147483648.0 ? -0x7FFFFFFF - 1 : (int)t);
+    }
+    uint64_t worst = KEY_EMPTY;   // the last key of a full queue
+    if (L == 1) worst = get_key(Q, 0);
     bool stop = false;
-    while (cur < Q.len && !stop) {
+    while (any_unchecked(Q) && !stop) {
         gsteps++;
         int sub_in_step = 0;
         for (;;) {
@@ -412,26 +415,23 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             }
             substeps++;
             sub_in_step++;
-            const int32_t v = key_id(get_key(Q, cur));
-            mark_checked(Q, cur);
-            int32_t v2 = -1;
-            if (m == 2) {
-                const int c2 = first_unchecked(Q);
-                if (c2 < Q.len) {
-                    v2 = key_id(get_key(Q, c2));
-                    mark_checked(Q, c2);
-                }
-            }
+            const int32_t v = take_first(Q.k, Q.un);
+            const int32_t v2 = m == 2 ? take_first(Q.k, Q.un) : -1;
             nexp += v2 >= 0 ? 2 : 1;
             const int32_t vl = second ? v2 : v;   // the vertex whose row this lane reads
             int32_t u = pu;
             if (vl != (second ? pv2 : pv)) u = adj_lane[(int64_t)(vl >= 0 ? vl : v) * R];
             // prefetch the rows of the next candidates while this step runs
-            const int nxt = first_unchecked(Q);
-            pv = nxt < Q.len ? key_id(get_key(Q, nxt)) : v;
-            if (two) {
-                const int nx2 = next_unchecked(Q, nxt);
-                pv2 = nx2 < Q.len ? key_id(get_key(Q, nx2)) : pv;
+            {
+                uint64_t ahead[NI];
+#pragma unroll
+                for (int i = 0; i < NI; ++i) ahead[i] = Q.un[i];
+                const int32_t a1 = take_first(Q.k, ahead);
+                pv = a1 >= 0 ? a1 : v;
+                if (two) {
+                    const int32_t a2 = take_first(Q.k, ahead);
+                    pv2 = a2 >= 0 ? a2 : pv;
+                }
             }
             pu = adj_lane[(int64_t)(second ? pv2 : pv) * R];
             if (aidx >= R || vl < 0 || u < 0 || u >= n) u = -1;   // idle walker, padding, malformed entries
@@ -454,7 +454,8 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             const bool send = SPEC ? ask : fresh;   // the vertices whose vectors are read
             const uint64_t am = __ballot(send);
             const int nsend = __popcll(am);
-            const int apos = __popcll(am & lanemask_lt());
+            const int apos = bits_below(am);
+            sid[lane] = 0;   // (a pass of the distances reads ids past the last)
             if (send) sid[apos] = u;
             __builtin_amdgcn_wave_barrier();
             distances<LPV, L2, DT, ACC32, GATHER_PB>(V, A.d, qs, sid, nsend, nkey);
@@ -468,10 +469,12 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             const uint64_t mk = lane < nsend ? nkey[lane] : KEY_EMPTY;
             __builtin_amdgcn_wave_barrier();
             // insert the survivors; the update position is the best place one of them takes
-            const uint64_t worst = Q.len == L ? get_key(Q, L - 1) : KEY_EMPTY;
             const uint64_t sbits = __ballot(mk < worst);
-            const int U = sbits ? insert_batch(Q, L, mk, sbits, nkey) : L;
-            cur = first_unchecked(Q);
+            int U = L;
+            if (sbits) {
+                U = insert_batch(Q, L, mk, sbits, nkey);
+                if (Q.len == L) worst = get_key(Q, L - 1);
+            }
             if (nslot + (two ? 2 * R : R) > cap) {
                 if (t2 < g2) {
                     // (one doubling suffices: nslot <= cap before, and at most 64 new < cap)
@@ -488,8 +491,8 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             bool merge_now;
             if (A.sync == SA_SYNC_BSP) merge_now = true;
             else if (A.sync == SA_SYNC_STATIC) merge_now = A.static_I > 0 && sub_in_step >= A.static_I;
-            else merge_now = (double)U >= (double)L * A.rho;
-            if (cur >= Q.len || merge_now) break;
+            else merge_now = U >= u_merge;
+            if (!any_unchecked(Q) || merge_now) break;
         }
         merges++;   // the queue is S unchanged
         if (two) m = 2;
