@@ -219,12 +219,12 @@ hipError_t lds_fill_log2(const void *k, int block, uint32_t base, int lmin, int 
         }
     }
     int want = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&want, k, block, base + (4u << lmin));
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&want, k, block, base + (5u << lmin));
     if (e != hipSuccess) return e;
     int l = lmin;
     for (int c = lmax; c > lmin; --c) {
         int got = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&got, k, block, base + (4u << c));
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&got, k, block, base + (5u << c));
         if (e != hipSuccess) return e;
         if (got >= want) {
             l = c;

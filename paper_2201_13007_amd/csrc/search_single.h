@@ -12,15 +12,20 @@
 // wave-uniform 64-bit masks, one per slot, so finding the first of them is scalar work.
 // The new entries of a step are merged in one pass (see insert_batch).
 //
-// Visited set.  Open addressing over 32-bit entries (id + 1; zero is empty) in the
-// query's workspace region, claimed with compare-and-swap; the first probe of a vertex
-// goes to the line of its id block (see block_slot).  The table in use is a prefix
-// of the region that doubles (rehashing the set) when it passes three quarters full.  A
-// set-associative LDS filter of recently claimed or rejected ids (exact tags) sits in
-// front of it: a neighbour found there is visited and needs no compare-and-swap.  When
-// the query ends it clears the table in use with whole-line stores, which leaves the region zero for the next launch:
+// Visited set.  It starts in LDS: sets of up to three exact tags, which stay.  As long as a
+// vertex's set has room, LDS alone tells whether it was visited.  A vertex that finds its
+// set full goes to a table in the query's workspace region: open addressing over 32-bit
+// entries (id + 1; zero is empty), claimed with compare-and-swap, the first probe of a
+// vertex at the line of its id block (see block_slot).  That table is a prefix of the region
+// that doubles (rehashing the set) when the visited count passes three quarters of it.  A
+// quarter as many sets of recent ids stand in front of it.  When the query ends it clears
+// the table in use with whole-line stores, which leaves the region zero for the next launch:
 // clearing only the slots it filled would write each of their lines back a second time
 // (they are long evicted by then), and listing them would cost writes of its own.
+// Every vertex used to be claimed in the table (a filter of recent ids in LDS kept repeats
+// away): 2,410 compare-and-swaps per query at L = 192, each a write of 64 B and a round trip
+// of its own.  10,000 queries over 1M rows: 2,376 -> 1,852 us (d = 128, two walkers,
+// L = 192) and 1,230 -> 993 us (d = 96 bf16, L = 112, re-ranked).
 //
 // Distances.  LPV lanes share one vector, each lane four float4 chunks (c = g, g + LPV,
 // ...), accumulated in double precision (in float32 where the data and the query are
@@ -35,7 +40,7 @@ namespace single_detail {
 using search_detail::KArgs;
 using search_detail::NO_SLOT;
 
-// LDS of a wavefront besides the filter of recently seen vertices: new keys (64, one that
+// LDS of a wavefront besides the visited set: new keys (64, one that
 // the insert drops what it does not want into, one for alignment), new ids, the query row
 template <int LPV>
 constexpr uint32_t single_lds_base()
@@ -43,11 +48,10 @@ constexpr uint32_t single_lds_base()
     return 66 * 8 + 64 * 4 + 64 * LPV;
 }
 
-// log2 of the sets of the per-query LDS filter of recently seen vertices (one 32-bit word
-// per set) that fits whatever the kernel's occupancy: the largest (up to 1024 sets, 4 KB)
-// that keeps a wavefront's LDS within 160 KB / 28.  The launcher grows the filter beyond it
-// (up to 2048 sets) where the kernel's registers hold fewer wavefronts per CU than that
-// (lds_fill_log2), so that the LDS they leave idle serves the filter.
+// log2 of the sets of the per-query visited set in LDS (one 32-bit word per set) that fits
+// whatever the kernel's occupancy: the largest (up to 1024 sets, 4 KB) that keeps a
+// wavefront's LDS within 160 KB / 28.  The launcher grows it (up to 2048 sets) where the
+// kernel's registers hold fewer wavefronts per CU than that (lds_fill_log2).
 template <int LPV>
 constexpr int seen_log2()
 {
@@ -186,6 +190,17 @@ __device__ __forceinline__ int insert_batch(Queue<NI> &Q, int L, uint64_t mk, ui
     return fmin;
 }
 
+// Whether a set's word (a count in the top two bits, that many tags of tb bits below) holds
+// tag.  (Written without conditions on lanes: those cost more than the selects.)
+__device__ __forceinline__ bool in_set(uint32_t word, uint32_t tag, uint32_t tb)
+{
+    const uint32_t t1 = word >> tb;
+    const uint32_t w0 = __builtin_amdgcn_ubfe(word, 0u, tb) == tag ? 0u : 3u;
+    const uint32_t w1 = __builtin_amdgcn_ubfe(t1, 0u, tb) == tag ? 1u : 3u;
+    const uint32_t w2 = __builtin_amdgcn_ubfe(t1, tb, tb) == tag ? 2u : 3u;
+    return min(min(w0, w1), w2) < (word >> 30);
+}
+
 // Slots of vertex u in a table of 2^t entries (t >= 6).  The first probe keeps the 32
 // vertices of one id block (u / 32) together in one 128-byte line, each at its own offset:
 // neighbours that a breadth-first numbering gave nearby ids then share lines, within a
@@ -287,14 +302,15 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     uint64_t *const nkey = reinterpret_cast<uint64_t *>(smem);    // [66] keys of new vertices
     int32_t *const sid = reinterpret_cast<int32_t *>(nkey + 66);   // [64] their ids
     float *const qs = reinterpret_cast<float *>(sid + 64);          // [16 LPV] the query
-    // [SEEN] sets of recently claimed or rejected vertices: a vertex found here is visited and
-    // needs no compare-and-swap in the workspace table.  A vertex's id u is mapped by
+    // [SEEN] the first vertices visited, in sets.  A vertex's id u is mapped by
     // h = u * K_B mod 2^B, with K_B the odd number nearest 2^B / golden ratio (Fibonacci
     // hashing at B bits: one-to-one on ids of B bits, and ids close together land in sets far
     // apart); the top SEEN_LOG2 bits of h pick the set and the other tb = B - SEEN_LOG2 bits
-    // are the tag, so a tag names one vertex exactly.  A set's word holds a count of valid
-    // tags in its top two bits and up to W = min(3, 30 / tb) tags below, newest lowest; a new
-    // tag pushes the oldest out.  (Ids of more than 15 + SEEN_LOG2 bits: no filter.)
+    // are the tag, so a tag names one vertex exactly.  A set's word holds a count of tags in
+    // its top two bits and up to W = min(3, 30 / tb) tags below.  Tags stay: as long as a set
+    // has room, a vertex that is not in it is new and is put there, with no access to the
+    // workspace table; a vertex that finds its set full is claimed in the table.  (Ids of more
+    // than 15 + SEEN_LOG2 bits: every vertex is.)
     uint32_t *const seen = reinterpret_cast<uint32_t *>(qs + 16 * LPV);
     const int SEEN_LOG2 = A.seen_log2;
     const int SEEN = 1 << SEEN_LOG2;
@@ -304,7 +320,14 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     const uint32_t hmul = (2654435769u >> (32 - hbits)) | 1u;
     const uint32_t tmask = (1u << tbits) - 1u;
     const uint32_t ways = tbits <= 10 ? 3u : 2u;
-    const uint32_t tagbits = filter ? (1u << (ways * tbits)) - 1u : 0u;
+    // [SEEN / 4] vertices lately claimed or found in the workspace table, by the same hash with
+    // two tag bits more, the newest tag lowest; a new tag pushes the oldest out.
+    uint32_t *const recent = seen + SEEN;
+    const int rbits = tbits + 2;
+    const bool rfilter = rbits <= 15;
+    const uint32_t rmask = (1u << rbits) - 1u;
+    const uint32_t rways = rbits <= 10 ? 3u : 2u;
+    const uint32_t rtagbits = rfilter ? (1u << (rways * rbits)) - 1u : 0u;
 
     const int lane = __lane_id();
     const int R = A.R, g2 = A.glog2;
@@ -335,7 +358,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
         // with two passes, each query is searched by exactly one of them
         if (A.acc_pass >= 0 && (__ballot(outside) == 0ull) != (A.acc_pass == 1)) return;
         sid[lane] = A.entry;
-        for (int i = lane; i < SEEN; i += 64) seen[i] = 0u;
+        for (int i = lane; i < SEEN + SEEN / 4; i += 64) seen[i] = 0u;   // and recent
     }
     __builtin_amdgcn_wave_barrier();
 
@@ -358,7 +381,11 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
         Q.un[0] = 1;
         Q.len = 1;
         bool fresh = false;
-        if (lane == 0) (void)claim(tbl, t2, (uint32_t)A.entry, &fresh);
+        if (lane == 0) {
+            const uint32_t h = ((uint32_t)A.entry * hmul) & (0xFFFFFFFFu >> (32 - hbits));
+            if (filter) seen[h >> tbits] = (1u << 30) | (h & tmask);
+            else (void)claim(tbl, t2, (uint32_t)A.entry, &fresh);
+        }
         nslot = 1;
     }
     __builtin_amdgcn_wave_barrier();
@@ -380,9 +407,9 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     // d = 96 float32 in double 1-5% and fp8 1-4% slower.
     constexpr int GATHER_PB =
         (DT == SA_BF16 && NI <= 2) || (DT == SA_F32 && NI <= 3 && (ACC32 || LPV >= 32)) ? 2 : 1;
-    // Gathers alongside the claims (SPEC) where the filter is the full 1024 sets, so that
-    // few vertices that reach the table are already in it (with the 128 sets that d = 960
-    // leaves room for, many are, and each wasted read is a 3.8 KB row: 30-60% slower), and
+    // Gathers alongside the claims (SPEC) where LDS holds the full 1024 sets, so that few
+    // vertices reach the table (with the 128 sets that d = 960 leaves room for, many do and
+    // were there already, and each wasted read is a 3.8 KB row: 30-60% slower), and
     // where the five registers it takes cost no wave that pays (not at NI = 7, 8; at NI = 3
     // with float32 accumulation the timed two-walker search went 0.5% slower at 5 waves).
     // Measured on 1M rows: d = 128 one walker +2.5% (L = 128), +2.3% (256), +3.4% (384);
@@ -436,22 +463,41 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             pu = adj_lane[(int64_t)(second ? pv2 : pv) * R];
             if (aidx >= R || vl < 0 || u < 0 || u >= n) u = -1;   // idle walker, padding, malformed entries
             bool fresh = false;
+            bool ask = u >= 0;   // not settled in LDS
             const uint32_t h = ((uint32_t)u * hmul) & (0xFFFFFFFFu >> (32 - hbits));
-            const uint32_t hs = h >> tbits, tag = h & tmask;
-            const uint32_t sw = u >= 0 && filter ? seen[hs] : 0u;
-            const uint32_t cnt = sw >> 30;
-            const bool known = (cnt > 0u && (sw & tmask) == tag) || (cnt > 1u && ((sw >> tbits) & tmask) == tag) ||
-                               (cnt > 2u && ((sw >> (2 * tbits)) & tmask) == tag);
-            const bool ask = u >= 0 && !known;
+            if (ask && filter) {
+                uint32_t *const set = seen + (h >> tbits);
+                const uint32_t tag = h & tmask;
+                uint32_t sw = *set;
+                for (;;) {
+                    const uint32_t cnt = sw >> 30;
+                    const bool known = in_set(sw, tag, tbits);
+                    ask = !known;
+                    if (known | (cnt == ways)) break;
+                    const uint32_t old = atomicCAS(set, sw, (sw + (1u << 30)) | (tag << (cnt * tbits)));
+                    if (old == sw) {
+                        fresh = true;
+                        ask = false;
+                        break;
+                    }
+                    sw = old;   // another lane put a vertex into the set
+                }
+            }
+            if (ask && rfilter) {
+                uint32_t *const set = recent + (h >> rbits);
+                const uint32_t tag = h & rmask, sw = *set;
+                ask = !in_set(sw, tag, rbits);
+                if (ask) *set = (min((sw >> 30) + 1u, rways) << 30) | (((sw << rbits) | tag) & rtagbits);
+            }
             // The first probe of each claim goes out now.  With SPEC the vectors of every vertex
-            // that passed the filter are read while it is in flight: nearly all of them turn out
-            // new, and the keys of the few found present are dropped after.  Without, the claims
-            // settle first and only new vertices are read.
+            // that was not found in LDS are read while it is in flight, and the keys of those
+            // found in the table are dropped after.  Without, the claims settle first and only
+            // new vertices are read.
             uint32_t old = 0u;
             if (ask) old = atomicCAS(&tbl[block_slot((uint32_t)u, t2)], 0u, (uint32_t)u + 1u);
-            if (ask && filter) seen[hs] = (min(cnt + 1u, ways) << 30) | (((sw << tbits) | tag) & tagbits);
-            if (!SPEC && ask) (void)claim_rest(tbl, t2, (uint32_t)u, old, &fresh);
-            const bool send = SPEC ? ask : fresh;   // the vertices whose vectors are read
+            bool claimed = false;
+            if (!SPEC && ask) (void)claim_rest(tbl, t2, (uint32_t)u, old, &claimed);
+            const bool send = fresh || (SPEC ? ask : claimed);   // the vertices whose vectors are read
             const uint64_t am = __ballot(send);
             const int nsend = __popcll(am);
             const int apos = bits_below(am);
@@ -459,7 +505,8 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             if (send) sid[apos] = u;
             __builtin_amdgcn_wave_barrier();
             distances<LPV, L2, DT, ACC32, GATHER_PB>(V, A.d, qs, sid, nsend, nkey);
-            if (SPEC && ask) (void)claim_rest(tbl, t2, (uint32_t)u, old, &fresh);
+            if (SPEC && ask) (void)claim_rest(tbl, t2, (uint32_t)u, old, &claimed);
+            fresh = fresh || claimed;
             nslot += __popcll(__ballot(fresh));
             if (SPEC) {
                 __builtin_amdgcn_wave_barrier();
@@ -575,7 +622,7 @@ hipError_t launch1(const KArgs &A, int64_t nq, hipStream_t s)
                                    : search_single_loop<LPV, NI, false, DT, ACC32>;
         hipError_t e = lds_fill_log2(reinterpret_cast<const void *>(k), 64, base, seen_log2<LPV>(), 11, &B.seen_log2);
         if (e != hipSuccess) return e;
-        const uint32_t lds = base + (4u << B.seen_log2);
+        const uint32_t lds = base + (5u << B.seen_log2);
         int64_t grid = nq;
         e = resident_grid(reinterpret_cast<const void *>(k), 64, lds, nq, &grid);
         if (e != hipSuccess) return e;
@@ -585,7 +632,7 @@ hipError_t launch1(const KArgs &A, int64_t nq, hipStream_t s)
     auto k = A.metric == SA_L2 ? search_single<LPV, NI, true, DT, ACC32> : search_single<LPV, NI, false, DT, ACC32>;
     const hipError_t e = lds_fill_log2(reinterpret_cast<const void *>(k), 64, base, seen_log2<LPV>(), 11, &B.seen_log2);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3((unsigned)nq), dim3(64), base + (4u << B.seen_log2), s, B);
+    hipLaunchKernelGGL(k, dim3((unsigned)nq), dim3(64), base + (5u << B.seen_log2), s, B);
     return hipGetLastError();
 }
 
