@@ -15,43 +15,78 @@ __device__ __forceinline__ uint32_t to_bf16(float x)
     return (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
 }
 
-__device__ __forceinline__ uint32_t to_e4m3(float x)
+// Four coordinates of one row as e4m3 codes, lowest byte first.  y = x / s comes as a product
+// with the reciprocal r and one correction by the exact remainder: with r and the product
+// rounded to nearest that is the correctly rounded quotient (Markstein, IBM J. Res. Dev. 34,
+// 1990) as long as nothing underflows, which `fast` promises for every quotient large enough
+// to get a code other than 0; else a division.  The conversion of the gfx950 rounds to
+// nearest even; what is not below 448 (a NaN among it) saturates.
+__device__ __forceinline__ uint32_t to_e4m3x4(float4 x, float s, float r, bool fast)
 {
-    const uint32_t sign = (__float_as_uint(x) >> 24) & 0x80u;
-    const float a = fabsf(x);
-    if (!(a < 448.f)) return sign | 0x7Eu;
-    if (a < 0.015625f) return sign | (uint32_t)rintf(a * 512.f);   // below 2^-6: units of 2^-9
-    int e = (int)((__float_as_uint(a) >> 23) & 0xFFu) - 127;          // a in [2^e, 2^(e+1)), e in [-6, 8]
-    const float frac = a * __uint_as_float((uint32_t)(127 - e) << 23); // a / 2^e, exact, in [1, 2)
-    uint32_t m = (uint32_t)rintf((frac - 1.f) * 8.f);
-    if (m == 8u) {
-        m = 0u;
-        ++e;
+    const float v[4] = {x.x, x.y, x.z, x.w};
+    float y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (fast) {
+            const float q = v[i] * r;
+            y[i] = __builtin_fmaf(__builtin_fmaf(-q, s, v[i]), r, q);
+        } else {
+            y[i] = v[i] / s;
+        }
+        y[i] = copysignf(fabsf(y[i]) < 448.f ? y[i] : 448.f, v[i]);   // (the remainder of -0 is +0)
     }
-    return sign | ((uint32_t)(e + 7) << 3) | m;
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], w, true);
+    return (uint32_t)w;
 }
 
-// one wavefront per row
+// G lanes per row, C chunks of four coordinates per lane (4 G C >= d): the row is read once,
+// 16 bytes a lane, stays in registers while its largest magnitude goes round the group, and
+// its codes are written four at a time.  Bound by memory: 4 d bytes in and d (fp8) or 2 d
+// (bf16) out per row.  A wavefront per row with a coordinate per lane and step, which this
+// replaced, read the row twice and spent some 40 instructions per coordinate on the division
+// and the rounding; 1M x 96 to fp8: 425 -> 83 us
+// (5.8 TB/s).
+template <int G, int C>
 __global__ void __launch_bounds__(256) quantize_kernel(const float *x, int64_t n, int d, int64_t ld, int dtype,
                                                        void *codes, int64_t ldc, float *scale)
 {
-    const int lane = __lane_id();
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= n) return;
-    const float *r = x + row * ld;
-    float s = 1.f;
-    if (dtype == SA_FP8E4M3) {
-        float amax = 0.f;
-        for (int c = lane; c < d; c += 64) amax = fmaxf(amax, fabsf(r[c]));
-        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-        s = amax > 0.f ? amax / 448.f : 1.f;
+    const int g = threadIdx.x % G;
+    const int64_t row = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
+    if (row >= n) return;   // whole groups
+    const int nch = d >> 2, nout = (int)(ldc >> 2);
+    const float4 *const r4 = reinterpret_cast<const float4 *>(x + row * ld);
+    float4 v[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) v[i] = g + G * i < nch ? r4[g + G * i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (dtype == SA_BF16) {
+        uint2 *const out = reinterpret_cast<uint2 *>(static_cast<uint16_t *>(codes) + row * ldc);
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (g + G * i < nch)
+                out[g + G * i] = make_uint2(to_bf16(v[i].x) | (to_bf16(v[i].y) << 16),
+                                            to_bf16(v[i].z) | (to_bf16(v[i].w) << 16));
+        for (int c = nch + g; c < nout; c += G) out[c] = make_uint2(0u, 0u);
+        if (g == 0) scale[row] = 1.f;
+        return;
     }
-    for (int c = lane; c < ldc; c += 64) {
-        const float v = c < d ? r[c] : 0.f;
-        if (dtype == SA_BF16) static_cast<uint16_t *>(codes)[row * ldc + c] = (uint16_t)to_bf16(v);
-        else static_cast<uint8_t *>(codes)[row * ldc + c] = (uint8_t)to_e4m3(v / s);
-    }
-    if (lane == 0) scale[row] = s;
+    float amax = 0.f;
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+        amax = fmaxf(fmaxf(fmaxf(amax, fabsf(v[i].x)), fmaxf(fabsf(v[i].y), fabsf(v[i].z))), fabsf(v[i].w));
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+    const float s = amax > 0.f ? amax / 448.f : 1.f;
+    // |x / s| >= 2^-10 (half the smallest code) means |x| >= 2^-70 here: the remainder, a
+    // multiple of 2^-46 |x| / 2^24 or so, stays clear of underflow
+    const bool fast = s >= 0x1p-60f && s <= 0x1p60f;
+    const float r = 1.f / s;
+    uint32_t *const out = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(codes) + row * ldc);
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+        if (g + G * i < nch) out[g + G * i] = to_e4m3x4(v[i], s, r, fast);
+    for (int c = nch + g; c < nout; c += G) out[c] = 0u;
+    if (g == 0) scale[row] = s;
 }
 
 }  // namespace
@@ -60,8 +95,18 @@ int launch_quantize(const float *x, int64_t n, int32_t d, int64_t ld, int32_t dt
                     float *scale, hipStream_t stream)
 {
     if (n == 0) return SA_OK;
-    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream, x, n, d, ld, dtype,
-                       codes, ldc, scale);
+    // the fewest lanes per row (at least 8, a line of fp8 codes) that hold it in four chunks
+    // each, and sixteen chunks a lane for d beyond 1024 (d <= 4096)
+    const auto go = [&](auto k, int G) {
+        const int64_t rows = 256 / G;
+        hipLaunchKernelGGL(k, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0, stream, x, n, d, ld, dtype, codes,
+                           ldc, scale);
+    };
+    if (d <= 128) go(quantize_kernel<8, 4>, 8);
+    else if (d <= 256) go(quantize_kernel<16, 4>, 16);
+    else if (d <= 512) go(quantize_kernel<32, 4>, 32);
+    else if (d <= 1024) go(quantize_kernel<64, 4>, 64);
+    else go(quantize_kernel<64, 16>, 64);
     SA_HIP(hipGetLastError());
     return SA_OK;
 }
