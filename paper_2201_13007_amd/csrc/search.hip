@@ -306,9 +306,27 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
     const bool compact = compact_table(a.M, llog2, a.p.sync, a.R);
     A.int_lo = a.int_lo; A.int_hi = a.int_hi; A.acc_pass = -1;
     if (compact) {
-        if (a.dtype == SA_BF16) rc = launch_search_single_bf16(A, a.nq, stream);
-        else if (a.dtype == SA_FP8E4M3) rc = launch_search_single_fp8(A, a.nq, stream);
-        else if (a.int_lo <= a.int_hi && search_detail::lanes_per_vector(a.d) <= 16) {
+        // Queries that are all resident at once in the form with the most registers (its
+        // occupancy says so: 1024 to 6144 of them) run in that form: more waves could not be in
+        // flight anyway.  At the line, 3,072 against 3,073 queries over 200K rows, one walker:
+        // d = 128 integers L = 192 725 / 759 us, L = 768 5,254 / 5,265; d = 96 L = 192 663 /
+        // 847, L = 768 4,779 / 6,705; fp8 L = 48 301 / 309, L = 768 5,558 / 7,687.
+        bool taken = false;
+        rc = SA_OK;
+        if (!a.jobctr) {
+            if (a.int_lo <= a.int_hi && search_detail::lanes_per_vector(a.d) <= 16) A.acc_pass = 2;
+            if (a.dtype == SA_BF16) rc = launch_search_few_bf16(A, a.nq, stream, &taken);
+            else if (a.dtype == SA_FP8E4M3) rc = launch_search_few_fp8(A, a.nq, stream, &taken);
+            else rc = launch_search_few_f32(A, a.nq, stream, &taken);
+            A.acc_pass = -1;
+        }
+        if (taken || rc != SA_OK) {
+            // launched, or failed
+        } else if (a.dtype == SA_BF16) {
+            rc = launch_search_single_bf16(A, a.nq, stream);
+        } else if (a.dtype == SA_FP8E4M3) {
+            rc = launch_search_single_fp8(A, a.nq, stream);
+        } else if (a.int_lo <= a.int_hi && search_detail::lanes_per_vector(a.d) <= 16) {
             // integer-valued data: the queries that are integers in the same range in
             // float32 (exact), the others in double; each workgroup checks its query and
             // leaves it to the other pass if it is not its own

@@ -83,7 +83,8 @@ struct KArgs {
     int32_t glog2_init;          // single worker: log2 of the table a query starts in (<= glog2)
     // single worker over integer-valued float32 vectors in [int_lo, int_hi] (see
     // index_integer_range): pass 1 takes the queries that are integers in that range and
-    // accumulates in float32, pass 0 takes the others; -1: one pass takes every query
+    // accumulates in float32, pass 0 takes the others; -1: one pass takes every query, in
+    // double; 2: one pass takes every query, each in the arithmetic it allows
     int32_t int_lo, int_hi, acc_pass;
     int32_t idbits;              // vertex ids fit in idbits bits (2^idbits >= n)
     int32_t seen_log2;           // single-worker kernel: log2 of the seen filter's sets (set by its launcher)
@@ -261,6 +262,88 @@ template <> struct Raw4T<SA_F32> { using type = float4; };
 template <> struct Raw4T<SA_BF16> { using type = uint2; };
 template <int DT> using Raw4 = typename Raw4T<DT>::type;
 
+// How distances are accumulated: in double, in float32 (only where every partial sum is an
+// integer below 2^24, so that the float32 sum is exact and equals the double one), or either
+// by a flag of the query.
+enum { ACC_F64 = 0, ACC_F32 = 1, ACC_EITHER = 2 };
+
+// Partial sums of one pass (see distances), summed over each lane group and written as keys.
+template <typename Acc, int LPV, bool L2, int DT, int PB>
+__device__ __forceinline__ void pass_keys(int nch, const float *qs, const Raw4<DT> (&x)[PB][4], const float (&sc)[PB],
+                                          const int32_t (&id)[PB], uint64_t *out)
+{
+    constexpr int VPW = 64 / LPV;
+    constexpr int SURE = LPV == 1 ? 1 : 2;          // chunks inside the row for every lane
+    constexpr bool F32 = std::is_same<Acc, float>::value;
+    const int lane = __lane_id(), grp = lane / LPV, g = lane % LPV;
+    Acc acc[PB];
+#pragma unroll
+    for (int pp = 0; pp < PB; ++pp) acc[pp] = 0;
+    float4 an = reinterpret_cast<const float4 *>(qs)[g];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool in = i < SURE || g + LPV * i < nch;
+        const float4 a = an;
+        if (i < 3) an = reinterpret_cast<const float4 *>(qs)[g + LPV * (i + 1)];
+        __builtin_amdgcn_sched_barrier(0);
+        const Acc ax = (Acc)a.x, ay = (Acc)a.y, az = (Acc)a.z, aw = (Acc)a.w;
+#pragma unroll
+        for (int pp = 0; pp < PB; ++pp) {
+            // codes outside the row are taken as code 0, which is 0.0 in every storage type
+            float bx, by, bz, bw;
+            if constexpr (DT == SA_F32) {
+                bx = in ? x[pp][i].x : 0.f; by = in ? x[pp][i].y : 0.f;
+                bz = in ? x[pp][i].z : 0.f; bw = in ? x[pp][i].w : 0.f;
+            } else if constexpr (DT == SA_BF16) {
+                const uint32_t lo = in ? x[pp][i].x : 0u, hi = in ? x[pp][i].y : 0u;
+                bx = __uint_as_float(lo << 16); by = __uint_as_float(lo & 0xFFFF0000u);
+                bz = __uint_as_float(hi << 16); bw = __uint_as_float(hi & 0xFFFF0000u);
+            } else {
+                // e4m3 -> f16 bit pattern, two codes at a time: same mantissa bits,
+                // exponent bias 15 instead of 7, so every value, subnormals included,
+                // comes out 2^-8 too small; 2^8 joins the scale, and s * 2^8 * v rounds
+                // once like s * value.  (The hardware fp8 conversion gives the same
+                // values for every code that is written, but not for codes 0x7F / 0xFF,
+                // NaN in e4m3, which decode as 480 / -480 here.)
+                typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+                const uint32_t w = in ? x[pp][i] : 0u, w1 = w >> 8;
+                const uint32_t h02 = ((w & 0x007F007Fu) << 7) | ((w & 0x00800080u) << 8);
+                const uint32_t h13 = ((w1 & 0x007F007Fu) << 7) | ((w1 & 0x00800080u) << 8);
+                const half2v e02 = __builtin_bit_cast(half2v, h02), e13 = __builtin_bit_cast(half2v, h13);
+                const float s8 = sc[pp] * 256.f;
+                bx = s8 * (float)e02.x;
+                by = s8 * (float)e13.x;
+                bz = s8 * (float)e02.y;
+                bw = s8 * (float)e13.y;
+            }
+            Acc s = acc[pp];
+            if constexpr (L2) {
+                const Acc t0 = ax - (Acc)bx, t1 = ay - (Acc)by, t2 = az - (Acc)bz, t3 = aw - (Acc)bw;
+                if constexpr (F32) {
+                    s = __builtin_fmaf(t0, t0, s); s = __builtin_fmaf(t1, t1, s);
+                    s = __builtin_fmaf(t2, t2, s); s = __builtin_fmaf(t3, t3, s);
+                } else {
+                    s += t0 * t0; s += t1 * t1; s += t2 * t2; s += t3 * t3;
+                }
+            } else if constexpr (F32) {
+                s = __builtin_fmaf(ax, bx, s); s = __builtin_fmaf(ay, by, s);
+                s = __builtin_fmaf(az, bz, s); s = __builtin_fmaf(aw, bw, s);
+            } else {
+                s = __builtin_fma(ax, (Acc)bx, s); s = __builtin_fma(ay, (Acc)by, s);
+                s = __builtin_fma(az, (Acc)bz, s); s = __builtin_fma(aw, (Acc)bw, s);
+            }
+            acc[pp] = s;
+        }
+    }
+#pragma unroll
+    for (int pp = 0; pp < PB; ++pp) {
+        Acc s = acc[pp];
+        if constexpr (F32) s = group_sum_f32<LPV>(s);
+        else s = group_sum<LPV>(s);
+        if (g == LPV - 1) out[pp * VPW + grp] = make_key(L2 ? (float)s : (float)(-s), id[pp]);
+    }
+}
+
 // Keys of the vectors ids[0..n) (n <= 64) to out[0..n), 64 / LPV vectors per pass; qs is
 // the query, zero padded to 16 LPV floats.  ids[n..64) must be rows of the index too (any;
 // a pass reads them with the rest), and out[n..64) is overwritten.  The loads are issued
@@ -268,31 +351,34 @@ template <int DT> using Raw4 = typename Raw4T<DT>::type;
 // the compiler moves under a lane condition gets a wait of its own, which turns one memory
 // round trip into two.  (Written as a pass loop over arrays: the same steps as a per-vector
 // helper cost some twenty more registers.)
-// ACC32: accumulate in float32 (only where every partial sum is an integer below 2^24, so
-// that the float32 sum is exact and equals the double one)
 // PB: vectors per lane group in one pass (PB 64 / LPV a pass, each pass one memory round
-// trip; each more in flight costs sixteen registers at d = 128)
+// trip; each more in flight costs sixteen registers at d = 128).  With HALVES a last pass that
+// needs half of them or fewer takes the half (9 registers at PB = 2, d = 128).
 //
 // The searches issue instructions for a quarter (many queries) to half (few) of a wave's
 // life, so a pass is kept short: the query is read and converted once for all of its
 // vectors, products that are exact (inner products of float32 in double, everything with
-// ACC32) go through one fused multiply-add, and only a lane's third and fourth chunk are
+// float32 sums) go through one fused multiply-add, and only a lane's third and fourth chunk are
 // masked, the ones that can lie past the row's end (LPV is the smallest power of two with
 // 4 LPV >= chunks).
-template <int LPV, bool L2, int DT, bool ACC32 = false, int PBMAX = 1>
+template <int LPV, bool L2, int DT, int ACC = ACC_F64, int PBMAX = 1, bool HALVES = false>
 __device__ __forceinline__ void distances(const VecSrc &V, int d, const float *qs, const int32_t *ids, int n,
-                                          uint64_t *out)
+                                          uint64_t *out, bool exact32 = false)
 {
     constexpr int VPW = 64 / LPV;
     constexpr int PB = PBMAX < LPV ? PBMAX : LPV;   // VPW PB <= 64
-    constexpr int SURE = LPV == 1 ? 1 : 2;          // chunks inside the row for every lane
-    using Acc = typename std::conditional<ACC32, float, double>::type;
+    constexpr int SURE = LPV == 1 ? 1 : 2;
+    constexpr int CB = sizeof(Raw4<DT>);            // bytes of a chunk
     const int lane = __lane_id(), grp = lane / LPV, g = lane % LPV;
     const int nch = d >> 2;
-    constexpr int CB = sizeof(Raw4<DT>);            // bytes of a chunk
     const uint64_t stride = (uint64_t)V.ld * (CB / 4);
     const char *const lane_base = static_cast<const char *>(V.p) + g * CB;
     for (int p0 = 0; p0 < n; p0 += VPW * PB) {
+        if constexpr (HALVES && PB > 1)
+            if (n - p0 <= VPW * PB / 2) {
+                distances<LPV, L2, DT, ACC, PB / 2, true>(V, d, qs, ids + p0, n - p0, out + p0, exact32);
+                return;
+            }
         Raw4<DT> x[PB][4];
         float sc[PB];
         int32_t id[PB];
@@ -307,72 +393,10 @@ __device__ __forceinline__ void distances(const VecSrc &V, int d, const float *q
             sc[pp] = DT == SA_FP8E4M3 ? V.scale[id[pp]] : 1.f;
         }
         asm volatile("" ::: "memory");
-        Acc acc[PB];
-#pragma unroll
-        for (int pp = 0; pp < PB; ++pp) acc[pp] = 0;
-        float4 an = reinterpret_cast<const float4 *>(qs)[g];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool in = i < SURE || g + LPV * i < nch;
-            const float4 a = an;
-            if (i < 3) an = reinterpret_cast<const float4 *>(qs)[g + LPV * (i + 1)];
-            __builtin_amdgcn_sched_barrier(0);
-            const Acc ax = (Acc)a.x, ay = (Acc)a.y, az = (Acc)a.z, aw = (Acc)a.w;
-#pragma unroll
-            for (int pp = 0; pp < PB; ++pp) {
-                // codes outside the row are taken as code 0, which is 0.0 in every storage type
-                float bx, by, bz, bw;
-                if constexpr (DT == SA_F32) {
-                    bx = in ? x[pp][i].x : 0.f; by = in ? x[pp][i].y : 0.f;
-                    bz = in ? x[pp][i].z : 0.f; bw = in ? x[pp][i].w : 0.f;
-                } else if constexpr (DT == SA_BF16) {
-                    const uint32_t lo = in ? x[pp][i].x : 0u, hi = in ? x[pp][i].y : 0u;
-                    bx = __uint_as_float(lo << 16); by = __uint_as_float(lo & 0xFFFF0000u);
-                    bz = __uint_as_float(hi << 16); bw = __uint_as_float(hi & 0xFFFF0000u);
-                } else {
-                    // e4m3 -> f16 bit pattern, two codes at a time: same mantissa bits,
-                    // exponent bias 15 instead of 7, so every value, subnormals included,
-                    // comes out 2^-8 too small; 2^8 joins the scale, and s * 2^8 * v rounds
-                    // once like s * value.  (The hardware fp8 conversion gives the same
-                    // values for every code that is written, but not for codes 0x7F / 0xFF,
-                    // NaN in e4m3, which decode as 480 / -480 here.)
-                    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-                    const uint32_t w = in ? x[pp][i] : 0u, w1 = w >> 8;
-                    const uint32_t h02 = ((w & 0x007F007Fu) << 7) | ((w & 0x00800080u) << 8);
-                    const uint32_t h13 = ((w1 & 0x007F007Fu) << 7) | ((w1 & 0x00800080u) << 8);
-                    const half2v e02 = __builtin_bit_cast(half2v, h02), e13 = __builtin_bit_cast(half2v, h13);
-                    const float s8 = sc[pp] * 256.f;
-                    bx = s8 * (float)e02.x;
-                    by = s8 * (float)e13.x;
-                    bz = s8 * (float)e02.y;
-                    bw = s8 * (float)e13.y;
-                }
-                Acc s = acc[pp];
-                if constexpr (L2) {
-                    const Acc t0 = ax - (Acc)bx, t1 = ay - (Acc)by, t2 = az - (Acc)bz, t3 = aw - (Acc)bw;
-                    if constexpr (ACC32) {
-                        s = __builtin_fmaf(t0, t0, s); s = __builtin_fmaf(t1, t1, s);
-                        s = __builtin_fmaf(t2, t2, s); s = __builtin_fmaf(t3, t3, s);
-                    } else {
-                        s += t0 * t0; s += t1 * t1; s += t2 * t2; s += t3 * t3;
-                    }
-                } else if constexpr (ACC32) {
-                    s = __builtin_fmaf(ax, bx, s); s = __builtin_fmaf(ay, by, s);
-                    s = __builtin_fmaf(az, bz, s); s = __builtin_fmaf(aw, bw, s);
-                } else {
-                    s = __builtin_fma(ax, (Acc)bx, s); s = __builtin_fma(ay, (Acc)by, s);
-                    s = __builtin_fma(az, (Acc)bz, s); s = __builtin_fma(aw, (Acc)bw, s);
-                }
-                acc[pp] = s;
-            }
-        }
-#pragma unroll
-        for (int pp = 0; pp < PB; ++pp) {
-            Acc s = acc[pp];
-            if constexpr (ACC32) s = group_sum_f32<LPV>(s);
-            else s = group_sum<LPV>(s);
-            if (g == LPV - 1) out[p0 + pp * VPW + grp] = make_key(L2 ? (float)s : (float)(-s), id[pp]);
-        }
+        if constexpr (ACC == ACC_F32) pass_keys<float, LPV, L2, DT, PB>(nch, qs, x, sc, id, out + p0);
+        else if constexpr (ACC == ACC_F64) pass_keys<double, LPV, L2, DT, PB>(nch, qs, x, sc, id, out + p0);
+        else if (exact32) pass_keys<float, LPV, L2, DT, PB>(nch, qs, x, sc, id, out + p0);
+        else pass_keys<double, LPV, L2, DT, PB>(nch, qs, x, sc, id, out + p0);
     }
 }
 
@@ -685,8 +709,8 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                     claim[lane] = 0;   // (the distances of a pass read 64 ids)
                     if (fresh) claim[bits_below(cm)] = u;
                     __builtin_amdgcn_wave_barrier();
-                    if (l2) distances<LPV, true, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
-                    else distances<LPV, false, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
+                    if (l2) distances<LPV, true, DT, ACC_F64, PB>(V, A.d, qs, claim, nclaim, nkey);
+                    else distances<LPV, false, DT, ACC_F64, PB>(V, A.d, qs, claim, nclaim, nkey);
                     __builtin_amdgcn_wave_barrier();
                     const uint64_t mk = lane < nclaim ? nkey[lane] : KEY_EMPTY;
                     __builtin_amdgcn_wave_barrier();
@@ -855,8 +879,8 @@ __device__ __forceinline__ void search_body(const KArgs &A, int64_t job, int64_t
                     claim[lane] = 0;   // (the distances of a pass read 64 ids)
                     if (claimed) claim[bits_below(cm)] = u;
                     __builtin_amdgcn_wave_barrier();
-                    if (l2) distances<LPV, true, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
-                    else distances<LPV, false, DT, false, PB>(V, A.d, qs, claim, nclaim, nkey);
+                    if (l2) distances<LPV, true, DT, ACC_F64, PB>(V, A.d, qs, claim, nclaim, nkey);
+                    else distances<LPV, false, DT, ACC_F64, PB>(V, A.d, qs, claim, nclaim, nkey);
                     __builtin_amdgcn_wave_barrier();
                     const uint64_t mk = lane < nclaim ? nkey[lane] : KEY_EMPTY;
                     __builtin_amdgcn_wave_barrier();
@@ -1088,6 +1112,10 @@ int launch_rerank(const float *vec32, int64_t ld32, const float *queries, int64_
 int launch_search_single_f32(const search_detail::KArgs &A, int64_t nq, hipStream_t s);
 int launch_search_single_bf16(const search_detail::KArgs &A, int64_t nq, hipStream_t s);
 int launch_search_single_fp8(const search_detail::KArgs &A, int64_t nq, hipStream_t s);
+// the forms for few queries; *taken tells whether the launch suits them (and was made)
+int launch_search_few_f32(const search_detail::KArgs &A, int64_t nq, hipStream_t s, bool *taken);
+int launch_search_few_bf16(const search_detail::KArgs &A, int64_t nq, hipStream_t s, bool *taken);
+int launch_search_few_fp8(const search_detail::KArgs &A, int64_t nq, hipStream_t s, bool *taken);
 int launch_search_multi_f32(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s);
 int launch_search_multi_bf16(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s);
 int launch_search_multi_fp8(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s);

@@ -37,15 +37,18 @@
 namespace sa {
 namespace single_detail {
 
+using search_detail::ACC_EITHER;
+using search_detail::ACC_F32;
+using search_detail::ACC_F64;
 using search_detail::KArgs;
 using search_detail::NO_SLOT;
 
-// LDS of a wavefront besides the visited set: new keys (64, one that
+// LDS of a wavefront besides the visited set: new keys (64, or all slots' keys; one that
 // the insert drops what it does not want into, one for alignment), new ids, the query row
 template <int LPV>
-constexpr uint32_t single_lds_base()
+constexpr uint32_t single_lds_base(int stage = 64)   // stage: keys that the insert exchanges at once
 {
-    return 66 * 8 + 64 * 4 + 64 * LPV;
+    return (stage + 2) * 8 + 64 * 4 + 64 * LPV;
 }
 
 // log2 of the sets of the per-query visited set in LDS (one 32-bit word per set) that fits
@@ -70,12 +73,46 @@ template <int NI>
 struct Queue {
     uint64_t k[NI];    // keys; KEY_EMPTY past the end
     uint64_t un[NI];   // unchecked entries (wave-uniform; zero past the end)
+    uint64_t top;      // NI > 4: in lane i the last key of slot i, KEY_EMPTY in the other lanes
     int len;
 };
 
+// Calls f with the constant s (uniform, in [LO, HI)), by halving: an access to the queue
+// indexed by a variable would make the compiler move the arrays to scratch memory.
+template <int LO, int HI, typename F>
+__device__ __forceinline__ void at_slot(int s, F f)
+{
+    if constexpr (HI - LO == 1) {
+        f(std::integral_constant<int, LO>{});
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (s < MID) at_slot<LO, MID>(s, f);
+        else at_slot<MID, HI>(s, f);
+    }
+}
+
+// Calls f with the constants first .. NI - 1, and I .. first downwards.
+template <int NI, int I = 0, typename F>
+__device__ __forceinline__ void slots_from(int first, F f)
+{
+    if constexpr (I < NI) {
+        if (I >= first) f(std::integral_constant<int, I>{});
+        slots_from<NI, I + 1>(first, f);
+    }
+}
+
+template <int I, typename F>
+__device__ __forceinline__ void slots_down(int first, F f)
+{
+    if constexpr (I >= 0) {
+        if (I < first) return;
+        f(std::integral_constant<int, I>{});
+        slots_down<I - 1>(first, f);
+    }
+}
+
 // Takes the first entry of the masks m (one bit per queue entry) out of them and returns its
-// id, or -1 if they are empty.  The key is read with a lane read in the branch of its slot:
-// an access indexed by the slot would make the compiler move the arrays to scratch memory.
+// id, or -1 if they are empty.
 template <int NI, int I = 0>
 __device__ __forceinline__ int32_t take_first(const uint64_t (&k)[NI], uint64_t (&m)[NI])
 {
@@ -103,49 +140,53 @@ __device__ __forceinline__ bool any_unchecked(const Queue<NI> &Q)
 template <int NI>
 __device__ __forceinline__ uint64_t get_key(const Queue<NI> &Q, int p)
 {
-    uint64_t r = KEY_EMPTY;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-        if (i == (p >> 6)) r = rdlane64(Q.k[i], p & 63);
+    uint64_t r;
+    at_slot<0, NI>(p >> 6, [&](auto i) { r = rdlane64(Q.k[i], p & 63); });
     return r;
 }
 
 // Inserts the unchecked keys mk of the lanes in sbits (distinct, none in the queue),
 // keeping at most L entries, and returns the update position: the best position one of
-// them takes (L if none stays).  One compare per new key and slot gives both the key's
-// place (queue keys below it; its rank among the new keys is added per lane) and, summed
-// per lane, how far each old entry moves up.  Then each slot from the last down to the
-// first that changes is put together in LDS: its own entries that stay in it, those that
-// come up from the slot below (none moves by more than 64) and the new ones.  The
-// unchecked flags travel as bit 31 of the ids.  stage: 65 keys of LDS; the last takes what
-// lands elsewhere.
+// them takes (L if none stays).  Every new key finds its place (the queue keys below it) by
+// compares with whole slots: all of them up to four slots, beyond only the slot that the
+// slots' last keys give.  Its rank among the new keys is added per lane.  An old entry moves
+// up by the new keys below it.  Then the slots from the first that changes on are put
+// together in LDS: in one exchange where STAGE holds all slots (few queries: one round trip
+// through LDS instead of one per slot), else slot by slot from the last down, each from its
+// own entries that stay in it, those that come up from the slot below (none moves by more
+// than 64) and the new ones.  The unchecked flags travel as bit 31 of the ids.
+// stage: 64 keys (STAGE: 64 NI) and one that takes what lands elsewhere.
 //
 // This replaced a form that kept a landing mask per slot and pulled every entry with
-// cross-lane permutes: some 60 instructions per new key and 30 per slot against 25 and 25.
-// With 10 new keys a step that was half of a step's 1,300 instructions.
-template <int NI>
+// cross-lane permutes: some 60 instructions per new key and 30 per slot against 25 and 25 at
+// three slots.  With 10 new keys a step that was half of a step's 1,300 instructions.
+template <int NI, bool STAGE>
 __device__ __forceinline__ int insert_batch(Queue<NI> &Q, int L, uint64_t mk, uint64_t sbits, uint64_t *stage)
 {
+    constexpr bool ALL = NI <= 4;   // compare with every slot, and keep the entries' moves from it
     const int lane = __lane_id();
-    // new keys below each entry: kept from the same compares up to four slots per lane;
-    // beyond, where the registers would cost waves, counted again per slot from the places
-    // (a new key is below entry p if its place among the old ones is at most p)
-    constexpr bool KEEP = NI <= 4;
-    int shift[KEEP ? NI : 1];
+    int shift[ALL ? NI : 1];
 #pragma unroll
-    for (int i = 0; i < (KEEP ? NI : 1); ++i) shift[i] = 0;
+    for (int i = 0; i < (ALL ? NI : 1); ++i) shift[i] = 0;
     int f = 1 << 20;   // where this lane's new key lands
     int r = 0;         // new keys below it
     int fmin = L;
     for (uint64_t b = sbits; b; b &= b - 1) {
         const int j = __builtin_ctzll(b);
         const uint64_t kj = rdlane64(mk, j);
-        int below = 64 * NI;
+        int below;
+        if constexpr (ALL) {
+            below = 64 * NI;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const bool above = Q.k[i] > kj;
-            if constexpr (KEEP) shift[i] += above ? 1 : 0;
-            below -= __popcll(__ballot(above));
+            for (int i = 0; i < NI; ++i) {
+                const bool above = Q.k[i] > kj;
+                shift[i] += above ? 1 : 0;
+                below -= __popcll(__ballot(above));
+            }
+        } else {
+            // (the last key of a full queue is above kj, so the slot exists)
+            const int s = __popcll(__ballot(Q.top < kj));
+            at_slot<0, NI>(s, [&](auto i) { below = 64 * i + __popcll(__ballot(Q.k[i] < kj)); });
         }
         r += kj < mk ? 1 : 0;
         f = lane == j ? below : f;
@@ -154,37 +195,58 @@ __device__ __forceinline__ int insert_batch(Queue<NI> &Q, int L, uint64_t mk, ui
     if (fmin >= L) return L;
     const int place = f;
     f += r;
-    const auto moves = [&](int i) {   // by how much this lane's entry of slot i moves up
-        if constexpr (KEEP) return shift[i];
-        const int p = 64 * i + lane;
-        int c = 0;
-        for (uint64_t b = sbits; b; b &= b - 1) c += (int)rdlane((uint32_t)place, __builtin_ctzll(b)) <= p ? 1 : 0;
-        return c;
-    };
     const int nlen = min(L, Q.len + __popcll(sbits));
     const int i_first = fmin >> 6;
-    int mine = moves(NI - 1);
-#pragma unroll
-    for (int i = NI - 1; i >= 0; --i) {
-        if (i < i_first) continue;
-        const int below = i > 0 ? moves(i > 0 ? i - 1 : 0) : 0;   // moves of the slot below
-        // offsets within the slot, 64 for what lands elsewhere
-        const uint32_t own = min((uint32_t)(lane + mine), 64u);
-        const uint32_t add = min((uint32_t)(f - 64 * i), 64u);
-        stage[own] = Q.k[i] | (__builtin_amdgcn_inverse_ballot_w64(Q.un[i]) ? 0x80000000ull : 0ull);
-        if (i > 0) {
-            const uint32_t up = min((uint32_t)(lane + below - 64), 64u);
-            stage[up] = Q.k[i > 0 ? i - 1 : 0] |
-                        (__builtin_amdgcn_inverse_ballot_w64(Q.un[i > 0 ? i - 1 : 0]) ? 0x80000000ull : 0ull);
-        }
-        stage[add] = mk | 0x80000000ull;
-        __builtin_amdgcn_wave_barrier();
-        const uint64_t v = stage[lane];
-        __builtin_amdgcn_wave_barrier();
+    // by how much this lane's entry of slot i moves up, and the same for the slots above
+    const auto moves = [&](int i) {
+        if constexpr (ALL) return shift[i];
+        int c = __popcll(__ballot(place < 64 * i));   // (lanes without a new key: 2^20)
+        for (uint64_t b = __ballot((place >> 6) == i); b; b &= b - 1)
+            c += (int)rdlane((uint32_t)place, __builtin_ctzll(b)) <= 64 * i + lane ? 1 : 0;
+        return c;
+    };
+    const auto flagged = [&](uint64_t key, uint64_t un) {
+        return key | (__builtin_amdgcn_inverse_ballot_w64(un) ? 0x80000000ull : 0ull);
+    };
+    const auto take = [&](auto i, uint64_t v) {
         const bool keep = lane < nlen - 64 * i;
         Q.un[i] = __ballot(keep && ((uint32_t)v >> 31) != 0u);
         Q.k[i] = keep ? v & ~0x80000000ull : KEY_EMPTY;
-        mine = below;
+        if constexpr (!ALL) {
+            const uint64_t last = rdlane64(Q.k[i], 63);
+            Q.top = lane == i ? last : Q.top;
+        }
+    };
+    if constexpr (STAGE) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            if (i < i_first) continue;
+            stage[min((uint32_t)(64 * i + lane + moves(i)), 64u * NI)] = flagged(Q.k[i], Q.un[i]);
+        }
+        stage[min((uint32_t)f, 64u * NI)] = mk | 0x80000000ull;
+        __builtin_amdgcn_wave_barrier();
+        uint64_t v[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) v[i] = stage[64 * i + lane];
+        __builtin_amdgcn_wave_barrier();
+        slots_from<NI>(i_first, [&](auto i) { take(i, v[i]); });
+    } else {
+        int mine = moves(NI - 1);
+        slots_down<NI - 1>(i_first, [&](auto ii) {
+            constexpr int i = ii, h = i > 0 ? i - 1 : 0;
+            const int below = i > 0 ? moves(h) : 0;   // moves of the slot below
+            // offsets within the slot, 64 for what lands elsewhere
+            const uint32_t own = min((uint32_t)(lane + mine), 64u);
+            const uint32_t add = min((uint32_t)(f - 64 * i), 64u);
+            stage[own] = flagged(Q.k[i], Q.un[i]);
+            if (i > 0) stage[min((uint32_t)(lane + below - 64), 64u)] = flagged(Q.k[h], Q.un[h]);
+            stage[add] = mk | 0x80000000ull;
+            __builtin_amdgcn_wave_barrier();
+            const uint64_t v = stage[lane];
+            __builtin_amdgcn_wave_barrier();
+            take(ii, v);
+            mine = below;
+        });
     }
     Q.len = nlen;
     return fmin;
@@ -295,12 +357,14 @@ __device__ __forceinline__ void clear_table(uint32_t *tbl, int t)
     for (int i = __lane_id(); i < (1 << (t - 2)); i += 64) p[i] = z;
 }
 
-template <int LPV, int NI, bool L2, int DT, bool ACC32>
+// FEW: the form for launches that leave the chip idle (see launch_few)
+template <int LPV, int NI, bool L2, int DT, int ACC, bool FEW>
 __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_t *tbl)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint64_t *const nkey = reinterpret_cast<uint64_t *>(smem);    // [66] keys of new vertices
-    int32_t *const sid = reinterpret_cast<int32_t *>(nkey + 66);   // [64] their ids
+    constexpr int STAGE = FEW ? 64 * NI : 64;
+    uint64_t *const nkey = reinterpret_cast<uint64_t *>(smem);    // [STAGE + 2] keys of new vertices
+    int32_t *const sid = reinterpret_cast<int32_t *>(nkey + STAGE + 2);   // [64] their ids
     float *const qs = reinterpret_cast<float *>(sid + 64);          // [16 LPV] the query
     // [SEEN] the first vertices visited, in sets.  A vertex's id u is mapped by
     // h = u * K_B mod 2^B, with K_B the odd number nearest 2^B / golden ratio (Fibonacci
@@ -342,6 +406,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     int t2 = A.glog2_init;
     int cap = (3 << t2) / 4;
     const VecSrc V{A.codes, A.scale, A.ldc};
+    bool exact32 = false;   // this query's distances are exact in float32
 
     {
         const int nch = A.d >> 2;
@@ -355,10 +420,14 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
                 outside |= !(v.x == rintf(v.x) && v.x >= lo && v.x <= hi) || !(v.y == rintf(v.y) && v.y >= lo && v.y <= hi) ||
                            !(v.z == rintf(v.z) && v.z >= lo && v.z <= hi) || !(v.w == rintf(v.w) && v.w >= lo && v.w <= hi);
         }
+        exact32 = __ballot(outside) == 0ull && A.acc_pass > 0;
         // with two passes, each query is searched by exactly one of them
-        if (A.acc_pass >= 0 && (__ballot(outside) == 0ull) != (A.acc_pass == 1)) return;
+        if (ACC != ACC_EITHER && A.acc_pass >= 0 && (__ballot(outside) == 0ull) != (A.acc_pass == 1)) return;
         sid[lane] = A.entry;
-        for (int i = lane; i < SEEN + SEEN / 4; i += 64) seen[i] = 0u;   // and recent
+        {   // and recent; 16 bytes at a time (at least 80 words)
+            uint4 *const z = reinterpret_cast<uint4 *>(seen);
+            for (int i = lane; i < (SEEN + SEEN / 4) / 4; i += 64) z[i] = make_uint4(0u, 0u, 0u, 0u);
+        }
     }
     __builtin_amdgcn_wave_barrier();
 
@@ -373,12 +442,13 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
         Q.un[i] = 0;
     }
     // dist(P, Q); P goes into the queue and the visited set
-    distances<LPV, L2, DT, ACC32>(V, A.d, qs, sid, 1, nkey);
+    distances<LPV, L2, DT, ACC>(V, A.d, qs, sid, 1, nkey, exact32);
     __builtin_amdgcn_wave_barrier();
     {
         const uint64_t k0 = nkey[0];
         if (lane == 0) Q.k[0] = k0;
         Q.un[0] = 1;
+        Q.top = KEY_EMPTY;
         Q.len = 1;
         bool fresh = false;
         if (lane == 0) {
@@ -405,8 +475,10 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     // integer data: +2.3% (two walkers, L = 192) and +2.8% (one, L = 128) at one wave less;
     // d = 960: +2% at L = 64 and 128; d = 96 bf16: +2.8% (two walkers, L = 112, re-ranked);
     // d = 96 float32 in double 1-5% and fp8 1-4% slower.
-    constexpr int GATHER_PB =
-        (DT == SA_BF16 && NI <= 2) || (DT == SA_F32 && NI <= 3 && (ACC32 || LPV >= 32)) ? 2 : 1;
+    // For few queries registers cost nothing: a pass takes 32 vectors (a step of one walker)
+    // where eight per lane group hold them.
+    constexpr int GATHER_PB = FEW ? (LPV >= 16 ? 8 : (LPV >= 2 ? LPV / 2 : 1)) :
+        (DT == SA_BF16 && NI <= 2) || (DT == SA_F32 && NI <= 3 && (ACC == ACC_F32 || LPV >= 32)) ? 2 : 1;
     // Gathers alongside the claims (SPEC) where LDS holds the full 1024 sets, so that few
     // vertices reach the table (with the 128 sets that d = 960 leaves room for, many do and
     // were there already, and each wasted read is a 3.8 KB row: 30-60% slower), and
@@ -414,7 +486,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     // with float32 accumulation the timed two-walker search went 0.5% slower at 5 waves).
     // Measured on 1M rows: d = 128 one walker +2.5% (L = 128), +2.3% (256), +3.4% (384);
     // d = 96 in double +4% (one walker, L = 128) and +3% (two, L = 192).
-    constexpr bool SPEC = seen_log2<LPV>() >= 10 && NI != 7 && NI != 8 && !(ACC32 && NI == 3);
+    constexpr bool SPEC = FEW || (seen_log2<LPV>() >= 10 && NI != 7 && NI != 8 && !(ACC == ACC_F32 && NI == 3));
     const bool second = two && lane >= 32;
     int m = two && !A.staged ? 2 : 1;   // walkers active in the next step (staged: 1, then 2)
     int nexp = 0;
@@ -504,7 +576,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             sid[lane] = 0;   // (a pass of the distances reads ids past the last)
             if (send) sid[apos] = u;
             __builtin_amdgcn_wave_barrier();
-            distances<LPV, L2, DT, ACC32, GATHER_PB>(V, A.d, qs, sid, nsend, nkey);
+            distances<LPV, L2, DT, ACC, GATHER_PB, FEW>(V, A.d, qs, sid, nsend, nkey, exact32);
             if (SPEC && ask) (void)claim_rest(tbl, t2, (uint32_t)u, old, &claimed);
             fresh = fresh || claimed;
             nslot += __popcll(__ballot(fresh));
@@ -519,7 +591,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             const uint64_t sbits = __ballot(mk < worst);
             int U = L;
             if (sbits) {
-                U = insert_batch(Q, L, mk, sbits, nkey);
+                U = insert_batch<NI, FEW>(Q, L, mk, sbits, nkey);
                 if (Q.len == L) worst = get_key(Q, L - 1);
             }
             if (nslot + (two ? 2 * R : R) > cap) {
@@ -585,17 +657,17 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
 // longest first is scheduled longest first.  (A persistent loop over jobs in one
 // workgroup was measured: any loop around the search costs 17-36 more VGPRs, about a
 // third of the occupancy this latency-bound search lives on.)
-template <int LPV, int NI, bool L2, int DT, bool ACC32>
+template <int LPV, int NI, bool L2, int DT, int ACC>
 __global__ void __launch_bounds__(64) search_single(KArgs A)
 {
     const int32_t job = blockIdx.x;
     uint32_t *const tbl = reinterpret_cast<uint32_t *>(A.ghash) + ((size_t)job << (A.glog2 + 1));
-    single_query<LPV, NI, L2, DT, ACC32>(A, A.order ? A.order[job] : job, tbl);
+    single_query<LPV, NI, L2, DT, ACC, false>(A, A.order ? A.order[job] : job, tbl);
 }
 
 // Persistent form: each resident workgroup takes jobs from the device counter until none
 // is left, every one in its own workspace region (see KArgs::jobctr).
-template <int LPV, int NI, bool L2, int DT, bool ACC32>
+template <int LPV, int NI, bool L2, int DT, int ACC>
 __global__ void __launch_bounds__(64) search_single_loop(KArgs A)
 {
     uint32_t *const tbl = reinterpret_cast<uint32_t *>(A.ghash) + ((size_t)blockIdx.x << (A.glog2 + 1));
@@ -607,19 +679,30 @@ __global__ void __launch_bounds__(64) search_single_loop(KArgs A)
         // (loads after stores are vector loads: made wave-uniform again, or everything
         // derived from the query index would take vector registers)
         const int32_t qi = A.order ? __builtin_amdgcn_readfirstlane(A.order[job]) : job;
-        single_query<LPV, NI, L2, DT, ACC32>(A, qi, tbl);
+        single_query<LPV, NI, L2, DT, ACC, false>(A, qi, tbl);
     }
     if (__lane_id() == 0) search_detail::release_jobs(A.jobctr);
 }
 
-template <int LPV, int NI, int DT, bool ACC32>
+// log2 of the visited set's sets where few queries share a CU: from l (what the kernel's
+// registers leave at full occupancy) up to 8192, as far as the LDS of a CU goes round its
+// share of the nq queries and until nearly every query's visited set (8 L to 15 L vertices,
+// three to a set) fits without going to the workspace table.
+inline int seen_log2_for(int64_t nq, uint32_t base, int l, int L)
+{
+    const int64_t per_cu = (nq + 255) / 256;
+    while (l < 13 && (1 << l) < 8 * L && (int64_t)(base + (5u << (l + 1)) + 1024u) * per_cu <= 160 * 1024) ++l;
+    return l;
+}
+
+template <int LPV, int NI, int DT, int ACC>
 hipError_t launch1(const KArgs &A, int64_t nq, hipStream_t s)
 {
     constexpr uint32_t base = single_lds_base<LPV>();
     KArgs B = A;
     if (A.jobctr) {
-        auto k = A.metric == SA_L2 ? search_single_loop<LPV, NI, true, DT, ACC32>
-                                   : search_single_loop<LPV, NI, false, DT, ACC32>;
+        auto k = A.metric == SA_L2 ? search_single_loop<LPV, NI, true, DT, ACC>
+                                   : search_single_loop<LPV, NI, false, DT, ACC>;
         hipError_t e = lds_fill_log2(reinterpret_cast<const void *>(k), 64, base, seen_log2<LPV>(), 11, &B.seen_log2);
         if (e != hipSuccess) return e;
         const uint32_t lds = base + (5u << B.seen_log2);
@@ -629,26 +712,27 @@ hipError_t launch1(const KArgs &A, int64_t nq, hipStream_t s)
         hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64), lds, s, B);
         return hipGetLastError();
     }
-    auto k = A.metric == SA_L2 ? search_single<LPV, NI, true, DT, ACC32> : search_single<LPV, NI, false, DT, ACC32>;
+    auto k = A.metric == SA_L2 ? search_single<LPV, NI, true, DT, ACC> : search_single<LPV, NI, false, DT, ACC>;
     const hipError_t e = lds_fill_log2(reinterpret_cast<const void *>(k), 64, base, seen_log2<LPV>(), 11, &B.seen_log2);
     if (e != hipSuccess) return e;
+    B.seen_log2 = seen_log2_for(nq, base, B.seen_log2, A.L);
     hipLaunchKernelGGL(k, dim3((unsigned)nq), dim3(64), base + (5u << B.seen_log2), s, B);
     return hipGetLastError();
 }
 
-template <int LPV, int DT, bool ACC32>
+template <int LPV, int DT, int ACC>
 hipError_t launch1_ni(const KArgs &A, int64_t nq, hipStream_t s)
 {
     const int ni = (A.L + 63) / 64;
-    if (ni <= 1) return launch1<LPV, 1, DT, ACC32>(A, nq, s);
-    if (ni <= 2) return launch1<LPV, 2, DT, ACC32>(A, nq, s);
-    if (ni <= 3) return launch1<LPV, 3, DT, ACC32>(A, nq, s);
-    if (ni <= 4) return launch1<LPV, 4, DT, ACC32>(A, nq, s);
-    if (ni <= 5) return launch1<LPV, 5, DT, ACC32>(A, nq, s);
-    if (ni <= 6) return launch1<LPV, 6, DT, ACC32>(A, nq, s);
-    if (ni <= 7) return launch1<LPV, 7, DT, ACC32>(A, nq, s);
-    if (ni <= 8) return launch1<LPV, 8, DT, ACC32>(A, nq, s);
-    return launch1<LPV, 16, DT, ACC32>(A, nq, s);
+    if (ni <= 1) return launch1<LPV, 1, DT, ACC>(A, nq, s);
+    if (ni <= 2) return launch1<LPV, 2, DT, ACC>(A, nq, s);
+    if (ni <= 3) return launch1<LPV, 3, DT, ACC>(A, nq, s);
+    if (ni <= 4) return launch1<LPV, 4, DT, ACC>(A, nq, s);
+    if (ni <= 5) return launch1<LPV, 5, DT, ACC>(A, nq, s);
+    if (ni <= 6) return launch1<LPV, 6, DT, ACC>(A, nq, s);
+    if (ni <= 7) return launch1<LPV, 7, DT, ACC>(A, nq, s);
+    if (ni <= 8) return launch1<LPV, 8, DT, ACC>(A, nq, s);
+    return launch1<LPV, 16, DT, ACC>(A, nq, s);
 }
 
 // one instantiation per storage type, each in a file of its own (search_single_*.hip)
@@ -658,8 +742,8 @@ template <int LPV, int DT>
 hipError_t launch_lpv(const KArgs &A, int64_t nq, hipStream_t s)
 {
     if constexpr (DT == SA_F32 && LPV <= 16)
-        if (A.acc_pass == 1) return launch1_ni<LPV, DT, true>(A, nq, s);
-    return launch1_ni<LPV, DT, false>(A, nq, s);
+        if (A.acc_pass == 1) return launch1_ni<LPV, DT, ACC_F32>(A, nq, s);
+    return launch1_ni<LPV, DT, ACC_F64>(A, nq, s);
 }
 
 template <int DT>
@@ -674,6 +758,65 @@ int launch_dt(const KArgs &A, int64_t nq, hipStream_t s)
     case 16: e = launch_lpv<16, DT>(A, nq, s); break;
     case 32: e = launch_lpv<32, DT>(A, nq, s); break;
     default: e = launch_lpv<64, DT>(A, nq, s); break;
+    }
+    if (e != hipSuccess) return hip_fail(e, "search kernel launch");
+    return SA_OK;
+}
+
+// The form for launches of so few queries that all are resident at once whatever their
+// registers: up to eight vectors per lane group in flight, and one launch for both
+// arithmetics of integer data.
+template <int LPV, int NI, bool L2, int DT>
+__global__ void __launch_bounds__(64) search_few(KArgs A)
+{
+    const int32_t job = blockIdx.x;
+    uint32_t *const tbl = reinterpret_cast<uint32_t *>(A.ghash) + ((size_t)job << (A.glog2 + 1));
+    constexpr int ACC = DT == SA_F32 && LPV <= 16 ? ACC_EITHER : ACC_F64;
+    single_query<LPV, NI, L2, DT, ACC, true>(A, A.order ? A.order[job] : job, tbl);
+}
+
+template <int LPV, int NI, int DT>
+hipError_t launch_few(const KArgs &A, int64_t nq, hipStream_t s, bool *taken)
+{
+    constexpr uint32_t base = single_lds_base<LPV>(64 * NI);
+    auto k = A.metric == SA_L2 ? search_few<LPV, NI, true, DT> : search_few<LPV, NI, false, DT>;
+    KArgs B = A;
+    B.seen_log2 = seen_log2_for(nq, base, seen_log2<LPV>(), A.L);
+    int64_t grid = 0;
+    const hipError_t e = resident_grid(reinterpret_cast<const void *>(k), 64, base + (5u << B.seen_log2), nq, &grid);
+    if (e != hipSuccess) return e;
+    *taken = grid >= nq;
+    if (!*taken) return hipSuccess;
+    hipLaunchKernelGGL(k, dim3((unsigned)nq), dim3(64), base + (5u << B.seen_log2), s, B);
+    return hipGetLastError();
+}
+
+template <int LPV, int DT>
+hipError_t launch_few_ni(const KArgs &A, int64_t nq, hipStream_t s, bool *taken)
+{
+    const int ni = (A.L + 63) / 64;
+    if (ni <= 1) return launch_few<LPV, 1, DT>(A, nq, s, taken);
+    if (ni <= 2) return launch_few<LPV, 2, DT>(A, nq, s, taken);
+    if (ni <= 3) return launch_few<LPV, 3, DT>(A, nq, s, taken);
+    if (ni <= 4) return launch_few<LPV, 4, DT>(A, nq, s, taken);
+    if (ni <= 6) return launch_few<LPV, 6, DT>(A, nq, s, taken);
+    if (ni <= 8) return launch_few<LPV, 8, DT>(A, nq, s, taken);
+    return launch_few<LPV, 16, DT>(A, nq, s, taken);
+}
+
+template <int DT>
+int launch_few_dt(const KArgs &A, int64_t nq, hipStream_t s, bool *taken)
+{
+    hipError_t e;
+    *taken = false;
+    switch (search_detail::lanes_per_vector(A.d)) {
+    case 1: e = launch_few_ni<1, DT>(A, nq, s, taken); break;
+    case 2: e = launch_few_ni<2, DT>(A, nq, s, taken); break;
+    case 4: e = launch_few_ni<4, DT>(A, nq, s, taken); break;
+    case 8: e = launch_few_ni<8, DT>(A, nq, s, taken); break;
+    case 16: e = launch_few_ni<16, DT>(A, nq, s, taken); break;
+    case 32: e = launch_few_ni<32, DT>(A, nq, s, taken); break;
+    default: e = launch_few_ni<64, DT>(A, nq, s, taken); break;
     }
     if (e != hipSuccess) return hip_fail(e, "search kernel launch");
     return SA_OK;

@@ -1,0 +1,99 @@
+"""The forms of the one- and two-walker search against the oracle: few queries (up to eight
+vectors per lane group in flight, all queue slots exchanged at once) and many, with the LDS
+visited set roomy, overflowing into the workspace table, or absent, at the edges of the
+vector layouts (1 to 64 lanes per vector, chunks past the row's end) and of the queue slots."""
+import numpy as np
+import pytest
+
+import oracle
+import parity
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+MANY = 8200    # more queries than can be resident at once in any form
+FIELDS = ("global_steps", "substeps", "expansions", "dist_comps", "merges")
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def graph(n, R, g):
+    """Random rows, each vertex linked to its neighbours on a ring too (all reachable)."""
+    adj = g.integers(0, n, (n, R)).astype(np.int32)
+    adj[:, 0] = (np.arange(n) + 1) % n
+    adj[:, 1] = (np.arange(n) - 1) % n
+    return adj
+
+
+def check(base, adj, q, k, L, M, sync, metric="l2", dtype="f32", exact=True, repeat=1, label="", **kw):
+    from paper_2201_13007_amd import binding as B
+    searched = base
+    if dtype != "f32":
+        searched = oracle.dequantize(*oracle.quantize(base, dtype), dtype)
+    ix = B.Index(dev(base), dev(adj), 0, metric=metric, dtype=dtype)
+    print(f"case: {label} n={base.shape[0]} d={base.shape[1]} nq={len(q) * repeat} L={L} M={M} {metric} {dtype}", flush=True)
+    qs = dev(np.tile(q, (repeat, 1)))
+    e = parity.oracle_search(searched, adj, 0, q, k, L, M, sync=sync, metric=metric)
+    for _ in range(2):    # the second pass finds the workspace as the first left it
+        r = ix.search(qs, k, L, M, stats=True, sync=sync, **kw)
+        torch.cuda.synchronize()
+        ids, d, st = r.ids.cpu().numpy(), r.dists.cpu().numpy(), r.stats.cpu().numpy()
+        m = len(q)
+        for x in (ids, d, st[:, :5]):    # every copy of the queries as the first
+            np.testing.assert_array_equal(x, np.tile(x[:m], (repeat, 1)), err_msg=label)
+        parity.compare((ids[:m], d[:m], st[:m]), e, exact, base=searched, queries=q, metric=metric, atol=1e-5,
+                       label=label)
+
+
+@pytest.mark.parametrize("nq", [5, MANY])
+@pytest.mark.parametrize("d", [4, 8, 16, 20, 36, 64, 68, 100, 128, 132, 256, 260, 516, 960, 1024])
+def test_vector_layouts(d, nq):
+    g = np.random.default_rng(d)
+    base = g.integers(-3, 4, (700, d)).astype(np.float32)
+    q = g.integers(-3, 4, (5, d)).astype(np.float32)
+    check(base, graph(700, 32, g), q, 10, 40, 2 if d % 8 else 1, "bsp", repeat=nq // 5, label="integers")
+
+
+@pytest.mark.parametrize("nq", [6, MANY])
+@pytest.mark.parametrize("dtype,metric", [("f32", "l2"), ("f32", "ip"), ("bf16", "ip"), ("fp8", "l2"), ("fp8", "ip")])
+@pytest.mark.parametrize("d", [12, 96, 200])
+def test_float_data(d, dtype, metric, nq):
+    g = np.random.default_rng([d, 7])
+    base = g.standard_normal((900, d)).astype(np.float32)
+    q = g.standard_normal((5, d)).astype(np.float32)
+    check(base, graph(900, 24, g), q, 10, 70, 1, "adaptive", metric, dtype, exact=False, repeat=nq // 5, label="floats")
+
+
+@pytest.mark.parametrize("nq", [4, MANY])
+@pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 128, 129, 192, 193, 256, 257, 320, 321, 385, 449, 512, 513, 1023, 1024])
+def test_queue_slots(L, nq):
+    """Every number of slots per lane, its first and last L; from L = 512 on, the visited
+    vertices outgrow the LDS sets of the many-queries form."""
+    g = np.random.default_rng(L)
+    n = 9000
+    base = g.integers(0, 16, (n, 16)).astype(np.float32)
+    q = g.integers(0, 16, (4, 16)).astype(np.float32)
+    check(base, graph(n, 32, g), q, min(L, 20), L, 1 + L % 2, "bsp", repeat=nq // 4, label="slots")
+
+
+@pytest.mark.parametrize("nq", [4, MANY])
+@pytest.mark.parametrize("n", [3, 500, 70_000])
+def test_visited_sets(n, nq):
+    """Two distinct tags per set, tags of few bits, and sets that overflow by far."""
+    g = np.random.default_rng(n)
+    base = g.integers(0, 9, (n, 960 if n < 10_000 else 8)).astype(np.float32)
+    q = g.integers(0, 9, (4, base.shape[1])).astype(np.float32)
+    check(base, graph(n, 48, g), q, 2, 400 if n > 400 else 3, 1, "adaptive", repeat=nq // 4, label="visited",
+          ws_hash_slots=1 << 16 if nq < 100 else 1 << 15)   # random rows: 48 new vertices a step
+
+
+@pytest.mark.parametrize("nq", [60, MANY])
+def test_integer_and_other_queries_together(nq):
+    """Integer-valued vectors: integer queries in float32, the others in double, in one call."""
+    g = np.random.default_rng(5)
+    base = g.integers(0, 200, (2000, 64)).astype(np.float32)
+    q = g.integers(0, 200, (20, 64)).astype(np.float32)
+    q[::3] += 0.5
+    q[1::7] = 1000.0
+    check(base, graph(2000, 32, g), q, 10, 96, 1, "adaptive", exact=False, repeat=nq // 20, label="mixed")
