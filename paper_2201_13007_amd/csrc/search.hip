@@ -337,6 +337,9 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
         } else {
             rc = launch_search_single_f32(A, a.nq, stream);
         }
+    } else if (a.M >= 2 && a.p.sync == SA_SYNC_BSP) {
+        if (a.dtype == SA_F32 && a.int_lo <= a.int_hi && search_detail::lanes_per_vector(a.d) <= 16) A.acc_pass = 2;
+        rc = launch_search_bsp(A, a.dtype, a.nq, stream);
     } else {
         if (a.dtype == SA_BF16) rc = launch_search_multi_bf16(A, a.nq, a.M, Y.total, stream);
         else if (a.dtype == SA_FP8E4M3) rc = launch_search_multi_fp8(A, a.nq, a.M, Y.total, stream);

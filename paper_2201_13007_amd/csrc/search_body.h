@@ -1116,6 +1116,7 @@ int launch_search_single_fp8(const search_detail::KArgs &A, int64_t nq, hipStrea
 int launch_search_few_f32(const search_detail::KArgs &A, int64_t nq, hipStream_t s, bool *taken);
 int launch_search_few_bf16(const search_detail::KArgs &A, int64_t nq, hipStream_t s, bool *taken);
 int launch_search_few_fp8(const search_detail::KArgs &A, int64_t nq, hipStream_t s, bool *taken);
+int launch_search_bsp(const search_detail::KArgs &A, int dtype, int64_t nq, hipStream_t s);
 int launch_search_multi_f32(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s);
 int launch_search_multi_bf16(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s);
 int launch_search_multi_fp8(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s);

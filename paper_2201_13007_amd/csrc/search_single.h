@@ -33,6 +33,7 @@
 // row shifts and broadcasts, and rounded once to float.  The query row sits in LDS.
 #pragma once
 #include "search_body.h"
+#include "search_visited.h"
 
 namespace sa {
 namespace single_detail {
@@ -62,7 +63,13 @@ constexpr int seen_log2()
     while (l > 6 && single_lds_base<LPV>() + (4u << l) > 160u * 1024u / 28u) --l;
     return l;
 }
+using search_detail::Seen;
 using search_detail::VecSrc;
+using search_detail::claim;
+using search_detail::claim_rest;
+using search_detail::block_slot;
+using search_detail::clear_table;
+using search_detail::grow_table;
 using search_detail::distances;
 using search_detail::rerank_list;
 using search_detail::bits_below;
@@ -252,111 +259,6 @@ __device__ __forceinline__ int insert_batch(Queue<NI> &Q, int L, uint64_t mk, ui
     return fmin;
 }
 
-// Whether a set's word (a count in the top two bits, that many tags of tb bits below) holds
-// tag.  (Written without conditions on lanes: those cost more than the selects.)
-__device__ __forceinline__ bool in_set(uint32_t word, uint32_t tag, uint32_t tb)
-{
-    const uint32_t t1 = word >> tb;
-    const uint32_t w0 = __builtin_amdgcn_ubfe(word, 0u, tb) == tag ? 0u : 3u;
-    const uint32_t w1 = __builtin_amdgcn_ubfe(t1, 0u, tb) == tag ? 1u : 3u;
-    const uint32_t w2 = __builtin_amdgcn_ubfe(t1, tb, tb) == tag ? 2u : 3u;
-    return min(min(w0, w1), w2) < (word >> 30);
-}
-
-// Slots of vertex u in a table of 2^t entries (t >= 6).  The first probe keeps the 32
-// vertices of one id block (u / 32) together in one 128-byte line, each at its own offset:
-// neighbours that a breadth-first numbering gave nearby ids then share lines, within a
-// step and from one step to the next, so a step's claims touch about half as many lines
-// and most of them are still in the L2 from the step before.  Later probes move by an odd
-// stride 32 r + 1 (r odd): a new line every time, and every slot of the table in turn.
-__device__ __forceinline__ uint32_t block_slot(uint32_t u, int t)
-{
-    return ((((u >> 5) * 2654435761u) >> (37 - t)) << 5) | (u & 31u);
-}
-
-__device__ __forceinline__ uint32_t block_stride(uint32_t u, int t)
-{
-    const uint32_t r = (((u ^ 0x9E3779B9u) * 2654435761u) >> (37 - t)) | 1u;
-    return ((r << 5) | 1u) & ((1u << t) - 1u);
-}
-
-// find or insert u; *fresh tells whether this call inserted it.  NO_SLOT: table full.
-__device__ __forceinline__ uint32_t claim(uint32_t *T, int log2cap, uint32_t u, bool *fresh)
-{
-    const uint32_t mask = (1u << log2cap) - 1u;
-    uint32_t s = block_slot(u, log2cap);
-    const uint32_t step = block_stride(u, log2cap);
-    *fresh = false;
-    for (uint32_t probe = 0; probe <= mask; ++probe) {
-        const uint32_t old = atomicCAS(&T[s], 0u, u + 1u);
-        if (old == 0u) {
-            *fresh = true;
-            return s;
-        }
-        if (old == u + 1u) return s;
-        s = (s + step) & mask;
-    }
-    return NO_SLOT;
-}
-
-// The rest of claim() after its first probe, given what that probe's compare-and-swap at
-// block_slot(u, log2cap) returned: lets the caller issue the first probes of a step, go on
-// with other loads, and read the results later.
-__device__ __forceinline__ uint32_t claim_rest(uint32_t *T, int log2cap, uint32_t u, uint32_t old, bool *fresh)
-{
-    const uint32_t mask = (1u << log2cap) - 1u;
-    uint32_t s = block_slot(u, log2cap);
-    *fresh = old == 0u;
-    if (old == 0u || old == u + 1u) return s;
-    const uint32_t step = block_stride(u, log2cap);
-    for (uint32_t probe = 1; probe <= mask; ++probe) {
-        s = (s + step) & mask;
-        old = atomicCAS(&T[s], 0u, u + 1u);
-        if (old == 0u) {
-            *fresh = true;
-            return s;
-        }
-        if (old == u + 1u) return s;
-    }
-    return NO_SLOT;
-}
-
-// Moves the visited set from the table in use (2^t1 entries) into one twice as large,
-// 2^t2 entries at the same address (the region holds the largest; past the table in use
-// it is zero).  The entries are copied out to scratch (the second half of the region) and
-// the table is cleared; then they are inserted again and scratch is cleared.  Returns the
-// number of entries moved.  The whole wavefront takes part.
-__device__ __forceinline__ int grow_table(uint32_t *tbl, uint32_t *scratch, int t1, int t2)
-{
-    const int lane = __lane_id();
-    int cnt = 0;
-    for (int b = 0; b < (1 << t1); b += 64) {   // 2^t1 >= 64 entries
-        const uint32_t e = tbl[b + lane];
-        const uint64_t m = __ballot(e != 0u);
-        if (e != 0u) scratch[cnt + bits_below(m)] = e;
-        tbl[b + lane] = 0u;
-        cnt += __popcll(m);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    for (int i = lane; i < cnt; i += 64) {
-        bool fresh;
-        (void)claim(tbl, t2, scratch[i] - 1u, &fresh);
-        scratch[i] = 0u;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    return cnt;
-}
-
-// Zeroes the first 2^t entries of tbl (2^t >= 64, 16-byte aligned) with 16-byte stores.
-__device__ __forceinline__ void clear_table(uint32_t *tbl, int t)
-{
-    uint4 *const p = reinterpret_cast<uint4 *>(tbl);
-    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = __lane_id(); i < (1 << (t - 2)); i += 64) p[i] = z;
-}
-
 // FEW: the form for launches that leave the chip idle (see launch_few)
 template <int LPV, int NI, bool L2, int DT, int ACC, bool FEW>
 __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_t *tbl)
@@ -366,32 +268,9 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
     uint64_t *const nkey = reinterpret_cast<uint64_t *>(smem);    // [STAGE + 2] keys of new vertices
     int32_t *const sid = reinterpret_cast<int32_t *>(nkey + STAGE + 2);   // [64] their ids
     float *const qs = reinterpret_cast<float *>(sid + 64);          // [16 LPV] the query
-    // [SEEN] the first vertices visited, in sets.  A vertex's id u is mapped by
-    // h = u * K_B mod 2^B, with K_B the odd number nearest 2^B / golden ratio (Fibonacci
-    // hashing at B bits: one-to-one on ids of B bits, and ids close together land in sets far
-    // apart); the top SEEN_LOG2 bits of h pick the set and the other tb = B - SEEN_LOG2 bits
-    // are the tag, so a tag names one vertex exactly.  A set's word holds a count of tags in
-    // its top two bits and up to W = min(3, 30 / tb) tags below.  Tags stay: as long as a set
-    // has room, a vertex that is not in it is new and is put there, with no access to the
-    // workspace table; a vertex that finds its set full is claimed in the table.  (Ids of more
-    // than 15 + SEEN_LOG2 bits: every vertex is.)
-    uint32_t *const seen = reinterpret_cast<uint32_t *>(qs + 16 * LPV);
-    const int SEEN_LOG2 = A.seen_log2;
-    const int SEEN = 1 << SEEN_LOG2;
-    const int hbits = A.idbits > SEEN_LOG2 ? A.idbits : SEEN_LOG2 + 1;
-    const int tbits = hbits - SEEN_LOG2;
-    const bool filter = tbits <= 15;
-    const uint32_t hmul = (2654435769u >> (32 - hbits)) | 1u;
-    const uint32_t tmask = (1u << tbits) - 1u;
-    const uint32_t ways = tbits <= 10 ? 3u : 2u;
-    // [SEEN / 4] vertices lately claimed or found in the workspace table, by the same hash with
-    // two tag bits more, the newest tag lowest; a new tag pushes the oldest out.
-    uint32_t *const recent = seen + SEEN;
-    const int rbits = tbits + 2;
-    const bool rfilter = rbits <= 15;
-    const uint32_t rmask = (1u << rbits) - 1u;
-    const uint32_t rways = rbits <= 10 ? 3u : 2u;
-    const uint32_t rtagbits = rfilter ? (1u << (rways * rbits)) - 1u : 0u;
+    // the visited set in LDS: [SEEN] sets and [SEEN / 4] sets of recent ids (see Seen)
+    const int SEEN = 1 << A.seen_log2;
+    const Seen seen(reinterpret_cast<uint32_t *>(qs + 16 * LPV), A.seen_log2, A.idbits);
 
     const int lane = __lane_id();
     const int R = A.R, g2 = A.glog2;
@@ -425,7 +304,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
         if (ACC != ACC_EITHER && A.acc_pass >= 0 && (__ballot(outside) == 0ull) != (A.acc_pass == 1)) return;
         sid[lane] = A.entry;
         {   // and recent; 16 bytes at a time (at least 80 words)
-            uint4 *const z = reinterpret_cast<uint4 *>(seen);
+            uint4 *const z = reinterpret_cast<uint4 *>(qs + 16 * LPV);
             for (int i = lane; i < (SEEN + SEEN / 4) / 4; i += 64) z[i] = make_uint4(0u, 0u, 0u, 0u);
         }
     }
@@ -452,9 +331,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
         Q.len = 1;
         bool fresh = false;
         if (lane == 0) {
-            const uint32_t h = ((uint32_t)A.entry * hmul) & (0xFFFFFFFFu >> (32 - hbits));
-            if (filter) seen[h >> tbits] = (1u << 30) | (h & tmask);
-            else (void)claim(tbl, t2, (uint32_t)A.entry, &fresh);
+            if (!seen.put_first((uint32_t)A.entry)) (void)claim(tbl, t2, (uint32_t)A.entry, &fresh);
         }
         nslot = 1;
     }
@@ -535,32 +412,7 @@ __device__ __forceinline__ void single_query(const KArgs &A, int64_t qi, uint32_
             pu = adj_lane[(int64_t)(second ? pv2 : pv) * R];
             if (aidx >= R || vl < 0 || u < 0 || u >= n) u = -1;   // idle walker, padding, malformed entries
             bool fresh = false;
-            bool ask = u >= 0;   // not settled in LDS
-            const uint32_t h = ((uint32_t)u * hmul) & (0xFFFFFFFFu >> (32 - hbits));
-            if (ask && filter) {
-                uint32_t *const set = seen + (h >> tbits);
-                const uint32_t tag = h & tmask;
-                uint32_t sw = *set;
-                for (;;) {
-                    const uint32_t cnt = sw >> 30;
-                    const bool known = in_set(sw, tag, tbits);
-                    ask = !known;
-                    if (known | (cnt == ways)) break;
-                    const uint32_t old = atomicCAS(set, sw, (sw + (1u << 30)) | (tag << (cnt * tbits)));
-                    if (old == sw) {
-                        fresh = true;
-                        ask = false;
-                        break;
-                    }
-                    sw = old;   // another lane put a vertex into the set
-                }
-            }
-            if (ask && rfilter) {
-                uint32_t *const set = recent + (h >> rbits);
-                const uint32_t tag = h & rmask, sw = *set;
-                ask = !in_set(sw, tag, rbits);
-                if (ask) *set = (min((sw >> 30) + 1u, rways) << 30) | (((sw << rbits) | tag) & rtagbits);
-            }
+            const bool ask = u >= 0 && seen.claim((uint32_t)u, &fresh);   // not settled in LDS
             // The first probe of each claim goes out now.  With SPEC the vectors of every vertex
             // that was not found in LDS are read while it is in flight, and the keys of those
             // found in the table are dropped after.  Without, the claims settle first and only

@@ -97,3 +97,52 @@ def test_integer_and_other_queries_together(nq):
     q[::3] += 0.5
     q[1::7] = 1000.0
     check(base, graph(2000, 32, g), q, 10, 96, 1, "adaptive", exact=False, repeat=nq // 20, label="mixed")
+
+
+@pytest.mark.parametrize("R", [20, 64])
+@pytest.mark.parametrize("M", [2, 3, 4, 7, 16])
+@pytest.mark.parametrize("L", [1, 2, 33, 64, 65, 200, 1024])
+def test_several_workers_every_step(L, M, R):
+    """Merges after every step: few and many new keys per step for the lanes that rank them,
+    lists shorter than the workers, the staged start and all workers at once."""
+    g = np.random.default_rng([L, M, R])
+    n = 6000
+    base = g.integers(0, 16, (n, 16)).astype(np.float32)
+    q = g.integers(0, 16, (6, 16)).astype(np.float32)
+    if R > 32 or M > 2:
+        check(base, graph(n, R, g), q, min(L, 20), L, M, "bsp", repeat=1 + (M % 3), label="every step",
+              ws_hash_slots=1 << 17)
+        check(base, graph(n, R, g), q, min(L, 20), L, M, "bsp", label="every step, table in the workspace",
+              ws_hash_slots=1 << 17, lds_hash_slots=-1)
+
+
+@pytest.mark.parametrize("d", [4, 20, 96, 132, 260, 960])
+@pytest.mark.parametrize("dtype,metric", [("f32", "l2"), ("bf16", "ip"), ("fp8", "l2")])
+def test_several_workers_layouts(d, dtype, metric):
+    g = np.random.default_rng([d, 11])
+    base = g.standard_normal((900, d)).astype(np.float32)
+    q = g.standard_normal((9, d)).astype(np.float32)
+    check(base, graph(900, 32, g), q, 10, 70, 8, "bsp", metric, dtype, exact=False, label="workers, floats")
+    if dtype == "f32":
+        b, i = np.rint(4 * base), np.rint(4 * q)
+        i[::2] += 0.5
+        check(b, graph(900, 32, g), i, 10, 70, 5, "bsp", metric, dtype, exact=False, label="workers, integers")
+
+
+def test_several_workers_limits():
+    """The step limit, and visited sets that spill and fill up: flags and counters as before."""
+    from paper_2201_13007_amd import binding as B
+    g = np.random.default_rng(3)
+    n = 70_000
+    base = g.integers(0, 9, (n, 8)).astype(np.float32)
+    adj = graph(n, 48, g)
+    q = g.integers(0, 9, (4, 8)).astype(np.float32)
+    ix = B.Index(dev(base), dev(adj), 0)
+    for kw in ({"max_substeps": 5}, {"ws_hash_slots": 4096}, {"lds_hash_slots": 1024, "ws_hash_slots": 1 << 16}):
+        a = ix.search(dev(q), 10, 300, 8, stats=True, sync="bsp", **kw)
+        b = ix.search(dev(q), 10, 300, 8, stats=True, sync="static", static_I=1, **kw)   # the same schedule
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(a.ids.cpu().numpy(), b.ids.cpu().numpy())
+        for name in FIELDS + ("flags",):
+            np.testing.assert_array_equal(a.stat(name).cpu().numpy(), b.stat(name).cpu().numpy(), err_msg=f"{kw} {name}")
+        assert a.stat("flags").cpu().numpy().any()
