@@ -14,10 +14,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspeedann.so")
-SOURCES = ["capi.hip", "search.hip", "search_single_f32.hip", "search_single_bf16.hip", "search_single_fp8.hip",
-           "search_few_f32.hip", "search_few_bf16.hip", "search_few_fp8.hip",
-           "search_bsp.hip", "search_multi_f32.hip", "search_multi_bf16.hip", "search_multi_fp8.hip", "knn.hip", "knn_mfma.hip",
+SOURCES = ["search_multi_large_f32.hip", "search_multi_large_bf16.hip", "search_multi_large_fp8.hip",
+           "search_multi_f32.hip", "search_multi_bf16.hip", "search_multi_fp8.hip", "search_single_f32.hip",
+           "search_few_f32.hip", "search_single_bf16.hip", "search_single_fp8.hip", "search_few_bf16.hip",
+           "search_few_fp8.hip", "search_bsp.hip", "capi.hip", "search.hip", "knn.hip", "knn_mfma.hip",
            "graph.hip", "quant.hip", "rerank.hip", "batch.hip", "server.hip", "reorder.hip", "probe.hip", "noalloc.hip"]
+# (the longest to compile first)
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off",

@@ -1,6 +1,6 @@
-// Host side of the search: parameter resolution, LDS layout, workspace sizing and the
-// launch of the single-worker kernel (search_single.h) or of the general kernel
-// (search_multi.h, whose body is in search_body.h), one instantiation per storage type.
+// Host side of the search: parameter resolution, LDS bounds, workspace sizing and the launch
+// of the single-worker kernel (search_single.h), of the one for every-step merges
+// (search_bsp.hip) or of the general kernel (search_multi.h).
 #include "search_body.h"
 
 #include <algorithm>
@@ -13,34 +13,20 @@
 namespace sa {
 namespace {
 
-using search_detail::Ctrl;
 using search_detail::KArgs;
-
-struct Layout {
-    uint32_t o_skey, o_srank, o_schk, o_pub, o_newkey, o_claim, o_ctrl, o_hash, o_q, total;
-};
 
 uint32_t align_up(uint32_t x, uint32_t a) { return (x + a - 1) / a * a; }
 
-// S, the rank array and the published new keys of a merge exist only with M >= 2; the
-// query takes 16 floats per lane of a vector group
-Layout make_layout(int L, int M, int llog2, int lpv)
+// LDS that a query of the general kernel is taken to need, which bounds (L, M, table): two
+// copies of S with ranks and flags, 512 published keys, per worker 64 keys and ids, 240 bytes
+// of counters, the visited table, 16 floats of the query per lane of a vector group.  The
+// kernels need no more than this wherever it comes near the 160 KB.
+uint32_t lds_bound(int L, int M, int llog2, int lpv)
 {
-    Layout Y;
     const uint32_t LL = M >= 2 ? (uint32_t)L : 0u;
-    uint32_t o = 0;
-    Y.o_skey = o; o += 2u * 8u * LL;
-    Y.o_srank = o; o += 4u * LL;
-    Y.o_schk = o; o = align_up(o + 2u * LL, 16);
-    Y.o_pub = o; o += M >= 2 ? 8u * search_detail::PUBCAP : 0u;
-    o = align_up(o, 16);
-    Y.o_newkey = o; o += 8u * 64u * M;
-    Y.o_claim = o; o += 4u * 64u * M;
-    Y.o_ctrl = o; o += align_up(sizeof(Ctrl), 16);
-    Y.o_hash = o; o += llog2 > 0 ? (8u << llog2) : 0u;
-    Y.o_q = o; o += 64u * (uint32_t)lpv;
-    Y.total = o;
-    return Y;
+    uint32_t o = align_up(2u * 8u * LL + 4u * LL + 2u * LL, 16);
+    o = align_up(o + (M >= 2 ? 8u * 512u : 0u), 16);
+    return o + 8u * 64u * M + 4u * 64u * M + 240u + (llog2 > 0 ? (8u << llog2) : 0u) + 64u * (uint32_t)lpv;
 }
 
 int ilog2_exact(int64_t v)
@@ -72,7 +58,7 @@ void resolve_params(const sa_search_params &in, int L, int M, int R, int &llog2,
         // visited set (some 8 L vertices) in LDS, if the layout leaves room for it
         llog2 = 12;
         for (int lg = ilog2_exact(std::min<int64_t>(16ll * L, 1 << 14)); lg > 12; --lg)
-            if (make_layout(L, M, lg, 64).total <= 160u * 1024u) {
+            if (lds_bound(L, M, lg, 64) <= 160u * 1024u) {
                 llog2 = lg;
                 break;
             }
@@ -104,7 +90,7 @@ size_t bytes_per_slot(int M, int llog2, int sync, int R) { return compact_table(
 
 uint32_t search_lds_bytes(int32_t L, int32_t M, int32_t llog2, int32_t d)
 {
-    return make_layout(L, M, llog2, search_detail::lanes_per_vector(d)).total;
+    return lds_bound(L, M, llog2, search_detail::lanes_per_vector(d));
 }
 
 void search_table_log2(const sa_search_params &p, int32_t L, int32_t M, int32_t R, int32_t *llog2, int32_t *glog2)
@@ -254,10 +240,10 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
         return set_error(SA_ECAPACITY, "workspace of %zu bytes is smaller than the %zu bytes needed", a.ws_bytes, need);
     if (a.workspace == nullptr && need > 0) return set_error(SA_EINVAL, "workspace is NULL");
     if (((uintptr_t)a.workspace & 255u) != 0) return set_error(SA_EINVAL, "workspace must be 256-byte aligned");
-    Layout Y = make_layout(a.L, a.M, llog2, search_detail::lanes_per_vector(a.d));
-    if (Y.total > 160u * 1024u)
+    const uint32_t lds = lds_bound(a.L, a.M, llog2, search_detail::lanes_per_vector(a.d));
+    if (lds > 160u * 1024u)
         return set_error(SA_ECAPACITY, "L=%d, M=%d need %u bytes of LDS per query (limit 163840); lower L, M or "
-                         "lds_hash_slots", a.L, a.M, Y.total);
+                         "lds_hash_slots", a.L, a.M, lds);
     KArgs A;
     A.codes = a.codes; A.scale = a.scale; A.ldc = a.ldc; A.vec32 = a.vec32; A.ld32 = a.ld32; A.rerank = a.p.rerank;
     A.adj = a.adj; A.queries = a.queries; A.ldq = a.ldq;
@@ -297,9 +283,6 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
         while (t < glog2 && (int64_t(1) << t) < want0) ++t;
         A.glog2_init = crowded ? std::min(t, glog2) : glog2;
     }
-    A.o_skey = Y.o_skey; A.o_srank = Y.o_srank; A.o_schk = Y.o_schk; A.o_pub = Y.o_pub;
-    A.o_newkey = Y.o_newkey; A.o_claim = Y.o_claim; A.o_ctrl = Y.o_ctrl;
-    A.o_hash = Y.o_hash; A.o_q = Y.o_q;
     if (a.nq == 0) return SA_OK;
     if (a.d > 1024) return set_error(SA_EUNSUPPORTED, "d=%d exceeds 1024", a.d);
     int rc;
@@ -341,9 +324,13 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
         if (a.dtype == SA_F32 && a.int_lo <= a.int_hi && search_detail::lanes_per_vector(a.d) <= 16) A.acc_pass = 2;
         rc = launch_search_bsp(A, a.dtype, a.nq, stream);
     } else {
-        if (a.dtype == SA_BF16) rc = launch_search_multi_bf16(A, a.nq, a.M, Y.total, stream);
-        else if (a.dtype == SA_FP8E4M3) rc = launch_search_multi_fp8(A, a.nq, a.M, Y.total, stream);
-        else rc = launch_search_multi_f32(A, a.nq, a.M, Y.total, stream);
+        const bool large = a.L > 256;
+        if (a.dtype == SA_BF16)
+            rc = large ? launch_search_multi_large_bf16(A, a.nq, stream) : launch_search_multi_bf16(A, a.nq, stream);
+        else if (a.dtype == SA_FP8E4M3)
+            rc = large ? launch_search_multi_large_fp8(A, a.nq, stream) : launch_search_multi_fp8(A, a.nq, stream);
+        else
+            rc = large ? launch_search_multi_large_f32(A, a.nq, stream) : launch_search_multi_f32(A, a.nq, stream);
     }
     if (rc == SA_OK && a.p.rerank != 0) {
         // the list sits at the end of the slot list, which follows the table in each region

@@ -59,13 +59,6 @@ __host__ __device__ inline BspLds bsp_lds(int L, int M, int lpv, int seen_log2)
     return Y;
 }
 
-// ids go through here with the unchecked flag below them
-__device__ __forceinline__ uint64_t entry_of(uint64_t key, uint32_t unchecked)
-{
-    return (key & 0xFFFFFFFF00000000ull) | ((uint32_t)key << 1) | unchecked;
-}
-__device__ __forceinline__ int32_t entry_id(uint64_t e) { return (int32_t)((uint32_t)e >> 1); }
-
 // the r-th (from 0) set bit of the wave-uniform m, which has more than r
 __device__ __forceinline__ int nth_bit(uint64_t m, int r)
 {

@@ -3,9 +3,9 @@
 
 namespace sa {
 
-int launch_search_multi_f32(const search_detail::KArgs &A, int64_t nq, int M, uint32_t lds, hipStream_t s)
+int launch_search_multi_f32(const search_detail::KArgs &A, int64_t nq, hipStream_t s)
 {
-    return search_detail::launch_dt<SA_F32>(A, nq, M, lds, s);
+    return search_detail::launch_multi_dt<SA_F32, false>(A, nq, s);
 }
 
 }  // namespace sa

@@ -26,7 +26,7 @@ def graph(n, R, g):
     return adj
 
 
-def check(base, adj, q, k, L, M, sync, metric="l2", dtype="f32", exact=True, repeat=1, label="", **kw):
+def check(base, adj, q, k, L, M, sync, metric="l2", dtype="f32", exact=True, repeat=1, label="", orc={}, **kw):
     from paper_2201_13007_amd import binding as B
     searched = base
     if dtype != "f32":
@@ -34,9 +34,9 @@ def check(base, adj, q, k, L, M, sync, metric="l2", dtype="f32", exact=True, rep
     ix = B.Index(dev(base), dev(adj), 0, metric=metric, dtype=dtype)
     print(f"case: {label} n={base.shape[0]} d={base.shape[1]} nq={len(q) * repeat} L={L} M={M} {metric} {dtype}", flush=True)
     qs = dev(np.tile(q, (repeat, 1)))
-    e = parity.oracle_search(searched, adj, 0, q, k, L, M, sync=sync, metric=metric)
+    e = parity.oracle_search(searched, adj, 0, q, k, L, M, sync=sync, metric=metric, **orc)
     for _ in range(2):    # the second pass finds the workspace as the first left it
-        r = ix.search(qs, k, L, M, stats=True, sync=sync, **kw)
+        r = ix.search(qs, k, L, M, stats=True, sync=sync, **orc, **kw)
         torch.cuda.synchronize()
         ids, d, st = r.ids.cpu().numpy(), r.dists.cpu().numpy(), r.stats.cpu().numpy()
         m = len(q)
@@ -146,3 +146,19 @@ def test_several_workers_limits():
         for name in FIELDS + ("flags",):
             np.testing.assert_array_equal(a.stat(name).cpu().numpy(), b.stat(name).cpu().numpy(), err_msg=f"{kw} {name}")
         assert a.stat("flags").cpu().numpy().any()
+
+
+@pytest.mark.parametrize("sync,I", [("adaptive", 0), ("static", 0), ("static", 3)])
+@pytest.mark.parametrize("M", [1, 2, 5, 16])
+@pytest.mark.parametrize("L", [1, 30, 64, 128, 200, 513])
+def test_several_workers_lazy(L, M, sync, I):
+    """Merges now and then, or only at the end: own entries that outgrow their slots and are
+    thinned out, entries that fall out of the local queue, more new entries than one round
+    of a merge publishes."""
+    g = np.random.default_rng([L, M, I])
+    n = 6000
+    base = g.integers(0, 16, (n, 16)).astype(np.float32)
+    q = g.integers(0, 16, (6, 16)).astype(np.float32)
+    for staged in (True, False):
+        check(base, graph(n, 64, g), q, min(L, 20), L, M, sync, label=f"lazy {sync} {I} staged={staged}",
+              ws_hash_slots=1 << 17, lds_hash_slots=4096, orc={"static_I": I, "rho": 0.7, "staged": staged})
