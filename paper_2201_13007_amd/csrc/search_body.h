@@ -147,6 +147,28 @@ __device__ __forceinline__ float group_sum_f32(float v)
     return v;
 }
 
+// The smallest key among the lanes and a lane that holds it.
+__device__ __forceinline__ uint64_t min_key(uint64_t k, int *at)
+{
+    const auto wave_min = [](uint32_t v) {
+        v = min(v, dpp32<DPP_ROW_SHR + 1>(v, v));
+        v = min(v, dpp32<DPP_ROW_SHR + 2>(v, v));
+        v = min(v, dpp32<DPP_ROW_SHR + 4>(v, v));
+        v = min(v, dpp32<DPP_ROW_SHR + 8>(v, v));
+        v = min(v, dpp32<DPP_ROW_BCAST15, 0xA>(v, v));
+        v = min(v, dpp32<DPP_ROW_BCAST31, 0xC>(v, v));
+        return rdlane(v, 63);
+    };
+    const uint32_t hi = wave_min((uint32_t)(k >> 32));
+    uint64_t b = __ballot((uint32_t)(k >> 32) == hi);
+    if (b & (b - 1ull)) {
+        const uint32_t lo = wave_min((b >> __lane_id()) & 1ull ? (uint32_t)k : 0xFFFFFFFFu);
+        b &= __ballot((uint32_t)k == lo);
+    }
+    *at = __builtin_ctzll(b);
+    return rdlane64(k, *at);
+}
+
 // bits [0, n) set, n in [0, 64]
 __device__ __forceinline__ uint64_t low_bits(int n)
 {

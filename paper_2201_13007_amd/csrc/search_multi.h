@@ -152,28 +152,6 @@ __device__ __forceinline__ void migrate_table(const unsigned long long *lh, int 
     }
 }
 
-// The smallest key among the lanes and a lane that holds it.
-__device__ __forceinline__ uint64_t min_key(uint64_t k, int *at)
-{
-    const auto wave_min = [](uint32_t v) {
-        v = min(v, dpp32<DPP_ROW_SHR + 1>(v, v));
-        v = min(v, dpp32<DPP_ROW_SHR + 2>(v, v));
-        v = min(v, dpp32<DPP_ROW_SHR + 4>(v, v));
-        v = min(v, dpp32<DPP_ROW_SHR + 8>(v, v));
-        v = min(v, dpp32<DPP_ROW_BCAST15, 0xA>(v, v));
-        v = min(v, dpp32<DPP_ROW_BCAST31, 0xC>(v, v));
-        return rdlane(v, 63);
-    };
-    const uint32_t hi = wave_min((uint32_t)(k >> 32));
-    uint64_t b = __ballot((uint32_t)(k >> 32) == hi);
-    if (b & (b - 1ull)) {
-        const uint32_t lo = wave_min((b >> __lane_id()) & 1ull ? (uint32_t)k : 0xFFFFFFFFu);
-        b &= __ballot((uint32_t)k == lo);
-    }
-    *at = __builtin_ctzll(b);
-    return rdlane64(k, *at);
-}
-
 // Entries of the sorted S (slen of them, nslots slots) below e, which all lanes hold.
 __device__ __forceinline__ int count_below(const uint64_t *S, int slen, int nslots, uint64_t e)
 {
