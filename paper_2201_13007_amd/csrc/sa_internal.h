@@ -102,6 +102,9 @@ struct SearchLaunch {
     // the workspace then needs one region per resident workgroup, at most nq.  Not with a
     // re-rank (its lists stay in the regions of their jobs).
     int32_t *jobctr = nullptr;
+    // queries of other launches that are or may soon be on the device too: the forms that
+    // spend registers and LDS on few queries count them in
+    int64_t company = 0;
 };
 
 // Workgroups of kernel k (block threads, lds bytes of dynamic LDS) that the device can

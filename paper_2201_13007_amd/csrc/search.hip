@@ -250,7 +250,7 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
     A.qL = a.qL; A.qk = a.qk; A.order = a.order; A.ldo = a.ldo > 0 ? a.ldo : a.k;
     if (a.jobctr && a.p.rerank != 0) return set_error(SA_EUNSUPPORTED, "the persistent form takes no re-rank");
     if (a.nq > 0x7FFFFFFF) return set_error(SA_EINVAL, "nq=%lld out of range", (long long)a.nq);
-    A.jobctr = a.jobctr; A.njobs = (int32_t)a.nq;
+    A.jobctr = a.jobctr; A.njobs = (int32_t)a.nq; A.company = a.company;
     A.ids = a.ids; A.dists = a.dists; A.stats = a.stats;
     A.ghash = reinterpret_cast<unsigned long long *>(a.workspace);
     A.n = a.n;

@@ -54,6 +54,7 @@ struct KArgs {
     // before a launch and the last workgroup sets them back to zero
     int32_t *jobctr;
     int32_t njobs;
+    int64_t company;             // host: queries of other launches on the device (see SearchLaunch)
 };
 
 // Persistent form, end of a workgroup (one thread): the last one to finish puts the job

@@ -368,7 +368,7 @@ hipError_t launch_bsp_one(const KArgs &A, int64_t nq, hipStream_t s)
     // one), as far as the LDS goes round the queries of a CU: its share of the launch, at most
     // the workgroups that 16 wavefronts make
     KArgs B = A;
-    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((nq + 255) / 256, 16 / A.M));
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((nq + A.company + 255) / 256, 16 / A.M));
     B.seen_log2 = 8;
     while (B.seen_log2 < 13 && (1 << B.seen_log2) < 8 * A.L &&
            (int64_t)bsp_lds(A.L, A.M, LPV, B.seen_log2 + 1).total * per_cu <= 156 * 1024)

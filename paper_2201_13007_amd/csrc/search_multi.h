@@ -849,11 +849,14 @@ inline hipError_t launch_multi_form(const void *k, std::atomic<uint64_t> &raised
     }
     int64_t grid = nq;
     if (A.jobctr || only_resident) {
-        e = resident_grid(k, 64 * A.M, lds, nq, &grid);
+        const int64_t all = A.jobctr ? nq : nq + A.company;
+        e = resident_grid(k, 64 * A.M, lds, all, &grid);
         if (e != hipSuccess) return e;
+        *taken = !only_resident || grid >= all;
+        if (!*taken) return hipSuccess;
+        if (!A.jobctr) grid = nq;
     }
-    *taken = !only_resident || grid >= nq;
-    if (!*taken) return hipSuccess;
+    *taken = true;
     KArgs B = A;
     void *args[] = {&B};
     return hipLaunchKernel(k, dim3((unsigned)grid), dim3(64 * A.M), args, lds, s);

@@ -390,7 +390,7 @@ hipError_t launch1(const KArgs &A, int64_t nq, hipStream_t s)
     auto k = A.metric == SA_L2 ? search_single<LPV, NI, true, DT, ACC> : search_single<LPV, NI, false, DT, ACC>;
     const hipError_t e = lds_fill_log2(reinterpret_cast<const void *>(k), 64, base, seen_log2<LPV>(), 11, &B.seen_log2);
     if (e != hipSuccess) return e;
-    B.seen_log2 = seen_log2_for(nq, base, B.seen_log2, A.L);
+    B.seen_log2 = seen_log2_for(nq + A.company, base, B.seen_log2, A.L);
     hipLaunchKernelGGL(k, dim3((unsigned)nq), dim3(64), base + (5u << B.seen_log2), s, B);
     return hipGetLastError();
 }
@@ -456,11 +456,12 @@ hipError_t launch_few(const KArgs &A, int64_t nq, hipStream_t s, bool *taken)
     constexpr uint32_t base = single_lds_base<LPV>(64 * NI);
     auto k = A.metric == SA_L2 ? search_few<LPV, NI, true, DT> : search_few<LPV, NI, false, DT>;
     KArgs B = A;
-    B.seen_log2 = seen_log2_for(nq, base, seen_log2<LPV>(), A.L);
+    const int64_t all = nq + A.company;
+    B.seen_log2 = seen_log2_for(all, base, seen_log2<LPV>(), A.L);
     int64_t grid = 0;
-    const hipError_t e = resident_grid(reinterpret_cast<const void *>(k), 64, base + (5u << B.seen_log2), nq, &grid);
+    const hipError_t e = resident_grid(reinterpret_cast<const void *>(k), 64, base + (5u << B.seen_log2), all, &grid);
     if (e != hipSuccess) return e;
-    *taken = grid >= nq;
+    *taken = grid >= all;
     if (!*taken) return hipSuccess;
     hipLaunchKernelGGL(k, dim3((unsigned)nq), dim3(64), base + (5u << B.seen_log2), s, B);
     return hipGetLastError();

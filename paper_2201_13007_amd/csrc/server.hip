@@ -128,6 +128,14 @@ size_t request_region(const sa_server *S, int32_t L, int32_t M)
 // class, shortest first, its launch, the copy of its result rows and its event.
 int launch_slot(sa_server *S, Slot &sl)
 {
+    // the requests in the other slots, and those that wait for one
+    int64_t company = 0;
+    for (const Slot &o : S->slots)
+        if (&o != &sl && o.busy) company += (int64_t)o.reqs.size();
+    {
+        std::lock_guard<std::mutex> g(S->mu);
+        company += S->nwaiting;
+    }
     const int b = (int)sl.reqs.size();
     const int d = S->d;
     const size_t o_L = align16(4 * (size_t)b * d), o_k = o_L + align16(4 * (size_t)b), n_in = o_k + 4 * (size_t)b;
@@ -183,6 +191,7 @@ int launch_slot(sa_server *S, Slot &sl)
         a.qk = reinterpret_cast<const int32_t *>(sl.d_in + o_k) + i;
         a.order = nullptr;
         a.ldo = kmax;
+        a.company = company;
         const int rc = launch_search(a, sl.stream);
         if (rc != SA_OK) return rc;
         const size_t rows = 4 * (size_t)(j - i) * kmax;
