@@ -320,10 +320,18 @@ int launch_search(const SearchLaunch &a, hipStream_t stream)
         } else {
             rc = launch_search_single_f32(A, a.nq, stream);
         }
-    } else if (a.M >= 2 && a.p.sync == SA_SYNC_BSP) {
+    } else if (a.M >= 2 && a.p.sync == SA_SYNC_BSP && (llog2 == 0 || glog2 >= llog2)) {
         if (a.dtype == SA_F32 && a.int_lo <= a.int_hi && search_detail::lanes_per_vector(a.d) <= 16) A.acc_pass = 2;
         rc = launch_search_bsp(A, a.dtype, a.nq, stream);
     } else {
+        if (a.M >= 2 && a.p.sync == SA_SYNC_BSP) {
+            // A search may visit half of 2^llog2 vertices before the workspace table's own bound
+            // (three quarters of 2^glog2) counts.  The every-step kernel keeps no LDS table of
+            // that size and may put any of them into the workspace table, so where that is the
+            // smaller one the search runs here, as the same schedule: one local step a merge.
+            A.sync = SA_SYNC_STATIC;
+            A.static_I = 1;
+        }
         const bool large = a.L > 256;
         if (a.dtype == SA_BF16)
             rc = large ? launch_search_multi_large_bf16(A, a.nq, stream) : launch_search_multi_bf16(A, a.nq, stream);

@@ -138,7 +138,9 @@ __device__ __forceinline__ void bsp_body(const KArgs &A, int64_t job, int64_t re
     __syncthreads();
 
     // Every wavefront keeps the same counts.  The visited set's bounds are those of the general
-    // kernel's tables, so that a search spills and stops where it did there.
+    // kernel's tables, so that a search spills and stops where it did there.  The table always
+    // has room for what they allow: glog2 >= llog2 (the launcher sees to it), so half of 2^llog2
+    // is at most half of it.
     int slen = 1, hcount = 1, steps = 0, nexp = 0, flags = 0;
     bool spilled = A.llog2 == 0, stop = false;
     int m = A.staged ? 1 : M;
