@@ -603,6 +603,12 @@ __global__ void __launch_bounds__(64) gateway_rows(const int32_t *src, int64_t n
     if (lane < R) row[lane] = out;
 }
 
+__global__ void put_rows(const int32_t *src, int64_t cnt, const int32_t *rows, int R, int32_t *adj)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < cnt * R) adj[(int64_t)src[e / R] * R + e % R] = rows[e];
+}
+
 // One level of a breadth-first walk: the out-neighbours of the vertices at level cur get
 // cur + 1; *changed is set if there was one.
 __global__ void __launch_bounds__(256) bfs_level(const int32_t *adj, int64_t n, int R, int32_t *level, int32_t cur, int32_t *changed)
@@ -820,6 +826,23 @@ void host_links(const std::vector<int32_t> &src, const std::vector<int32_t> &rep
     }
 }
 
+// Puts rows back that a repair which then fails has written: its caller's rows are either
+// repaired or as they were.
+struct RowsBack {
+    const int32_t *src = nullptr, *rows = nullptr;
+    int64_t cnt = 0;
+    int32_t *adj;
+    int R;
+    hipStream_t s;
+    RowsBack(int32_t *adj_, int R_, hipStream_t s_) : adj(adj_), R(R_), s(s_) {}
+    ~RowsBack()
+    {
+        if (cnt == 0) return;
+        hipLaunchKernelGGL(put_rows, dim3(blocks_for(cnt * R, 256)), dim3(256), 0, s, src, cnt, rows, R, adj);
+        (void)hipStreamSynchronize(s);
+    }
+};
+
 }  // namespace
 
 int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, int32_t *adj_dev, int R,
@@ -850,6 +873,8 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
 
     // (2) gateway rows for the representatives (each component's medoid), the entry and the
     // hubs (the vertices nearest to the mean of all rows)
+    Arena D;
+    RowsBack back(adj_dev, R, s);   // (before D goes)
     if (nc > 1) {
         int32_t *const comp = par;   // (the union-find is done with it)
         hipLaunchKernelGGL(comp_of, bn, t256, 0, s, root, num, n, comp);
@@ -915,8 +940,8 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
             for (size_t j = 0; j < take; ++j) src.push_back(hv[j].v);
         }
         const int64_t nsrc = (int64_t)src.size();
-        Arena D;
         const size_t o_src = D.want<int32_t>(nsrc), o_dv = D.want<float>(nsrc * nc), o_links = D.want<int32_t>(nsrc * R);
+        const size_t o_old = D.want<int32_t>(nsrc * R);
         if (D.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
         int32_t *const src_dev = D.get<int32_t>(o_src), *const links = D.get<int32_t>(o_links);
         float *const dv = D.get<float>(o_dv);
@@ -940,6 +965,12 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
             SA_HIP(hipMemcpyAsync(links, hl.data(), sizeof(int32_t) * hl.size(), hipMemcpyHostToDevice, s));
             SA_HIP(hipStreamSynchronize(s));
         }
+        hipLaunchKernelGGL(gather_rows, dim3(blocks_for(nsrc * R, 256)), t256, 0, s, adj_dev, (int64_t)R, R, src_dev, nsrc,
+                           D.get<int32_t>(o_old));
+        SA_HIP(hipGetLastError());
+        back.src = src_dev;
+        back.rows = D.get<int32_t>(o_old);
+        back.cnt = nsrc;
         hipLaunchKernelGGL(gateway_rows, dim3((unsigned)nsrc), dim3(64), 0, s, src_dev, nc, links, R, keep_local, hub_keep_local,
                            adj_dev);
         SA_HIP(hipGetLastError());
@@ -1115,6 +1146,7 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
         SA_HIP(hipGetLastError());
         SA_HIP(hipStreamSynchronize(s));
     }
+    back.cnt = 0;
     if (bridges_out) *bridges_out = added;
     return SA_OK;
 }
