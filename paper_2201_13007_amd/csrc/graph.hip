@@ -242,10 +242,10 @@ __global__ void fill_u64_n(unsigned long long *p, int64_t cnt, unsigned long lon
 __global__ void __launch_bounds__(256) row_degrees(const int32_t *adj, int64_t n, int R, int prefix, int32_t *deg)
 {
     const int lane = __lane_id();
-    const int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (v >= n) return;
-    const uint64_t neg = __ballot(lane >= R || adj[v * R + (lane < R ? lane : 0)] < 0);
-    if (lane == 0) deg[v] = prefix ? (neg ? __builtin_ctzll(neg) : 64) : 64 - __popcll(neg);
+    for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < n; v += (int64_t)gridDim.x * 4) {
+        const uint64_t neg = __ballot(lane >= R || adj[v * R + (lane < R ? lane : 0)] < 0);
+        if (lane == 0) deg[v] = prefix ? (neg ? __builtin_ctzll(neg) : 64) : 64 - __popcll(neg);
+    }
 }
 
 constexpr int SCAN_CHUNK = 2048;   // elements per workgroup of the prefix sum
@@ -321,7 +321,9 @@ __global__ void fill_i32(int32_t *p, int64_t cnt, int32_t v)
     if (i < cnt) p[i] = v;
 }
 
-unsigned blocks_for(int64_t cnt, int per) { return (unsigned)((cnt + per - 1) / per); }
+// A launch takes fewer than 2^32 work items along x, which a wavefront a row reaches at 2^26
+// rows and a thread an edge at 2^32 edges: such kernels walk their work in strides of the grid.
+unsigned blocks_for(int64_t cnt, int per) { return (unsigned)std::min<int64_t>((cnt + per - 1) / per, 1 << 23); }
 
 // ---------------------------------------------------------------- reverse edges
 
@@ -330,13 +332,13 @@ unsigned blocks_for(int64_t cnt, int per) { return (unsigned)((cnt + per - 1) / 
 __global__ void in_edges(const float *base, int64_t n, int d, int64_t ld, int metric, const int32_t *adj, int R,
                          const int32_t *deg, int32_t *cnt, const int64_t *start, uint64_t *in)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * R) return;
-    const int64_t p = e / R;
-    const int32_t c = adj[e];
-    if (c < 0 || c >= n || deg[c] >= R) return;
-    const int pos = atomicAdd(cnt + c, 1);
-    if (in) in[start[c] + pos] = make_key(dist_seq(base + (int64_t)c * ld, base + p * ld, d, metric), (int32_t)p);
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * R; e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t p = e / R;
+        const int32_t c = adj[e];
+        if (c < 0 || c >= n || deg[c] >= R) continue;
+        const int pos = atomicAdd(cnt + c, 1);
+        if (in) in[start[c] + pos] = make_key(dist_seq(base + (int64_t)c * ld, base + p * ld, d, metric), (int32_t)p);
+    }
 }
 
 // sorts one key per lane, ascending
@@ -361,44 +363,44 @@ __global__ void __launch_bounds__(256) append_in_edges(int64_t n, int R, const i
                                                        const uint64_t *in, int32_t *adj, unsigned long long *added)
 {
     const int lane = __lane_id();
-    const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (c >= n) return;
-    int len = deg[c];
-    const int64_t b = start[c], e = start[c + 1];
-    if (len >= R || b == e) return;
-    const int before = len;
-    int32_t row = lane < len ? adj[c * R + lane] : -1;
-    uint64_t last = 0;
-    bool some = false, more = true;
-    while (more && len < R) {
-        uint64_t best = KEY_EMPTY;
-        for (int64_t i0 = b; i0 < e; i0 += 64) {
-            uint64_t v = i0 + lane < e ? in[i0 + lane] : KEY_EMPTY;
-            if (some && v <= last) v = KEY_EMPTY;
-            const uint64_t worst = (uint64_t)__shfl((unsigned long long)best, 63, 64);
-            if (__ballot(v < worst) == 0) continue;
-            v = sort64(v);
-            // the smaller of best[l] and v[63 - l] are the 64 smallest, bitonic in l
-            const uint64_t r = (uint64_t)__shfl((unsigned long long)v, 63 - lane, 64);
-            best = r < best ? r : best;
-            for (int j = 32; j > 0; j >>= 1) {
-                const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)best, j, 64);
-                best = ((lane & j) == 0) == (o < best) ? o : best;
+    for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c < n; c += (int64_t)gridDim.x * 4) {
+        int len = deg[c];
+        const int64_t b = start[c], e = start[c + 1];
+        if (len >= R || b == e) continue;
+        const int before = len;
+        int32_t row = lane < len ? adj[c * R + lane] : -1;
+        uint64_t last = 0;
+        bool some = false, more = true;
+        while (more && len < R) {
+            uint64_t best = KEY_EMPTY;
+            for (int64_t i0 = b; i0 < e; i0 += 64) {
+                uint64_t v = i0 + lane < e ? in[i0 + lane] : KEY_EMPTY;
+                if (some && v <= last) v = KEY_EMPTY;
+                const uint64_t worst = (uint64_t)__shfl((unsigned long long)best, 63, 64);
+                if (__ballot(v < worst) == 0) continue;
+                v = sort64(v);
+                // the smaller of best[l] and v[63 - l] are the 64 smallest, bitonic in l
+                const uint64_t r = (uint64_t)__shfl((unsigned long long)v, 63 - lane, 64);
+                best = r < best ? r : best;
+                for (int j = 32; j > 0; j >>= 1) {
+                    const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)best, j, 64);
+                    best = ((lane & j) == 0) == (o < best) ? o : best;
+                }
             }
+            const int got = __popcll(__ballot(best != KEY_EMPTY));
+            for (int i = 0; i < got && len < R; ++i) {
+                const int32_t p = key_id((uint64_t)__shfl((unsigned long long)best, i, 64));
+                if (__ballot(row == p)) continue;
+                if (lane == len) row = p;
+                ++len;
+            }
+            more = got == 64;
+            some = true;
+            last = (uint64_t)__shfl((unsigned long long)best, 63, 64);
         }
-        const int got = __popcll(__ballot(best != KEY_EMPTY));
-        for (int i = 0; i < got && len < R; ++i) {
-            const int32_t p = key_id((uint64_t)__shfl((unsigned long long)best, i, 64));
-            if (__ballot(row == p)) continue;
-            if (lane == len) row = p;
-            ++len;
-        }
-        more = got == 64;
-        some = true;
-        last = (uint64_t)__shfl((unsigned long long)best, 63, 64);
+        if (lane >= before && lane < len) adj[c * R + lane] = row;
+        if (lane == 0 && len > before) atomicAdd(added, (unsigned long long)(len - before));
     }
-    if (lane >= before && lane < len) adj[c * R + lane] = row;
-    if (lane == 0 && len > before) atomicAdd(added, (unsigned long long)(len - before));
 }
 
 // ---------------------------------------------------------------- repair
@@ -430,17 +432,17 @@ __global__ void uf_init(int32_t *par, int64_t n)
 
 __global__ void uf_hook(const int32_t *adj, int64_t n, int R, int32_t *par)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * R) return;
-    const int32_t u = adj[e];
-    if (u < 0 || u >= n) return;
-    int32_t a = uf_root(par, (int32_t)(e / R)), b = uf_root(par, u);
-    while (a != b) {
-        const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
-        const int32_t old = atomicCAS(par + hi, hi, lo);
-        if (old == hi) break;   // hi was still a root
-        a = uf_root(par, old);
-        b = uf_root(par, lo);
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * R; e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t u = adj[e];
+        if (u < 0 || u >= n) continue;
+        int32_t a = uf_root(par, (int32_t)(e / R)), b = uf_root(par, u);
+        while (a != b) {
+            const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
+            const int32_t old = atomicCAS(par + hi, hi, lo);
+            if (old == hi) break;   // hi was still a root
+            a = uf_root(par, old);
+            b = uf_root(par, lo);
+        }
     }
 }
 
@@ -511,9 +513,8 @@ __global__ void nearest_member(const double *dist, const int32_t *comp, int64_t 
 __global__ void pair_dists(const float *base, int d, int64_t ld, int metric, const int32_t *us, int64_t nu,
                            const int32_t *ws, int64_t nw, float *out)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nu * nw) return;
-    out[e] = dist_seq(base + (int64_t)us[e / nw] * ld, base + (int64_t)ws[e % nw] * ld, d, metric);
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nu * nw; e += (int64_t)gridDim.x * blockDim.x)
+        out[e] = dist_seq(base + (int64_t)us[e / nw] * ld, base + (int64_t)ws[e % nw] * ld, d, metric);
 }
 
 constexpr int LINK_REPS = 4096;   // representatives the link kernel can sort in LDS
@@ -605,8 +606,8 @@ __global__ void __launch_bounds__(64) gateway_rows(const int32_t *src, int64_t n
 
 __global__ void put_rows(const int32_t *src, int64_t cnt, const int32_t *rows, int R, int32_t *adj)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < cnt * R) adj[(int64_t)src[e / R] * R + e % R] = rows[e];
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < cnt * R; e += (int64_t)gridDim.x * blockDim.x)
+        adj[(int64_t)src[e / R] * R + e % R] = rows[e];
 }
 
 // One level of a breadth-first walk: the out-neighbours of the vertices at level cur get
@@ -638,8 +639,8 @@ __global__ void level_marks(const int32_t *level, int64_t n, uint8_t *mark)
 // rows ids[i] of src (row_words 32-bit words, stride words apart) to dst row i
 __global__ void gather_rows(const int32_t *src, int64_t stride, int row_words, const int32_t *ids, int64_t cnt, int32_t *dst)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < cnt * row_words) dst[e] = src[(int64_t)ids[e / row_words] * stride + e % row_words];
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < cnt * row_words; e += (int64_t)gridDim.x * blockDim.x)
+        dst[e] = src[(int64_t)ids[e / row_words] * stride + e % row_words];
 }
 
 __global__ void apply_edits(const int64_t *pos, const int32_t *val, int64_t cnt, int32_t *adj)

@@ -31,3 +31,27 @@ def test_failed_repair_leaves_the_rows():
     g = torch.from_numpy(wide).cuda()
     assert B.repair(torch.from_numpy(base).cuda(), g, 0, keep_local=1, hubs=1, hub_keep_local=2) == (b, c)
     np.testing.assert_array_equal(g.cpu().numpy(), want)
+
+
+def test_more_rows_than_a_launch_has_wavefronts():
+    """2^26 + 1000 rows of 64 entries: a tree, every vertex linked to its 64 children.  The
+    vertices with room get their parent; then all are one component within reach."""
+    from paper_2201_13007_amd import binding as B
+    n, R = (1 << 26) + 1000, 64
+    base = torch.zeros((n, 4), device="cuda")
+    base[:, 0] = torch.arange(n, device="cuda") % 1000
+    adj = torch.empty((n, R), dtype=torch.int32, device="cuda")
+    for r0 in range(0, n, 1 << 23):
+        v = torch.arange(r0, min(n, r0 + (1 << 23)), device="cuda")
+        c = v[:, None] * R + 1 + torch.arange(R, device="cuda")
+        adj[r0:r0 + len(v)] = torch.where(c < n, c, -1).int()
+        del c
+    inner = (n - 1) // R      # vertices whose row is full; the next may have some children
+    some = n - 1 - inner * R
+    print(f"case: tree of {n} rows", flush=True)
+    assert B.reverse_edges(base, adj) == n - inner
+    v = torch.arange(inner + 1, n, device="cuda")
+    assert bool((adj[inner + 1:, 0] == ((v - 1) // R).int()).all()) and bool((adj[inner + 1:, 1:] == -1).all())
+    assert adj[inner, some].item() == (inner - 1) // R
+    info = B.repair(base, adj, 0)
+    assert tuple(info) == (0, 1)
