@@ -747,9 +747,9 @@ struct Forms {
     bool integer, flt;
 };
 
-Forms knn_forms(int64_t n, int32_t d, int32_t k, int32_t path)
+Forms knn_forms(int64_t n, int32_t d, int32_t k, int32_t path, bool any_k = true)
 {
-    const bool large_k = path == SA_KNN_AUTO && n >= 2048;
+    const bool large_k = any_k && path == SA_KNN_AUTO && n >= 2048;
     Forms f;
     f.integer = path != SA_KNN_SCAN && n >= 1 && d <= 256 && (k <= 128 || large_k);
     f.flt = path != SA_KNN_SCAN && n >= 1 && d <= 1024 && (k <= 96 || large_k);
@@ -784,26 +784,35 @@ int launch_knn(const float *base, int64_t n, int32_t d, int64_t ld, const float 
     if (path != SA_KNN_AUTO && path != SA_KNN_SCAN && path != SA_KNN_MFMA)
         return set_error(SA_EINVAL, "unknown kNN path %d", path);
     if (nq == 0) return SA_OK;
-    const Forms f = knn_forms(n, d, k, path);
+    Forms f = knn_forms(n, d, k, path);
     if (path == SA_KNN_MFMA && !f.integer && !f.flt)
         return set_error(SA_EUNSUPPORTED, "the MFMA kNN path needs n >= 1 and d <= 256, k <= 128 (integer data) or "
                          "d <= 1024, k <= 96 (n=%lld, d=%d, k=%d)", (long long)n, d, k);
+    DeviceBlock mem;
+    std::vector<Plan> plan;
+    for (int64_t qc = std::min<int64_t>(nq, QCHUNK); f.integer || f.flt;) {
+        // one block for whichever form runs; smaller chunks of queries if it does not fit
+        const size_t need = knn_plans(f, n, d, nq, k, qc, plan);
+        if (ws ? need <= ws_bytes : hipMalloc(&mem.p, need) == hipSuccess) break;
+        if (!ws) {
+            (void)hipGetLastError();
+            mem.p = nullptr;
+        }
+        const Forms least = knn_forms(n, d, k, path, false);
+        if (qc > 1024) {
+            qc = std::max<int64_t>(1024, qc / 2);
+        } else if (!ws && (f.integer != least.integer || f.flt != least.flt)) {
+            // forms that only SA_KNN_AUTO's larger k allows must not cost the call: the scan
+            // needs no memory
+            f = least;
+            qc = std::min<int64_t>(nq, QCHUNK);
+        } else {
+            return ws ? set_error(SA_ECAPACITY, "workspace of %zu bytes is smaller than the %zu bytes needed", ws_bytes, need)
+                      : set_error(SA_ENOMEM, "hipMalloc of the bf16 copies failed");
+        }
+    }
     if (f.integer || f.flt) {
         bool ran = false;
-        DeviceBlock mem;
-        std::vector<Plan> plan;
-        for (int64_t qc = std::min<int64_t>(nq, QCHUNK);; qc = std::max<int64_t>(1024, qc / 2)) {
-            // one block for whichever form runs; smaller chunks of queries if it does not fit
-            const size_t need = knn_plans(f, n, d, nq, k, qc, plan);
-            if (ws ? need <= ws_bytes : hipMalloc(&mem.p, need) == hipSuccess) break;
-            if (!ws) {
-                (void)hipGetLastError();
-                mem.p = nullptr;
-            }
-            if (qc <= 1024)
-                return ws ? set_error(SA_ECAPACITY, "workspace of %zu bytes is smaller than the %zu bytes needed", ws_bytes, need)
-                          : set_error(SA_ENOMEM, "hipMalloc of the bf16 copies failed");
-        }
         unsigned char *const m = static_cast<unsigned char *>(ws ? ws : mem.p);
         const Call c{base, n, d, ld, queries, nq, ldq, k, metric, exclude_self, ids, dists, stream};
         int rc = SA_OK;
