@@ -21,8 +21,14 @@ def test_large_k_without_memory(d, k, integer):
     base, q = x.cpu().numpy(), qs.cpu().numpy()
     torch.cuda.empty_cache()
     print(f"case: n={n} d={d} k={k}", flush=True)
-    free = torch.cuda.mem_get_info()[0]
-    fill = torch.empty(free - (192 << 20), dtype=torch.uint8, device="cuda")
+    fill = [torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")]
+    try:
+        while len(fill) < 40:
+            fill.append(torch.empty(96 << 20, dtype=torch.uint8, device="cuda"))
+    except torch.OutOfMemoryError:
+        del fill[1:3]
+        torch.cuda.empty_cache()
+    assert len(fill) < 40
     try:
         ids, dists, path = B.knn(x, qs, k, return_path=True)
         torch.cuda.synchronize()
