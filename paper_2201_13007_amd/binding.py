@@ -171,8 +171,13 @@ def _scratch(nbytes: int, device, stream=None):
     keeps it for the next call; None (the library allocates its own) where there is none left."""
     if nbytes <= 0:
         return None
+    if stream is None:
+        stream = torch.cuda.current_stream()
+    elif not isinstance(stream, torch.cuda.Stream):    # any object with a stream's handle will do
+        h = int(stream.cuda_stream)
+        stream = torch.cuda.ExternalStream(h, device=device) if h else torch.cuda.default_stream(device)
     try:
-        with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream()):
+        with torch.cuda.stream(stream):
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
         return None
