@@ -166,10 +166,17 @@ def pad_dim(x: torch.Tensor) -> torch.Tensor:
     return out
 
 
+# The most scratch memory that is left with torch's allocator after a call.  Allocating and
+# freeing costs some 0.4 ms a call, little for calls that need more than this, and what torch
+# keeps the library's own allocations cannot have.
+KEEP_SCRATCH = 2 << 30
+
+
 def _scratch(nbytes: int, device, stream=None):
     """Device memory for one synchronous library call on `stream`, from torch's allocator, which
-    keeps it for the next call; None (the library allocates its own) where there is none left."""
-    if nbytes <= 0:
+    keeps it for the next call; None (the library allocates its own and frees it) beyond
+    KEEP_SCRATCH or where there is none left."""
+    if not 0 < nbytes <= KEEP_SCRATCH:
         return None
     if stream is None:
         stream = torch.cuda.current_stream()

@@ -39,3 +39,17 @@ def test_large_k_without_memory(d, k, integer):
     eids, ed = oracle.knn(base, q, k)
     np.testing.assert_array_equal(ids.cpu().numpy(), eids)
     np.testing.assert_array_equal(dists.cpu().numpy(), ed)
+
+
+def test_large_scratch_is_given_back():
+    from paper_2201_13007_amd import binding as B
+    x = torch.zeros((700_000, 1024), device="cuda")      # 2.9 GB of bf16 copies
+    x[:, 0] = torch.arange(700_000, device="cuda") * 0.5
+    B.knn(x[:1000].clone(), x[:2].clone(), 3)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.memory_reserved()
+    print("case: 700,000 x 1024", flush=True)
+    ids, _ = B.knn(x, x[[5, 699_999]].clone(), 1)
+    assert ids.flatten().tolist() == [5, 699_999]
+    assert torch.cuda.memory_reserved() - before < (64 << 20)
