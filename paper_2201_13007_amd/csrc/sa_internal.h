@@ -109,7 +109,7 @@ struct SearchLaunch {
 
 // Workgroups of kernel k (block threads, lds bytes of dynamic LDS) that the device can
 // hold at once, at most njobs: the grid of a persistent launch.  Cached per kernel,
-// LDS size and device.
+// workgroup size, LDS size and device.
 hipError_t resident_grid(const void *k, int block, uint32_t lds, int64_t njobs, int64_t *grid);
 // The largest log2 of sets, in [lmin, lmax], for a filter of 4 << l bytes of LDS on top of
 // base that leaves kernel k (block threads) as many workgroups per CU as the smallest

@@ -166,14 +166,14 @@ int index_integer_range(const float *x, int64_t n, int32_t d, int64_t ld, int32_
 hipError_t resident_grid(const void *k, int block, uint32_t lds, int64_t njobs, int64_t *grid)
 {
     static std::mutex mu;
-    static std::map<std::tuple<const void *, uint32_t, int>, int64_t> cache;
+    static std::map<std::tuple<const void *, int, uint32_t, int>, int64_t> cache;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     int64_t slots = 0;
     {
         std::lock_guard<std::mutex> g(mu);
-        auto it = cache.find({k, lds, dev});
+        auto it = cache.find({k, block, lds, dev});
         if (it != cache.end()) slots = it->second;
     }
     if (slots == 0) {
@@ -183,7 +183,7 @@ hipError_t resident_grid(const void *k, int block, uint32_t lds, int64_t njobs, 
         if (e != hipSuccess) return e;
         slots = std::max<int64_t>(1, (int64_t)per_cu * cus);
         std::lock_guard<std::mutex> g(mu);
-        cache[{k, lds, dev}] = slots;
+        cache[{k, block, lds, dev}] = slots;
     }
     *grid = std::max<int64_t>(1, std::min(njobs, slots));
     return hipSuccess;
