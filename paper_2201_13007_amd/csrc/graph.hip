@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(256) scan_write(const int32_t *cnt, int64_t n,
 {
     __shared__ int64_t part[4];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
-    int64_t run = sums[blockIdx.x];
+    int64_t run = sums ? sums[blockIdx.x] : 0;
     for (int j0 = 0; j0 < SCAN_CHUNK; j0 += 256) {
         const int64_t i = (int64_t)blockIdx.x * SCAN_CHUNK + j0 + threadIdx.x;
         const int64_t v = i < n ? cnt[i] : 0;
@@ -303,12 +303,17 @@ __global__ void __launch_bounds__(256) scan_write(const int32_t *cnt, int64_t n,
         run += part[0] + part[1] + part[2] + part[3];
         __syncthreads();
     }
+    if (!sums && threadIdx.x == 0) out[n] = run;
 }
 
 // sums: room for (n + SCAN_CHUNK - 1) / SCAN_CHUNK entries
 hipError_t prefix_sums(const int32_t *cnt, int64_t n, int64_t *sums, int64_t *out, hipStream_t s)
 {
     const int64_t nchunk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    if (nchunk == 1) {
+        hipLaunchKernelGGL(scan_write, dim3(1), dim3(256), 0, s, cnt, n, (const int64_t *)nullptr, out);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(scan_sums, dim3((unsigned)nchunk), dim3(256), 0, s, cnt, n, sums);
     hipLaunchKernelGGL(scan_chunks, dim3(1), dim3(64), 0, s, sums, nchunk, out + n);
     hipLaunchKernelGGL(scan_write, dim3((unsigned)nchunk), dim3(256), 0, s, cnt, n, sums, out);
@@ -327,8 +332,8 @@ unsigned blocks_for(int64_t cnt, int per) { return (unsigned)std::min<int64_t>((
 
 // ---------------------------------------------------------------- reverse edges
 
-// In-edges of the vertices that have room, counted (in null) or written as keys
-// (d(c, p), p) in any order behind start[c]
+// In-edges of the vertices that have room, counted (in null) or, counting back down, written
+// as keys (d(c, p), p) in any order behind start[c]
 __global__ void in_edges(const float *base, int64_t n, int d, int64_t ld, int metric, const int32_t *adj, int R,
                          const int32_t *deg, int32_t *cnt, const int64_t *start, uint64_t *in)
 {
@@ -336,7 +341,7 @@ __global__ void in_edges(const float *base, int64_t n, int d, int64_t ld, int me
         const int64_t p = e / R;
         const int32_t c = adj[e];
         if (c < 0 || c >= n || deg[c] >= R) continue;
-        const int pos = atomicAdd(cnt + c, 1);
+        const int pos = in ? atomicSub(cnt + c, 1) - 1 : atomicAdd(cnt + c, 1);
         if (in) in[start[c] + pos] = make_key(dist_seq(base + (int64_t)c * ld, base + p * ld, d, metric), (int32_t)p);
     }
 }
@@ -462,16 +467,17 @@ __global__ void comp_of(const int32_t *root, const int64_t *number, int64_t n, i
     if (i < n) comp[i] = (int32_t)number[root[i]];
 }
 
-// mean of each group of rows: members[start[g] .. start[g + 1]) (members null: the rows
-// themselves), summed in that order; one wavefront per 64 columns and group
-__global__ void __launch_bounds__(64) group_means(const float *base, int d, int64_t ld, const int32_t *members,
-                                                  const int64_t *start, double *mean)
+// mean of each group g < nc of rows: members[start[g] .. start[g + 1]), summed in that order, and
+// of the n rows themselves (g = nc); one wavefront per 64 columns and group, all at once: a
+// large group's sum takes 26 ns a row, one addition after the other
+__global__ void __launch_bounds__(64) group_means(const float *base, int64_t n, int d, int64_t ld, const int32_t *members,
+                                                  const int64_t *start, int64_t nc, double *mean)
 {
     const int64_t g = blockIdx.x;
     const int c = blockIdx.y * 64 + threadIdx.x;
     if (c >= d) return;
-    const int64_t b = start[g], cnt = start[g + 1] - b;
-    const double s = members ? seq_sum(base + c, ld, members + b, cnt) : seq_sum(base + b * ld + c, ld, nullptr, cnt);
+    const int64_t b = g < nc ? start[g] : 0, cnt = g < nc ? start[g + 1] - b : n;
+    const double s = g < nc ? seq_sum(base + c, ld, members + b, cnt) : seq_sum(base + c, ld, nullptr, n);
     mean[g * d + c] = s / (double)cnt;
 }
 
@@ -750,14 +756,15 @@ int reverse_edges_device(const float *base, int64_t n, int d, int64_t ld, int me
     if (n < 1) return SA_OK;
     const int64_t ne = n * R, nchunk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
     Arena A;
-    const size_t o_deg = A.want<int32_t>(n), o_cnt = A.want<int32_t>(n), o_start = A.want<int64_t>(n + 1);
-    const size_t o_sums = A.want<int64_t>(nchunk), o_added = A.want<unsigned long long>(1);
+    const size_t o_deg = A.want<int32_t>(n), o_start = A.want<int64_t>(n + 1), o_sums = A.want<int64_t>(nchunk);
+    const size_t o_cnt = A.want<int32_t>(n), o_added = A.want<unsigned long long>(1);   // (zeroed together)
     if (A.alloc() != hipSuccess) return set_error(SA_ENOMEM, "reverse edges: device allocation failed");
     int32_t *const deg = A.get<int32_t>(o_deg), *const cnt = A.get<int32_t>(o_cnt);
     int64_t *const start = A.get<int64_t>(o_start);
     unsigned long long *const added = A.get<unsigned long long>(o_added);
     hipLaunchKernelGGL(row_degrees, dim3(blocks_for(n, 4)), dim3(256), 0, s, adj_dev, n, R, 1, deg);
-    hipLaunchKernelGGL(fill_i32, dim3(blocks_for(n, 256)), dim3(256), 0, s, cnt, n, 0);
+    const int64_t zeroed = (int64_t)(o_added + 8 - o_cnt) / 4;
+    hipLaunchKernelGGL(fill_i32, dim3(blocks_for(zeroed, 256)), dim3(256), 0, s, cnt, zeroed, 0);
     hipLaunchKernelGGL(in_edges, dim3(blocks_for(ne, 256)), dim3(256), 0, s, base, n, d, ld, metric, adj_dev, R, deg, cnt,
                        (const int64_t *)nullptr, (uint64_t *)nullptr);
     SA_HIP(hipGetLastError());
@@ -769,8 +776,6 @@ int reverse_edges_device(const float *base, int64_t n, int d, int64_t ld, int me
     const size_t o_in = K.want<uint64_t>(total);
     if (K.alloc() != hipSuccess) return set_error(SA_ENOMEM, "reverse edges: device allocation failed");
     uint64_t *const in = K.get<uint64_t>(o_in);
-    hipLaunchKernelGGL(fill_i32, dim3(blocks_for(n, 256)), dim3(256), 0, s, cnt, n, 0);
-    hipLaunchKernelGGL(fill_u64_n, dim3(1), dim3(64), 0, s, added, (int64_t)1, 0ull);
     hipLaunchKernelGGL(in_edges, dim3(blocks_for(ne, 256)), dim3(256), 0, s, base, n, d, ld, metric, adj_dev, R, deg, cnt,
                        (const int64_t *)start, in);
     hipLaunchKernelGGL(append_in_edges, dim3(blocks_for(n, 4)), dim3(256), 0, s, n, R, deg, start, in, adj_dev, added);
@@ -827,6 +832,31 @@ void host_links(const std::vector<int32_t> &src, const std::vector<int32_t> &rep
     }
 }
 
+// Weakly connected components of n rows, numbered by their smallest vertices; returns how many.
+int64_t host_components(const std::vector<int32_t> &adj, int64_t n, int R, std::vector<int32_t> &comp)
+{
+    std::vector<int32_t> par((size_t)n);
+    for (int64_t i = 0; i < n; ++i) par[i] = (int32_t)i;
+    const auto root = [&](int32_t x) {
+        while (par[x] != x) x = par[x] = par[par[x]];
+        return x;
+    };
+    for (int64_t v = 0; v < n; ++v)
+        for (int r = 0; r < R; ++r) {
+            const int32_t u = adj[v * R + r];
+            if (u < 0 || u >= n) continue;
+            const int32_t a = root((int32_t)v), b = root(u);
+            if (a != b) par[std::max(a, b)] = std::min(a, b);
+        }
+    comp.resize((size_t)n);
+    int64_t nc = 0;
+    for (int64_t i = 0; i < n; ++i) {   // (a root is the smallest vertex of its component)
+        const int32_t x = root((int32_t)i);
+        comp[i] = x == i ? (int32_t)nc++ : comp[x];
+    }
+    return nc;
+}
+
 // Puts rows back that a repair which then fails has written: its caller's rows are either
 // repaired or as they were.
 struct RowsBack {
@@ -852,24 +882,43 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
 {
     const int64_t ne = n * R, nchunk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
     const int dcol = (d + 63) / 64;
+    // Components and reachability of up to 2^17 edges come from a copy of the rows on the host:
+    // some twenty launches and three looks at their results take 200 us on any connected graph,
+    // the copy and the host 61 us at 300 rows of 32 and 442 at 3,000 (against 540).
+    const bool small = ne <= (1 << 17);
+    std::vector<int32_t> hadj, hcomp;
     Arena A;
     const size_t o_par = A.want<int32_t>(n), o_root = A.want<int32_t>(n), o_flag = A.want<int32_t>(n), o_num = A.want<int64_t>(n + 1);
     const size_t o_sums = A.want<int64_t>(nchunk), o_dist = A.want<double>(n), o_mark = A.want<uint8_t>(n), o_chg = A.want<int32_t>(1);
-    if (A.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
-    int32_t *const par = A.get<int32_t>(o_par), *const root = A.get<int32_t>(o_root), *const flag = A.get<int32_t>(o_flag);
-    int64_t *const num = A.get<int64_t>(o_num);
-    double *const dist = A.get<double>(o_dist);
     const dim3 bn(blocks_for(n, 256)), t256(256);
+    const auto copy_rows = [&]() -> int {
+        hadj.resize((size_t)ne);
+        SA_HIP(hipMemcpyAsync(hadj.data(), adj_dev, sizeof(int32_t) * ne, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipStreamSynchronize(s));
+        return SA_OK;
+    };
 
     // (1) weakly connected components, numbered by smallest member
-    hipLaunchKernelGGL(uf_init, bn, t256, 0, s, par, n);
-    hipLaunchKernelGGL(uf_hook, dim3(blocks_for(ne, 256)), t256, 0, s, adj_dev, n, R, par);
-    hipLaunchKernelGGL(uf_flatten, bn, t256, 0, s, par, n, root, flag);
-    SA_HIP(hipGetLastError());
-    SA_HIP(prefix_sums(flag, n, A.get<int64_t>(o_sums), num, s));
     int64_t nc = 0;
-    SA_HIP(hipMemcpyAsync(&nc, num + n, 8, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipStreamSynchronize(s));
+    if (small) {
+        const int rc = copy_rows();
+        if (rc != SA_OK) return rc;
+        nc = host_components(hadj, n, R, hcomp);
+    }
+    if (!small || nc > 1)
+        if (A.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+    int32_t *par = A.get<int32_t>(o_par);
+    if (!small) {
+        int32_t *const root = A.get<int32_t>(o_root), *const flag = A.get<int32_t>(o_flag);
+        int64_t *const num = A.get<int64_t>(o_num);
+        hipLaunchKernelGGL(uf_init, bn, t256, 0, s, par, n);
+        hipLaunchKernelGGL(uf_hook, dim3(blocks_for(ne, 256)), t256, 0, s, adj_dev, n, R, par);
+        hipLaunchKernelGGL(uf_flatten, bn, t256, 0, s, par, n, root, flag);
+        SA_HIP(hipGetLastError());
+        SA_HIP(prefix_sums(flag, n, A.get<int64_t>(o_sums), num, s));
+        SA_HIP(hipMemcpyAsync(&nc, num + n, 8, hipMemcpyDeviceToHost, s));
+        SA_HIP(hipStreamSynchronize(s));
+    }
     if (ncomp_out) *ncomp_out = nc;
 
     // (2) gateway rows for the representatives (each component's medoid), the entry and the
@@ -878,10 +927,16 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
     RowsBack back(adj_dev, R, s);   // (before D goes)
     if (nc > 1) {
         int32_t *const comp = par;   // (the union-find is done with it)
-        hipLaunchKernelGGL(comp_of, bn, t256, 0, s, root, num, n, comp);
-        std::vector<int32_t> hcomp((size_t)n), members((size_t)n);
-        SA_HIP(hipMemcpyAsync(hcomp.data(), comp, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
-        SA_HIP(hipStreamSynchronize(s));
+        double *const dist = A.get<double>(o_dist);
+        if (small) {
+            SA_HIP(hipMemcpyAsync(comp, hcomp.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+        } else {
+            hipLaunchKernelGGL(comp_of, bn, t256, 0, s, A.get<int32_t>(o_root), A.get<int64_t>(o_num), n, comp);
+            hcomp.resize((size_t)n);
+            SA_HIP(hipMemcpyAsync(hcomp.data(), comp, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+            SA_HIP(hipStreamSynchronize(s));
+        }
+        std::vector<int32_t> members((size_t)n);
         std::vector<int64_t> start((size_t)nc + 1, 0);
         for (int64_t i = 0; i < n; ++i) start[hcomp[i] + 1]++;
         for (int64_t c = 0; c < nc; ++c) start[c + 1] += start[c];
@@ -890,18 +945,17 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
             for (int64_t i = 0; i < n; ++i) members[fill[hcomp[i]]++] = (int32_t)i;
         }
         Arena C;
-        const size_t o_mem = C.want<int32_t>(n), o_start = C.want<int64_t>(nc + 3), o_mean = C.want<double>(nc * d);
+        const size_t o_mem = C.want<int32_t>(n), o_start = C.want<int64_t>(nc + 1), o_mean = C.want<double>((nc + 1) * d);
         const size_t o_best = C.want<unsigned long long>(nc), o_rep = C.want<int32_t>(nc);
         if (C.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
         int32_t *const rep_dev = C.get<int32_t>(o_rep);
         int64_t *const start_dev = C.get<int64_t>(o_start);
         double *const mean = C.get<double>(o_mean);
-        start.push_back(0);   // (after the groups: the one group of all rows)
-        start.push_back(n);
         SA_HIP(hipMemcpyAsync(C.get<int32_t>(o_mem), members.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-        SA_HIP(hipMemcpyAsync(start_dev, start.data(), sizeof(int64_t) * (nc + 3), hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(group_means, dim3((unsigned)nc, (unsigned)dcol), dim3(64), 0, s, base, d, ld, C.get<int32_t>(o_mem),
-                           start_dev, mean);
+        SA_HIP(hipMemcpyAsync(start_dev, start.data(), sizeof(int64_t) * (nc + 1), hipMemcpyHostToDevice, s));
+        const bool want_hubs = hubs > 1;
+        hipLaunchKernelGGL(group_means, dim3((unsigned)(nc + (want_hubs ? 1 : 0)), (unsigned)dcol), dim3(64), 0, s, base, n, d,
+                           ld, C.get<int32_t>(o_mem), start_dev, nc, mean);
         hipLaunchKernelGGL(mean_dists, bn, t256, 0, s, base, n, d, ld, mean, comp, dist);
         hipLaunchKernelGGL(fill_u64_n, dim3(blocks_for(nc, 256)), t256, 0, s, C.get<unsigned long long>(o_best), nc,
                            (unsigned long long)KEY_EMPTY);
@@ -911,12 +965,9 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
         SA_HIP(hipGetLastError());
         std::vector<int32_t> rep((size_t)nc);
         SA_HIP(hipMemcpyAsync(rep.data(), rep_dev, sizeof(int32_t) * nc, hipMemcpyDeviceToHost, s));
-        const bool want_hubs = hubs > 1;
         std::vector<double> hd;
         if (want_hubs) {
-            hipLaunchKernelGGL(group_means, dim3(1, (unsigned)dcol), dim3(64), 0, s, base, d, ld, (const int32_t *)nullptr,
-                               start_dev + nc + 1, mean);
-            hipLaunchKernelGGL(mean_dists, bn, t256, 0, s, base, n, d, ld, mean, (const int32_t *)nullptr, dist);
+            hipLaunchKernelGGL(mean_dists, bn, t256, 0, s, base, n, d, ld, mean + nc * d, (const int32_t *)nullptr, dist);
             SA_HIP(hipGetLastError());
             hd.resize((size_t)n);
             SA_HIP(hipMemcpyAsync(hd.data(), dist, sizeof(double) * n, hipMemcpyDeviceToHost, s));
@@ -980,48 +1031,65 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
 
     // (3) reachability: bridge every unreachable vertex, in id order, from the nearest
     // reachable vertex with a free slot
-    int32_t *const level = root, *const deg = flag, *const changed = A.get<int32_t>(o_chg);
-    uint8_t *const dmask = A.get<uint8_t>(o_mark);
-    hipLaunchKernelGGL(fill_i32, bn, t256, 0, s, level, n, -1);
-    hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, level + entry, (int64_t)1, 0);
-    SA_HIP(hipGetLastError());
-    // A level a launch, eight launches a look at the flag; what is not finished after 128
-    // levels is a long thin graph, which the host walks faster (a level is some 6 us here).
-    bool done = false;
-    for (int32_t cur = 0; !done && cur < 128; cur += 8) {
-        for (int32_t i = 0; i < 8; ++i) {
-            if (i == 7) hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, changed, (int64_t)1, 0);
-            hipLaunchKernelGGL(bfs_level, dim3(blocks_for(n, 256)), t256, 0, s, adj_dev, n, R, level, cur + i, changed);
+    std::vector<uint8_t> mark;
+    if (small) {
+        if (nc > 1) {
+            const int rc = copy_rows();
+            if (rc != SA_OK) return rc;
         }
-        SA_HIP(hipGetLastError());
-        int32_t h = 0;
-        SA_HIP(hipMemcpyAsync(&h, changed, 4, hipMemcpyDeviceToHost, s));
-        SA_HIP(hipStreamSynchronize(s));
-        done = h == 0;
-    }
-    if (!done) {
-        std::vector<int32_t> adj((size_t)ne), lv((size_t)n), walk;
-        SA_HIP(hipMemcpyAsync(adj.data(), adj_dev, sizeof(int32_t) * ne, hipMemcpyDeviceToHost, s));
-        SA_HIP(hipMemcpyAsync(lv.data(), level, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
-        SA_HIP(hipStreamSynchronize(s));
-        for (int64_t v = 0; v < n; ++v)
-            if (lv[v] >= 0) walk.push_back((int32_t)v);
+        mark.assign((size_t)n, 0);
+        std::vector<int32_t> walk(1, entry);
+        mark[entry] = 1;
         for (size_t h = 0; h < walk.size(); ++h)
             for (int r = 0; r < R; ++r) {
-                const int32_t u = adj[(int64_t)walk[h] * R + r];
-                if (u < 0 || u >= n || lv[u] >= 0) continue;
-                lv[u] = 0;
+                const int32_t u = hadj[(int64_t)walk[h] * R + r];
+                if (u < 0 || u >= n || mark[u]) continue;
+                mark[u] = 1;
                 walk.push_back(u);
             }
-        SA_HIP(hipMemcpyAsync(level, lv.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+    } else {
+        int32_t *const level = A.get<int32_t>(o_root), *const changed = A.get<int32_t>(o_chg);
+        hipLaunchKernelGGL(fill_i32, bn, t256, 0, s, level, n, -1);
+        hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, level + entry, (int64_t)1, 0);
+        SA_HIP(hipGetLastError());
+        // A level a launch, eight launches a look at the flag; what is not finished after 128
+        // levels is a long thin graph, which the host walks faster (a level is some 6 us here).
+        bool done = false;
+        for (int32_t cur = 0; !done && cur < 128; cur += 8) {
+            for (int32_t i = 0; i < 8; ++i) {
+                if (i == 7) hipLaunchKernelGGL(fill_i32, dim3(1), dim3(64), 0, s, changed, (int64_t)1, 0);
+                hipLaunchKernelGGL(bfs_level, dim3(blocks_for(n, 256)), t256, 0, s, adj_dev, n, R, level, cur + i, changed);
+            }
+            SA_HIP(hipGetLastError());
+            int32_t h = 0;
+            SA_HIP(hipMemcpyAsync(&h, changed, 4, hipMemcpyDeviceToHost, s));
+            SA_HIP(hipStreamSynchronize(s));
+            done = h == 0;
+        }
+        if (!done) {
+            std::vector<int32_t> adj((size_t)ne), lv((size_t)n), walk;
+            SA_HIP(hipMemcpyAsync(adj.data(), adj_dev, sizeof(int32_t) * ne, hipMemcpyDeviceToHost, s));
+            SA_HIP(hipMemcpyAsync(lv.data(), level, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+            SA_HIP(hipStreamSynchronize(s));
+            for (int64_t v = 0; v < n; ++v)
+                if (lv[v] >= 0) walk.push_back((int32_t)v);
+            for (size_t h = 0; h < walk.size(); ++h)
+                for (int r = 0; r < R; ++r) {
+                    const int32_t u = adj[(int64_t)walk[h] * R + r];
+                    if (u < 0 || u >= n || lv[u] >= 0) continue;
+                    lv[u] = 0;
+                    walk.push_back(u);
+                }
+            SA_HIP(hipMemcpyAsync(level, lv.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+            SA_HIP(hipStreamSynchronize(s));
+        }
+        hipLaunchKernelGGL(level_marks, bn, t256, 0, s, level, n, A.get<uint8_t>(o_mark));
+        hipLaunchKernelGGL(row_degrees, dim3(blocks_for(n, 4)), t256, 0, s, adj_dev, n, R, 0, A.get<int32_t>(o_flag));
+        SA_HIP(hipGetLastError());
+        mark.resize((size_t)n);
+        SA_HIP(hipMemcpyAsync(mark.data(), A.get<uint8_t>(o_mark), n, hipMemcpyDeviceToHost, s));
         SA_HIP(hipStreamSynchronize(s));
     }
-    hipLaunchKernelGGL(level_marks, bn, t256, 0, s, level, n, dmask);
-    hipLaunchKernelGGL(row_degrees, dim3(blocks_for(n, 4)), t256, 0, s, adj_dev, n, R, 0, deg);
-    SA_HIP(hipGetLastError());
-    std::vector<uint8_t> mark((size_t)n);
-    SA_HIP(hipMemcpyAsync(mark.data(), dmask, n, hipMemcpyDeviceToHost, s));
-    SA_HIP(hipStreamSynchronize(s));
     std::vector<int32_t> lost;   // unreachable vertices, in id order
     for (int64_t v = 0; v < n; ++v)
         if (!mark[v]) lost.push_back((int32_t)v);
@@ -1032,6 +1100,9 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
         const int64_t nl = (int64_t)lost.size();
         constexpr int WIN = 256;
         constexpr size_t MAX_NEW = 4096;
+        if (!A.p && A.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
+        int32_t *const deg = A.get<int32_t>(o_flag);
+        uint8_t *const dmask = A.get<uint8_t>(o_mark);
         std::vector<int32_t> hdeg((size_t)n), lrow((size_t)nl * R);
         std::vector<float> lvec((size_t)nl * d);
         Arena G;
@@ -1040,7 +1111,10 @@ int repair_device(const float *base, int64_t n, int d, int64_t ld, int metric, i
         if (G.alloc() != hipSuccess) return set_error(SA_ENOMEM, "repair: device allocation failed");
         int32_t *const ids = G.get<int32_t>(o_ids), *const dus = G.get<int32_t>(o_us);
         unsigned long long *const dres = G.get<unsigned long long>(o_res);
-        SA_HIP(hipMemcpyAsync(hdeg.data(), deg, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+        if (small)
+            for (int64_t e = 0; e < ne; ++e) hdeg[e / R] += hadj[e] >= 0 ? 1 : 0;
+        else
+            SA_HIP(hipMemcpyAsync(hdeg.data(), deg, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
         SA_HIP(hipMemcpyAsync(ids, lost.data(), sizeof(int32_t) * nl, hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(gather_rows, dim3(blocks_for(nl * R, 256)), t256, 0, s, adj_dev, (int64_t)R, R, ids, nl,
                            G.get<int32_t>(o_rows));

@@ -55,3 +55,49 @@ def test_more_rows_than_a_launch_has_wavefronts():
     assert adj[inner, some].item() == (inner - 1) // R
     info = B.repair(base, adj, 0)
     assert tuple(info) == (0, 1)
+
+
+# 4,096 rows of 32 are the largest whose components and reachability come from the host
+@pytest.mark.parametrize("n", [4096, 4097, 7000])
+@pytest.mark.parametrize("groups,gone", [(1, 0), (1, 60), (3, 25), (90, 200)])
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+def test_repair_host_and_device(n, groups, gone, metric):
+    from paper_2201_13007_amd import binding as B
+    R = 32
+    rng = np.random.default_rng([n, groups, gone])
+    base = rng.standard_normal((n, 12)).astype(np.float32)
+    label = rng.integers(0, groups, n)
+    label[:groups] = np.arange(groups)
+    adj = np.full((n, R), -1, np.int32)
+    for c in range(groups):
+        m = np.flatnonzero(label == c)
+        if len(m) > 1:
+            adj[m, 0] = np.roll(m, -1)
+            adj[m, 1] = np.roll(m, -len(m) // 2)
+            adj[m, 2] = rng.permutation(m)
+    adj[np.isin(adj, rng.choice(n, gone, replace=False))] = -1    # nobody points there
+    adj = np.take_along_axis(adj, np.argsort(adj < 0, axis=1, kind="stable"), axis=1)
+    entry = oracle.medoid(base)
+    want = adj.copy()
+    wb, wc = oracle.repair(base, want, entry, keep_local=1, hubs=9, hub_keep_local=2, metric=metric)
+    g = torch.from_numpy(adj).cuda()
+    print(f"case: n={n} groups={groups} gone={gone} {metric} bridges={wb} components={wc}", flush=True)
+    assert B.repair(torch.from_numpy(base).cuda(), g, entry, keep_local=1, metric=metric, hubs=9, hub_keep_local=2) == (wb, wc)
+    np.testing.assert_array_equal(g.cpu().numpy(), want)
+
+
+# a prefix sum of up to 2,048 counts is one launch
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 6000])
+def test_reverse_edges_chunks(n):
+    from paper_2201_13007_amd import binding as B
+    rng = np.random.default_rng(n)
+    base = rng.integers(-3, 4, (n, 4)).astype(np.float32)
+    adj = rng.integers(0, n, (n, 6)).astype(np.int32)
+    adj[:, 2:] = -1
+    adj[:, 1] = np.where(adj[:, 1] == adj[:, 0], -1, adj[:, 1])
+    want = adj.copy()
+    wa = oracle.reverse_edges(base, want)
+    g = torch.from_numpy(adj).cuda()
+    print(f"case: reverse edges n={n} added={wa}", flush=True)
+    assert B.reverse_edges(torch.from_numpy(base).cuda(), g) == wa
+    np.testing.assert_array_equal(g.cpu().numpy(), want)
