@@ -141,7 +141,7 @@ void search_table_log2(const sa_search_params &p, int32_t L, int32_t M, int32_t 
 // Register-queue slots per lane the search kernels are compiled for: ceil(L / 64)
 // rounded up: for one walker (the single-worker kernel) to 1, 2, ..., 8 or 16, for more
 // (the general kernel) to 1, 2, 4, 6, 8 or 16.
-inline int queue_slots_bucket(int L, int M)
+__host__ __device__ inline int queue_slots_bucket(int L, int M)
 {
     const int ni = (L + 63) / 64;
     if (M == 1 && ni <= 8) return ni < 1 ? 1 : ni;

@@ -41,13 +41,23 @@
 #include "search_queue.h"
 #include "search_visited.h"
 
+#include <algorithm>
 #include <atomic>
+#include <climits>
 
 namespace sa {
 namespace search_detail {
 
 constexpr int MAXW = 16;
 constexpr int PUBCAP = 512;   // new keys published per round of a merge
+
+// Room for them: no more than the workers can have (the 1 KB less at L <= 64 lets a fourth
+// query of three workers into a CU).
+__host__ __device__ inline uint32_t pub_room(int L, int M)
+{
+    const int all = 64 * M * (queue_slots_bucket(L, 2) + 1);
+    return (uint32_t)(all < PUBCAP ? all : PUBCAP);
+}
 
 struct Ctrl {
     int32_t U[MAXW];
@@ -72,7 +82,7 @@ __host__ __device__ inline MultiLds multi_lds(int L, int M, int lpv, int llog2)
     const uint32_t Lp = (uint32_t)(L + 63) / 64 * 64;
     uint32_t o = 0;
     Y.o_key = o; o += 8u * 2u * Lp;
-    Y.o_pub = o; o += 8u * PUBCAP;
+    Y.o_pub = o; o += 8u * pub_room(L, M);
     Y.o_stage = o; o += 8u * 66u * M;   // a worker's new keys, then its insert
     Y.o_un = o; o += 8u * 16u;
     Y.o_ids = o; o += 4u * 64u * M;
@@ -335,7 +345,7 @@ __device__ __forceinline__ void multi_body(const KArgs &A, int64_t job, int64_t 
     const MultiLds Y = multi_lds(A.L, M, LPV, A.llog2);
     uint64_t *S = reinterpret_cast<uint64_t *>(smem + Y.o_key);
     uint64_t *Sn = S + (A.L + 63) / 64 * 64;
-    uint64_t *const pub = reinterpret_cast<uint64_t *>(smem + Y.o_pub);            // [PUBCAP]
+    uint64_t *const pub = reinterpret_cast<uint64_t *>(smem + Y.o_pub);            // [pub_room]
     uint64_t *const stage = reinterpret_cast<uint64_t *>(smem + Y.o_stage) + 66 * w;
     uint64_t *const un = reinterpret_cast<uint64_t *>(smem + Y.o_un);              // [16] unchecked entries of S
     int32_t *const claimed_ids = reinterpret_cast<int32_t *>(smem + Y.o_ids) + 64 * w;
@@ -802,14 +812,14 @@ __device__ __forceinline__ void multi_body(const KArgs &A, int64_t job, int64_t 
     }
 }
 
-// Workgroup b runs job b in workspace region b.  Three forms, by the wavefronts that a SIMD
-// can hold and the registers that this leaves to the gathers: 2 (up to eight workers only),
-// 4 and 8.
-template <int LPV, int NI, int DT, int WAVES>
-__global__ void __launch_bounds__(WAVES == 2 ? 512 : 1024) __attribute__((amdgpu_waves_per_eu(WAVES)))
+// Workgroup b runs job b in workspace region b.  WAVES: wavefronts that a SIMD can hold, which
+// bounds the registers (five: up to four workers only, two or three: up to eight); PB: vectors per lane group in
+// flight in a gather pass.
+template <int LPV, int NI, int DT, int WAVES, int PB>
+__global__ void __launch_bounds__(WAVES == 5 ? 256 : WAVES <= 3 ? 512 : 1024) __attribute__((amdgpu_waves_per_eu(WAVES)))
 search_multi(KArgs A)
 {
-    multi_body<LPV, NI, DT, WAVES == 2 ? 8 : (WAVES == 4 ? 2 : 1)>(A, blockIdx.x, blockIdx.x);
+    multi_body<LPV, NI, DT, PB>(A, blockIdx.x, blockIdx.x);
 }
 
 // Persistent form: each resident workgroup takes jobs from the device counter until none
@@ -831,13 +841,16 @@ __global__ void __launch_bounds__(1024) search_multi_loop(KArgs A)
     if (threadIdx.x == 0) release_jobs(A.jobctr);
 }
 
-// Launches the kernel k of form `form`.  only_resident: unless some queries would have to wait
-// for others to end; *taken tells.
-inline hipError_t launch_multi_form(const void *k, std::atomic<uint64_t> &raised, const KArgs &A, uint32_t lds,
-                                    int64_t nq, bool only_resident, hipStream_t s, bool *taken)
+// A kernel of a launch and how many of its queries the device can hold at once.
+struct MultiForm {
+    const void *k;
+    int64_t slots;
+};
+
+// Raises the dynamic LDS limit of kernel k to the whole 160 KB, once per kernel and device, not
+// on every launch (the latency path launches one query at a time), and asks for its slots.
+inline hipError_t multi_form(const void *k, std::atomic<uint64_t> &raised, const KArgs &A, uint32_t lds, MultiForm *f)
 {
-    // the dynamic LDS limit is raised to the whole 160 KB once per kernel and device, not
-    // on every launch (the latency path launches one query at a time)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -847,48 +860,81 @@ inline hipError_t launch_multi_form(const void *k, std::atomic<uint64_t> &raised
         if (e != hipSuccess) return e;
         raised.fetch_or(bit, std::memory_order_acq_rel);
     }
-    int64_t grid = nq;
-    if (A.jobctr || only_resident) {
-        const int64_t all = A.jobctr ? nq : nq + A.company;
-        e = resident_grid(k, 64 * A.M, lds, all, &grid);
-        if (e != hipSuccess) return e;
-        *taken = !only_resident || grid >= all;
-        if (!*taken) return hipSuccess;
-        if (!A.jobctr) grid = nq;
-    }
-    *taken = true;
-    KArgs B = A;
-    void *args[] = {&B};
-    return hipLaunchKernel(k, dim3((unsigned)grid), dim3(64 * A.M), args, lds, s);
+    f->k = k;
+    // (beyond four wavefronts a workgroup takes as many of each SIMD as of its fullest: at three
+    // waves per SIMD a CU holds one workgroup of five, not two)
+    return resident_grid(k, A.M <= 4 ? 64 * A.M : (A.M + 3) / 4 * 256, lds, INT32_MAX, &f->slots);
 }
 
-// Up to four workers always take the registers; up to eight do while all queries are then
-// resident at once, and take half of them beyond; more workers take half while resident and
-// a quarter beyond.  Where the LDS of a query (its visited table at large L) leaves room for
-// one workgroup per CU anyway, fewer registers gain nothing.  Over 200K x 128, adaptive, us:
-// 4 workers, 1,000 queries, L = 128: 624 (2 waves per SIMD) against 762 (8); 8 workers,
-// 1,000 queries, L = 128: 897 (2), 574 (4), 673 (8); 16 workers, 1,000 queries, L = 128:
-// 1,208 (4), 1,050 (8).
+// The form of a launch.  Fewer registers let more queries run at once, and make each slower.
+//   Up to four workers: three waves per SIMD (at 64 < L <= 128 the compiler stays at that when
+// allowed two, and is 1-4% faster), unless the launch takes fewer rounds of the chip at five (at
+// L <= 64: four, or five).
+// That is so for two workers, who have no LDS table; with more, the table leaves a CU three or
+// four queries either way.  200K x 128, adaptive, us at 2 / 3 / 5 waves: two workers, L = 192,
+// 1,000 queries 1,192 / 1,164 / 1,220, 2,500 2,398 / 1,833 / 1,519, 10,000 6,696 / 4,912 / 3,928;
+// four workers, L = 192, 1,000 queries 955 / 907 / 960, 10,000 7,252 / 5,010 / 5,291.  (Two waves
+// whatever the launch had cost full batches of up to four workers a tenth to a third.)
+//   Five to eight workers take those registers while all queries are then resident at once, and
+// four waves beyond; more workers four waves while resident and eight beyond.  Where the LDS of a
+// query (its visited table at large L) leaves room for one workgroup per CU anyway, fewer
+// registers gain nothing.  1,000 queries, L = 128: 8 workers 850 (3 waves), 539 (4), 673 (8);
+// 16 workers 1,054 (4), 966 (8).
+//   Two waves, with eight vectors in flight, only while all queries are resident, at L > 384 or
+// d > 256: 33 queries, four workers, L = 768 2,147 (2) against 2,260 (3); 300 of d = 960, L = 64
+// 241 against 250.
+//   Four waves with two vectors in flight spill five to ten registers at L <= 256 (25 at 512);
+// with one none, but eight workers at L = 64 are 9% slower then (704 / 780 us).
 template <int LPV, int NI, int DT>
 hipError_t launch_multi(const KArgs &A, int64_t nq, hipStream_t s)
 {
-    static std::atomic<uint64_t> raised[4] = {{0}, {0}, {0}, {0}};
+    static std::atomic<uint64_t> raised[6] = {{0}, {0}, {0}, {0}, {0}, {0}};
     const uint32_t lds = multi_lds(A.L, A.M, LPV, A.llog2).total;
-    bool taken = false;
-    hipError_t e = hipSuccess;
-    if (A.jobctr)
-        return launch_multi_form(reinterpret_cast<const void *>(search_multi_loop<LPV, NI, DT>), raised[0], A, lds, nq,
-                                 false, s, &taken);
-    if (A.M <= 8)
-        e = launch_multi_form(reinterpret_cast<const void *>(search_multi<LPV, NI, DT, 2>), raised[1], A, lds, nq,
-                              A.M > 4 && lds <= 80u * 1024u, s, &taken);
-    if (e == hipSuccess && !taken)
-        e = launch_multi_form(reinterpret_cast<const void *>(search_multi<LPV, NI, DT, 4>), raised[2], A, lds, nq,
-                              A.M > 8 && lds <= 80u * 1024u, s, &taken);
-    if (e == hipSuccess && !taken)
-        e = launch_multi_form(reinterpret_cast<const void *>(search_multi<LPV, NI, DT, 8>), raised[3], A, lds, nq,
-                              false, s, &taken);
-    return e;
+    const int64_t all = nq + A.company;
+    const auto form = [&](auto k, int i, MultiForm *f) {
+        return multi_form(reinterpret_cast<const void *>(k), raised[i], A, lds, f);
+    };
+    const auto launch = [&](const MultiForm &f, int64_t grid) {
+        KArgs B = A;
+        void *args[] = {&B};
+        return hipLaunchKernel(f.k, dim3((unsigned)grid), dim3(64 * A.M), args, lds, s);
+    };
+    constexpr bool TWO = LPV >= 32 || NI >= 8;
+    const bool one_a_cu = lds > 80u * 1024u;
+    MultiForm f, g;
+    hipError_t e;
+    if (A.jobctr) {
+        e = form(search_multi_loop<LPV, NI, DT>, 0, &f);
+        return e == hipSuccess ? launch(f, std::min(nq, f.slots)) : e;
+    }
+    if constexpr (TWO) {
+        if (A.M <= 8) {
+            e = form(search_multi<LPV, NI, DT, 2, 8>, 1, &f);
+            if (e != hipSuccess) return e;
+            if (all <= f.slots || one_a_cu) return launch(f, nq);
+        }
+    }
+    if (A.M <= (TWO ? 4 : 8)) {
+        e = form(search_multi<LPV, NI, DT, NI == 2 ? 2 : 3, 4>, 2, &f);
+        if (e != hipSuccess) return e;
+        if (all <= f.slots || one_a_cu) return launch(f, nq);
+    }
+    if (A.M <= 4) {
+        const auto rounds = [&](const MultiForm &x) { return (all + x.slots - 1) / x.slots; };
+        if constexpr (NI == 1) {
+            e = form(search_multi<LPV, NI, DT, 4, 2>, 4, &g);
+            if (e != hipSuccess) return e;
+            if (rounds(g) < rounds(f)) f = g;
+        }
+        e = form(search_multi<LPV, NI, DT, NI <= 8 ? 5 : 4, 1>, 3, &g);
+        if (e != hipSuccess) return e;
+        return launch(rounds(g) < rounds(f) ? g : f, nq);
+    }
+    e = form(search_multi<LPV, NI, DT, 4, 2>, 4, &f);
+    if (e != hipSuccess) return e;
+    if (A.M <= 8 || all <= f.slots || one_a_cu) return launch(f, nq);
+    e = form(search_multi<LPV, NI, DT, 8, 1>, 5, &f);
+    return e == hipSuccess ? launch(f, nq) : e;
 }
 
 template <int LPV, int DT, bool LARGE>
