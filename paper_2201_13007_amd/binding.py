@@ -178,12 +178,12 @@ def _scratch(nbytes: int, device, stream=None):
     KEEP_SCRATCH or where there is none left."""
     if not 0 < nbytes <= KEEP_SCRATCH:
         return None
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    elif not isinstance(stream, torch.cuda.Stream):    # any object with a stream's handle will do
-        h = int(stream.cuda_stream)
-        stream = torch.cuda.ExternalStream(h, device=device) if h else torch.cuda.default_stream(device)
     try:
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if not isinstance(stream, torch.cuda.Stream):    # any object with a stream's handle will do
+            h = int(stream.cuda_stream)
+            stream = torch.cuda.ExternalStream(h, device=device) if h else torch.cuda.default_stream(device)
         with torch.cuda.stream(stream):
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:

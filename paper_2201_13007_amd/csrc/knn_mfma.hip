@@ -111,24 +111,6 @@ __global__ void __launch_bounds__(256) knn_prep_kernel(PrepArgs P)
     }
 }
 
-// Results of the integer form: the first k of each query's list; the queries whose buffers
-// overflowed are listed for the scan.
-__global__ void knn_emit_kernel(const uint64_t *list, int kt, const int32_t *over, int64_t nq, int64_t q0, int k,
-                                int32_t *ids, float *dists, int32_t *failed, int32_t *failed_list)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nq * k) return;
-    const int64_t q = i / k, j = i - q * k;
-    if (over[q]) {
-        if (j == 0) failed_list[atomicAdd(failed, 1)] = (int32_t)(q0 + q);
-        return;
-    }
-    const uint64_t key = list[q * kt + j];
-    const bool ok = key != KEY_EMPTY;
-    ids[(q0 + q) * k + j] = ok ? key_id(key) : -1;
-    dists[(q0 + q) * k + j] = ok ? key_dist(key) : __builtin_inff();
-}
-
 // ---------------------------------------------------------------- stages (host)
 
 struct Stage {
@@ -148,13 +130,17 @@ constexpr int QCHUNK = 65536;   // queries per pass over the base: bounds the bu
 //   A workgroup takes 256 queries where that leaves 512 workgroups (two per CU), else 128
 // or 64 (the stages of few tiles); a stage is split over two to four times the workgroups
 // that the device holds (1024 to 2048), which bounds what an uneven last round costs.
-//   From 256 queries up a wavefront selects per query, below a workgroup does.
+//   From 256 queries up a wavefront selects per query, below a workgroup does (mostly: see `one`).
 std::vector<Stage> plan_stages(int ntile, int kt, int64_t nq, bool wide)
 {
     std::vector<Stage> st;
     const bool many = nq >= 4096;
     const int unit = wide ? 2 : 1;
-    const int m0 = std::min(ntile, many && kt <= 64 ? 4 : many && kt <= 128 ? 8 : 16);
+    // Few queries over a base of up to 2048 rows: one stage.  From lists of up to 64 a wavefront
+    // selects there too.  One query over 1,100 x 128 integers, k = 1: 102 us in two stages, 97 in
+    // one, 72 with the wavefront; 100 over 2,000 x 512 floats: 224 and 192.
+    const bool one = nq < 256 && ntile <= 32;
+    const int m0 = one ? ntile : std::min(ntile, many && kt <= 64 ? 4 : many && kt <= 128 ? 8 : 16);
     const double rmax = std::min(many ? 6.0 : 16.0, std::max(3.0, 1024.0 / kt));
     const double ratio = (double)ntile / m0;
     const int ns = ratio > 1.0 ? std::max(1, (int)std::ceil(std::log(ratio) / std::log(rmax))) : 0;
@@ -180,7 +166,7 @@ std::vector<Stage> plan_stages(int ntile, int kt, int64_t nq, bool wide)
             s.capseg = std::min(most, ((int)(mu + 6.0 * std::sqrt(mu) + 16.0) + 1) / 2 * 2);
             keys = kt + all + 6.0 * std::sqrt(all);
         }
-        if (nq >= 256 && s.splits <= 256) {
+        if ((nq >= 256 || (one && kt <= 64)) && s.splits <= 256) {
             s.lane_keys = 4;
             while (s.lane_keys < 32 && 64 * s.lane_keys < keys) s.lane_keys *= 2;
         }
@@ -235,8 +221,9 @@ SKernel pick_select(int lane_keys)
 
 // The stages of one chunk of queries (A holds everything but the stage's own fields).
 // lds_wq: bytes of LDS of the product kernel per 64 queries of its workgroup, on top of lds0
+// out: where the last selection leaves results (ids null: nowhere)
 int run_stages(TileArgs A, const std::vector<Stage> &st, const Kernels &kern, size_t lds0, size_t lds_wq, int kt,
-               uint64_t *list, uint64_t *thr, int32_t *over, hipStream_t s)
+               uint64_t *list, uint64_t *thr, int32_t *over, const SelArgs &out, hipStream_t s)
 {
     bool first = true;
     int sort_cap = 64;
@@ -247,7 +234,8 @@ int run_stages(TileArgs A, const std::vector<Stage> &st, const Kernels &kern, si
         const int64_t jobs = (int64_t)g.splits * A.qtiles, per = (jobs + 7) / 8;
         hipLaunchKernelGGL(kern.of(g.wq), dim3((unsigned)(8 * per)), dim3(MNT), lds0 + lds_wq * g.wq, s, A);
         SA_HIP(hipGetLastError());
-        SelArgs S;
+        SelArgs S = out;
+        if (&g != &st.back()) S.ids = nullptr;
         S.buf = A.buf; S.cnt = A.cnt; S.splits = g.splits; S.capseg = g.capseg;
         S.dense_rows = A.dense ? (g.t1 - g.t0) * TROWS : 0;
         S.kt = kt; S.nq = A.nq; S.first = first ? 1 : 0;
@@ -659,13 +647,13 @@ int run_integer(const Plan &P, const Call &c, unsigned char *m, bool *ran)
         const int64_t cn = std::min(P.qc, c.nq - q0);
         if (c.nq > P.qc) SA_HIP(prep(c.queries + q0 * c.ldq, cn, c.ldq, P.qpad, 0, qt, qn, nullptr));
         A.q0 = q0; A.nq = (int32_t)cn;
-        const int rc = run_stages(A, P.st, kern, tile_lds(P), tile_lds_wq(P), P.kt, list, thr, over, s);
+        SelArgs out{};
+        out.ids = c.ids; out.dists = c.dists; out.q0 = q0; out.k = c.k; out.failed = flags + 1; out.failed_list = failed_list;
+        const int rc = run_stages(A, P.st, kern, tile_lds(P), tile_lds_wq(P), P.kt, list, thr, over, out, s);
         if (rc != SA_OK) return rc;
-        hipLaunchKernelGGL(knn_emit_kernel, dim3((unsigned)((cn * c.k + 255) / 256)), dim3(256), 0, s, list, P.kt, over, cn,
-                           q0, c.k, c.ids, c.dists, flags + 1, failed_list);
-        SA_HIP(hipGetLastError());
     }
-    SA_HIP(hipMemcpyAsync(hf, flags, 16, hipMemcpyDeviceToHost, s));
+    // (one stage: every distance was kept, none can have overflowed)
+    if (P.st.size() > 1) SA_HIP(hipMemcpyAsync(hf, flags, 16, hipMemcpyDeviceToHost, s));
     SA_HIP(hipStreamSynchronize(s));
     *ran = true;
     return hf[1] > 0 ? rescan(c, hf[1], failed_list) : SA_OK;
@@ -716,7 +704,7 @@ int run_float(const Plan &P, const Call &c, unsigned char *m, bool *ran)
         const int64_t cn = std::min(P.qc, c.nq - q0);
         SA_HIP(prep(c.queries + q0 * c.ldq, cn, c.ldq, P.qpad, false));
         A.q0 = q0; A.nq = (int32_t)cn;
-        const int rc = run_stages(A, P.st, kern, tile_lds(P), tile_lds_wq(P), P.kt, list, thr, over, s);
+        const int rc = run_stages(A, P.st, kern, tile_lds(P), tile_lds_wq(P), P.kt, list, thr, over, SelArgs{}, s);
         if (rc != SA_OK) return rc;
         EArgs E{c.base, c.n, c.ld, c.queries, q0, c.ldq, c.d, c.k, P.kt, c.metric, c.exclude_self, list, over,
                 reinterpret_cast<float *>(m + P.o_qn), flags, c.ids, c.dists, failed, failed_list};

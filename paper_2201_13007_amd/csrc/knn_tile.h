@@ -367,7 +367,30 @@ struct SelArgs {
     uint64_t *list;                       // [query][kt] smallest keys so far, sorted (KEY_EMPTY past the end)
     uint64_t *thr;
     int32_t *over;                        // per query: a buffer overflowed
+    // last stage of the integer form (ids null otherwise): the first k keys are the results of
+    // query q0 + q; queries whose buffers overflowed are listed for the scan instead
+    int32_t *ids;
+    float *dists;
+    int64_t q0;
+    int32_t k;
+    int32_t *failed, *failed_list;
 };
+
+__device__ __forceinline__ void put_result(const SelArgs &S, int64_t q, int i, uint64_t key)
+{
+    if (!S.ids || i >= S.k) return;
+    const bool ok = key != KEY_EMPTY;
+    S.ids[(S.q0 + q) * S.k + i] = ok ? key_id(key) : -1;
+    S.dists[(S.q0 + q) * S.k + i] = ok ? key_dist(key) : __builtin_inff();
+}
+
+// one lane: the query's buffer overflowed
+__device__ __forceinline__ void give_up(const SelArgs &S, int64_t q)
+{
+    S.over[q] = 1;
+    S.thr[q] = 0ull;   // (answered elsewhere: nothing more passes for this query)
+    if (S.ids) S.failed_list[atomicAdd(S.failed, 1)] = (int32_t)(S.q0 + q);
+}
 
 // sorts the P (a power of two) keys of LDS array a, ascending, with the whole workgroup
 __device__ __forceinline__ void sort_lds(uint64_t *a, int P)
@@ -446,10 +469,7 @@ __global__ void __launch_bounds__(256) knn_select_wave_kernel(SelArgs S)
         }
         const int total = __builtin_amdgcn_readlane(inc, 63);
         if (__ballot(over) != 0 || total + S.kt > 64 * NK || (!S.first && S.over[q])) {
-            if (lane == 0) {
-                S.over[q] = 1;
-                S.thr[q] = 0ull;
-            }
+            if (lane == 0) give_up(S, q);
             return;
         }
         int base = inc - sum;
@@ -520,7 +540,11 @@ __global__ void __launch_bounds__(256) knn_select_wave_kernel(SelArgs S)
     while (P < n) P <<= 1;
     for (int i = n + lane; i < P; i += 64) a[i] = KEY_EMPTY;
     sort_lds_wave(a, P);
-    for (int i = lane; i < S.kt; i += 64) S.list[q * S.kt + i] = i < P ? a[i] : KEY_EMPTY;
+    for (int i = lane; i < S.kt; i += 64) {
+        const uint64_t v = i < P ? a[i] : KEY_EMPTY;
+        S.list[q * S.kt + i] = v;
+        put_result(S, q, i, v);
+    }
     if (lane == 0) {
         S.thr[q] = S.kt <= n ? a[S.kt - 1] : KEY_EMPTY;
         if (S.first) S.over[q] = 0;
@@ -570,11 +594,7 @@ __global__ void __launch_bounds__(256) knn_select_kernel(SelArgs S)
         if (total + S.kt > SELCAP && tid == 0) over = 1;
         __syncthreads();
         if (over) {
-            // answered elsewhere: nothing more passes for this query
-            if (tid == 0) {
-                S.over[q] = 1;
-                S.thr[q] = 0ull;
-            }
+            if (tid == 0) give_up(S, q);
             return;
         }
         for (int i = tid; i < total; i += 256) {
@@ -593,7 +613,11 @@ __global__ void __launch_bounds__(256) knn_select_kernel(SelArgs S)
     while (P < total) P <<= 1;
     for (int i = total + tid; i < P; i += 256) a[i] = KEY_EMPTY;
     sort_lds(a, P);
-    for (int i = tid; i < S.kt; i += 256) S.list[(int64_t)q * S.kt + i] = i < P ? a[i] : KEY_EMPTY;
+    for (int i = tid; i < S.kt; i += 256) {
+        const uint64_t v = i < P ? a[i] : KEY_EMPTY;
+        S.list[(int64_t)q * S.kt + i] = v;
+        put_result(S, q, i, v);
+    }
     if (tid == 0) {
         S.thr[q] = S.kt <= P ? a[S.kt - 1] : KEY_EMPTY;
         if (S.first) S.over[q] = 0;
