@@ -134,24 +134,26 @@ int sa_knn(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float 
  *   SA_KNN_SCAN  double-precision accumulation on the vector units, any float data.
  *   SA_KNN_MFMA  bf16 matrix-core products, in one of two forms.
  *                Integer-valued data (every base and query coordinate an integer in
- *                [-255, 255], d <= 256, k <= 128): the coordinates, products and partial
+ *                [-255, 255], d <= 256): the coordinates, products and partial
  *                sums are all exact (each sum stays below 2^24 in magnitude), the squared
  *                distance |q|^2 + |x|^2 - 2 q.x is formed in 32-bit integers and rounded
  *                once to float32, and the keys equal the double-precision ones bit for bit.
- *                Other finite float data (d <= 1024, k <= 96): coordinates split into bf16
+ *                Other finite float data (d <= 1024): coordinates split into bf16
  *                high and low parts, three products per block give approximate distances
  *                within a proven bound (L2 data are first moved by the base mean, which
- *                leaves distances unchanged), each query keeps its 128 best candidates (k + 32 or more
- *                above k = 96), and a
- *                second kernel rescores them with the scan's double-precision arithmetic;
- *                where the bound shows that no other point can enter a query's k best,
- *                its row is the scan's bit for bit, and the queries for which it cannot
- *                (many distances tied within the bound) are rescored by the scan alone
+ *                leaves distances unchanged), each query keeps its 128 best candidates (k + 32
+ *                or more above k = 96), and a second kernel rescores them with the scan's
+ *                double-precision arithmetic; where the bound shows that no other point can
+ *                enter a query's k best, its row is the scan's bit for bit, and the queries
+ *                for which it cannot (many distances tied within the bound) are rescored by
+ *                the scan alone
  *                (sa_knn_last_rescanned counts them).  Either form copies
  *                base and queries to temporary bf16 arrays (hipMalloc, freed before
  *                returning; see sa_knn_ws) and checks the values on the device first.
+ *                Asked for by name it takes k <= 128 (integer data) or k <= 96.
  *   SA_KNN_AUTO  SA_KNN_MFMA when a form applies and succeeds, else SA_KNN_SCAN.  From 2048
- *                base rows up the forms apply to every k up to 256. */
+ *                base rows up the forms apply to every k up to 256; a call that only this
+ *                larger k lets in runs the scan where memory for the copies is short. */
 typedef enum { SA_KNN_AUTO = 0, SA_KNN_SCAN = 1, SA_KNN_MFMA = 2 } sa_knn_path;
 
 /* sa_knn with an explicit path.  SA_KNN_MFMA on data or shapes it cannot take exactly
@@ -163,8 +165,10 @@ int sa_knn_ex(const float *base_dev, int64_t n, int32_t d, int64_t ld, const flo
 
 /* sa_knn_ex in device memory of the caller's (256-byte aligned, any contents; NULL: allocated
  * for the call, as sa_knn_ex does), for callers whose allocator keeps memory: allocating and
- * freeing it takes some 0.4 ms a call.  sa_knn_workspace_bytes is what a call runs best with
- * (0 where it needs none); with less, its queries go in smaller chunks, and SA_ECAPACITY is
+ * freeing large ones takes some 0.4 ms a call.  sa_knn_workspace_bytes is what a call runs best
+ * with (0 where it needs none): the copies (2 bytes a coordinate for the integer form, 4 for the
+ * float one, d rounded up to 32) and buffers that grow with the queries of a chunk, 0.65 to
+ * 1.3 GB at its 65,536.  With less, the queries go in smaller chunks, and SA_ECAPACITY is
  * returned if not even a small chunk fits. */
 size_t sa_knn_workspace_bytes(int64_t n, int32_t d, int64_t nq, int32_t k, int32_t path);
 int sa_knn_ws(const float *base_dev, int64_t n, int32_t d, int64_t ld, const float *queries_dev, int64_t nq,

@@ -198,8 +198,9 @@ def knn(base: torch.Tensor, queries: torch.Tensor, k: int, metric="l2", exclude_
     """Exact top-k by (distance, id) over all rows of base (linear scan on the GPU).
 
     path: "scan" (double precision, any data), "mfma" (bf16 matrix cores: integer-valued
-    data, or finite floats with d <= 1024 and k <= 96; exact either way), "auto" (mfma
-    where it applies).  With return_path the path that ran is returned as a third value."""
+    data with d <= 256 and k <= 128, or finite floats with d <= 1024 and k <= 96; exact either
+    way), "auto" (mfma where it applies, from 2048 rows of base up for any k up to 256).  With
+    return_path the path that ran is returned as a third value."""
     base = pad_dim(_mat(base, "base"))
     queries = base if (exclude_self and queries is None) else pad_dim(_mat(queries, "queries"))
     nq = queries.shape[0]

@@ -118,7 +118,7 @@ struct Stage {
     int lane_keys;   // keys per lane of a selection by one wavefront; 0: by a workgroup
 };
 
-constexpr int QCHUNK = 65536;   // queries per pass over the base: bounds the buffers at about half a gigabyte
+constexpr int QCHUNK = 65536;   // queries per pass over the base: bounds the buffers at 0.65 to 1.3 GB (kt = 24 to 320)
 
 // The stages of one pass over the base for nq queries (wide: the 128 x 128 kernel, tile
 // pairs): a first sample of the tiles, then each up to r times as many.  A stage lets

@@ -170,19 +170,6 @@ __device__ __forceinline__ uint64_t min_key(uint64_t k, int *at)
     return rdlane64(k, *at);
 }
 
-// bits [0, n) set, n in [0, 64]
-__device__ __forceinline__ uint64_t low_bits(int n)
-{
-    return n <= 0 ? 0ull : (n >= 64 ? ~0ull : (~0ull >> (64 - n)));
-}
-
-__device__ __forceinline__ uint64_t bpermute64(int addr, uint64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
 // lanes per vector: the smallest power of two that leaves at most four float4 chunks per
 // lane (d <= 1024)
 __host__ __device__ inline int lanes_per_vector(int d)

@@ -17,7 +17,7 @@
 //      it is written to its place in the next S, which is marked in a bit mask
 //   4. the other places are filled from S in order, and the slots' unchecked masks built
 // Few instructions and four barriers a step; bound by the row and the vectors, two dependent
-// round trips to memory.  The general kernel (search_body.h), which this replaced for the
+// round trips to memory.  The general kernel (search_multi.h), which this replaced for the
 // schedule, inserted into every local queue, one key after the other, and ranked each against
 // all other queues behind eight barriers.  Over 1M x 128, one query with 16 workers, L = 176:
 // 291 -> 102 us; over 200K x 128, 1,000 queries with 4 workers, L = 192: 842 -> 237 us; L = 768,

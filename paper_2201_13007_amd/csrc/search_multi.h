@@ -34,8 +34,8 @@
 // the gather and some eight round trips through LDS.  The form before this held every
 // worker's copy of S in registers with a tag per entry: a new key was compared with all of
 // it, a merge reloaded it, and all of it was published.  Over 200K x 128, adaptive: 33 queries
-// with 8 workers, L = 272 636 -> 552 us, L = 500 1,516 -> 1,076; with 16 workers, L = 768
-// 2,038 -> 1,278; 1,000 queries with 4 workers, L = 192 1,130 -> 951.
+// with 8 workers, L = 272 903 -> 793 us, L = 512 1,520 -> 1,093; with 16 workers, L = 768
+// 2,043 -> 1,302; four workers, L = 192, 1,000 queries 1,124 -> 900 and 10,000 5,947 -> 4,997.
 #pragma once
 #include "search_body.h"
 #include "search_queue.h"
