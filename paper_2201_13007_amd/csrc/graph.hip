@@ -469,7 +469,7 @@ __global__ void comp_of(const int32_t *root, const int64_t *number, int64_t n, i
 
 // mean of each group g < nc of rows: members[start[g] .. start[g + 1]), summed in that order, and
 // of the n rows themselves (g = nc); one wavefront per 64 columns and group, all at once: a
-// large group's sum takes 26 ns a row, one addition after the other
+// large group's sum takes some 50 ns a row (1M rows: 52 ms), one addition after the other
 __global__ void __launch_bounds__(64) group_means(const float *base, int64_t n, int d, int64_t ld, const int32_t *members,
                                                   const int64_t *start, int64_t nc, double *mean)
 {
